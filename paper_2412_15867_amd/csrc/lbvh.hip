@@ -892,8 +892,9 @@ hipError_t sort_pairs(int n, uint64_t* k0, uint32_t* v0, uint64_t* k1, uint32_t*
 static size_t ploc_scratch_bytes(int n)
 {
     const size_t nb = static_cast<size_t>(blocks_for(n, kPlocBlock));
+    // eight arrays, each rounded up to 256 bytes by ploc_tree
     return static_cast<size_t>(n) * (2 * (sizeof(int) + 6 * sizeof(float)) + 4 * sizeof(int)) +
-           nb * sizeof(uint32_t) + 256;
+           nb * sizeof(uint32_t) + 2 * sizeof(int) + 8 * 256;
 }
 
 hipError_t lbvh_sort_scratch_bytes(int n, size_t* bytes)
