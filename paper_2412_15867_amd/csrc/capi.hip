@@ -185,18 +185,19 @@ int ovf_slots_of(irgs_scene s)
 }
 
 // Forward scratch: the ray-claim counter heads the deferred-list buffer.
-constexpr size_t kClaimBytes = 256;
+constexpr size_t kClaimBytes = kWaveClaimBytes;
 // Backward without stored hit lists: list capacity of the retrace and the
 // size its batches of lists (ids, T, O, D, n_hits, features) stay within.
 constexpr int kRetraceCap = 256;
 constexpr size_t kRetraceBytes = size_t(4) << 30;
-FlatScratch flat_scratch(void* ovf, int slots, void* dq)
+FlatScratch flat_scratch(void* ovf, int slots, void* dq, int wide_depth)
 {
     FlatScratch f{};
     f.ovf = static_cast<int*>(ovf);
     f.ovf_slots = slots;
     f.next_ray = static_cast<unsigned long long*>(dq);
     f.dbuf = dq ? reinterpret_cast<int*>(static_cast<char*>(dq) + kClaimBytes) : nullptr;
+    f.wide_depth = wide_depth;
     f.defer_cap = kDeferCap;
     f.fixed_words = 0;
     return f;
@@ -536,13 +537,15 @@ irgs_status irgs_trace(irgs_scene s, const irgs_params* p, int64_t R, const floa
     const int slots = bvh ? ovf_slots_of(s) : 0;
     const bool sorted = bvh && (p->flags & IRGS_FLAG_SORT_RAYS) && ray_sort_words(R) > 0;
     AsyncBuf ovf, dq, srt;
-    const size_t thr = static_cast<size_t>(trace_threads(R));
+    // one wave per ray: no scratch but the claim counters
+    const bool lanes = !use_wave_trace(bvh, out->counters != nullptr, s->wide_depth);
+    const size_t thr = lanes ? static_cast<size_t>(trace_threads(R)) : 0;
     hipError_t e = ovf.alloc(thr * slots * sizeof(int), hs);
     if (e == hipSuccess && bvh) e = dq.alloc(kClaimBytes + thr * 2 * kDeferCap * sizeof(int), hs);
     if (e == hipSuccess && sorted) e = srt.alloc(ray_sort_words(R) * sizeof(float), hs);
     if (e != hipSuccess) return hip_fail(e, "trace scratch");
     const SceneView sv = view_of(s);
-    FlatScratch fs = flat_scratch(ovf.p, slots, dq.p);
+    FlatScratch fs = flat_scratch(ovf.p, slots, dq.p, s->wide_depth);
     if (sorted) {
         e = ray_order_by_origin(sv, R, ro, srt.p, &fs.order, hs);
         if (e != hipSuccess) return hip_fail(e, "ray order");
@@ -573,7 +576,7 @@ irgs_status irgs_trace_noalloc(irgs_scene s, const irgs_params* p, int64_t R, co
     char* base = nullptr;
     st = noalloc_scratch_ptr(&base);
     if (st != IRGS_OK) return st;
-    FlatScratch fs = flat_scratch(base + kClaimBytes, slots, base);
+    FlatScratch fs = flat_scratch(base + kClaimBytes, slots, base, s->wide_depth);
     fs.dbuf = nullptr;  // placed by the launch after every thread's overflow slots
     fs.fixed_words = words;
     const hipError_t e = launch_trace(view_of(s), trace_params(p, s->F), p->k, bvh, R, ro, rd, out_ptrs(out), fs,
@@ -629,7 +632,8 @@ irgs_status irgs_trace_backward(irgs_scene s, const irgs_params* p, int64_t R, c
     const bool sorted = bvh && (p->flags & IRGS_FLAG_SORT_RAYS) && ray_sort_words(B) > 0;
     AsyncBuf ovf, dq, ck, lists, srt;
     hipError_t e = ovf.alloc(thr * slots * sizeof(int), hs);
-    if (e == hipSuccess && bvh) e = dq.alloc(kClaimBytes + thr * 2 * kDeferCap * sizeof(int), hs);
+    const size_t lane_thr = use_wave_trace(bvh, false, s->wide_depth) ? 0 : thr;  // of the retrace
+    if (e == hipSuccess && bvh) e = dq.alloc(kClaimBytes + lane_thr * 2 * kDeferCap * sizeof(int), hs);
     if (e == hipSuccess && sorted) e = srt.alloc(ray_sort_words(B) * sizeof(float), hs);
     if (e == hipSuccess) e = ck.alloc(backward_scratch_words(B, s->n, s->F) * sizeof(float), hs);
     if (e == hipSuccess) e = lists.alloc(static_cast<size_t>(B) * per_ray, hs);
@@ -643,7 +647,7 @@ irgs_status irgs_trace_backward(irgs_scene s, const irgs_params* p, int64_t R, c
     tmp.feat = reinterpret_cast<float*>(tmp.n_hits + B);
     tmp.H_cap = kRetraceCap;
     const SceneView sv = view_of(s);
-    FlatScratch fs = flat_scratch(ovf.p, bvh ? ovf_slots_of(s) : 0, dq.p);
+    FlatScratch fs = flat_scratch(ovf.p, bvh ? ovf_slots_of(s) : 0, dq.p, s->wide_depth);
     for (int64_t b0 = 0; b0 < R; b0 += B) {
         const int64_t nb = std::min(B, R - b0);
         const float* bro = ro + 3 * b0;
@@ -672,7 +676,7 @@ irgs_status irgs_trace_packed(const irgs_scene* scenes, int32_t n_scenes, const 
     if (p->flags & (IRGS_FLAG_SH | IRGS_FLAG_NORMAL))
         return fail(IRGS_E_INVALID, "IRGS_FLAG_SH / IRGS_FLAG_NORMAL are not supported by the packed launch");
     int32_t Fmax = 0;
-    int slots = 0;
+    int slots = 0, wide_depth = 0;
     std::vector<SceneView> views(n_scenes);
     for (int i = 0; i < n_scenes; ++i) {
         irgs_scene s = scenes[i];
@@ -683,6 +687,7 @@ irgs_status irgs_trace_packed(const irgs_scene* scenes, int32_t n_scenes, const 
         if (s->n > 0 && !s->p.feat) return fail(IRGS_E_INVALID, "scene %d features are NULL", i);
         Fmax = s->F > Fmax ? s->F : Fmax;
         slots = ovf_slots_of(s) > slots ? ovf_slots_of(s) : slots;
+        wide_depth = std::max(wide_depth, s->wide_depth);
         views[i] = view_of(s);
     }
     if (p->feature_dim < Fmax) return fail(IRGS_E_INVALID, "feature_dim %d < largest scene F %d", p->feature_dim, Fmax);
@@ -709,7 +714,7 @@ irgs_status irgs_trace_packed(const irgs_scene* scenes, int32_t n_scenes, const 
     if (chunks == 0) return IRGS_OK;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     const int grid = static_cast<int>(trace_threads(chunks) / kBlock);
-    const size_t thr = static_cast<size_t>(grid) * kBlock;
+    const size_t thr = use_wave_trace(true, counters, wide_depth) ? 0 : static_cast<size_t>(grid) * kBlock;
     const size_t vb = sizeof(SceneView) * n_scenes, wb = sizeof(WorkItem) * n_items;
     const size_t items_off = (vb + 63) / 64 * 64;
     AsyncBuf meta, ovf, dq;
@@ -726,8 +731,8 @@ irgs_status irgs_trace_packed(const irgs_scene* scenes, int32_t n_scenes, const 
     if (e == hipSuccess) e = hipMemcpyAsync(ditems, w.data(), wb, hipMemcpyHostToDevice, hs);
     if (e == hipSuccess) {
         TraceParams tp = trace_params(p, Fmax);
-        e = launch_packed(dviews, ditems, n_items, chunks, tp, p->k, flat_scratch(ovf.p, slots, dq.p), grid, counters,
-                          hs);
+        e = launch_packed(dviews, ditems, n_items, chunks, tp, p->k, flat_scratch(ovf.p, slots, dq.p, wide_depth),
+                          grid, counters, hs);
     }
     if (e != hipSuccess) return hip_fail(e, "packed launch");
     return IRGS_OK;

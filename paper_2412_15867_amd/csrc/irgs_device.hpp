@@ -44,17 +44,32 @@ struct __align__(16) BvhNode {
     int4 ch;    // child0, child1, parent, unused
 };
 
-// 4-wide node used by the traversal (collapsed from the binary tree), child
-// boxes stored per axis so the four slab tests share instructions.  A child
+// 4-wide node used by the traversal (collapsed from the binary tree): four
+// children of 32 bytes, so that a lane that tests one child reads it with two
+// 16-byte loads and four neighbouring lanes read one 128-byte line.  A child
 // reference r >= 0 is a wide node; r with kLeafBit set is a cluster of
 // ((r & 15) + 1) surfels starting at leaf position ((r & ~kLeafBit) >> 4);
 // kNoChild is an empty slot (its box is all +inf).
-struct __align__(16) WideNode {
-    float4 lo_x, lo_y, lo_z;
-    float4 hi_x, hi_y, hi_z;
-    int4 child;
-    int4 meta;  // unused
+struct __align__(16) WideChild {
+    float lo[3], hi[3];
+    int32_t ref;
+    int32_t pad;  // unused
 };
+struct __align__(128) WideNode {
+    WideChild c[4];
+};
+
+__device__ __forceinline__ WideChild load_child(const WideNode* __restrict__ nodes, int node, int slot)
+{
+    const float4* p = reinterpret_cast<const float4*>(&nodes[node].c[slot]);
+    const float4 a = p[0], b = p[1];
+    WideChild w;
+    w.lo[0] = a.x, w.lo[1] = a.y, w.lo[2] = a.z;
+    w.hi[0] = a.w, w.hi[1] = b.x, w.hi[2] = b.y;
+    w.ref = __float_as_int(b.z);
+    w.pad = 0;
+    return w;
+}
 
 constexpr int kLeafDefault = 12;  // surfels per cluster leaf (at most 16)
 
@@ -186,16 +201,16 @@ constexpr uint64_t kKeyNone = 0xFFF0000000000000ull;
 __device__ __forceinline__ void root_box(const WideNode* __restrict__ root, float lo[3], float hi[3])
 {
     const float inf = __int_as_float(0x7f800000);
-    const float* w = reinterpret_cast<const float*>(root);  // lo_x[4], lo_y[4], lo_z[4], hi_x[4], hi_y[4], hi_z[4]
     for (int a = 0; a < 3; ++a) {
         lo[a] = inf;
         hi[a] = -inf;
     }
     for (int c = 0; c < 4; ++c) {
-        if (w[c] == inf) continue;  // empty slot
+        const WideChild& w = root->c[c];
+        if (w.lo[0] == inf) continue;  // empty slot
         for (int a = 0; a < 3; ++a) {
-            lo[a] = fminf(lo[a], w[4 * a + c]);
-            hi[a] = fmaxf(hi[a], w[12 + 4 * a + c]);
+            lo[a] = fminf(lo[a], w.lo[a]);
+            hi[a] = fmaxf(hi[a], w.hi[a]);
         }
     }
 }
@@ -234,26 +249,14 @@ struct SlabRay {
 // always rejects (the +inf slab of an axis with positive inverse direction
 // pushes the entry to +inf, and with all inverse directions negative the
 // exit drops to -inf).
-__device__ __forceinline__ bool box_hit(float lx, float ly, float lz, float hx, float hy, float hz,
-                                        const SlabRay& q, float lo, float hi, float* t_enter)
+// box_span gives the entry and exit distance clamped to [lo, hi]: the box is
+// crossed inside the window when *tn <= *tf.
+__device__ __forceinline__ void box_span(const WideChild& w, const SlabRay& q, float lo, float hi, float* tn,
+                                         float* tf)
 {
-    const float t0x = fmaf(lx, q.ix, q.nox), t1x = fmaf(hx, q.ix, q.nox);
-    const float t0y = fmaf(ly, q.iy, q.noy), t1y = fmaf(hy, q.iy, q.noy);
-    const float t0z = fmaf(lz, q.iz, q.noz), t1z = fmaf(hz, q.iz, q.noz);
-    const float tn = fmaxf(fmaxf(fminf(t0x, t1x), fminf(t0y, t1y)), fmaxf(fminf(t0z, t1z), lo));
-    const float tf = fminf(fminf(fmaxf(t0x, t1x), fmaxf(t0y, t1y)), fminf(fmaxf(t0z, t1z), hi));
-    *t_enter = tn;
-    return tn <= tf;
-}
-
-// Entry and exit distance of a ray in a box, clamped to [lo, hi]; the box is
-// crossed inside the window when *tn <= *tf.  Same arithmetic as box_hit.
-__device__ __forceinline__ void box_span(float lx, float ly, float lz, float hx, float hy, float hz,
-                                         const SlabRay& q, float lo, float hi, float* tn, float* tf)
-{
-    const float t0x = fmaf(lx, q.ix, q.nox), t1x = fmaf(hx, q.ix, q.nox);
-    const float t0y = fmaf(ly, q.iy, q.noy), t1y = fmaf(hy, q.iy, q.noy);
-    const float t0z = fmaf(lz, q.iz, q.noz), t1z = fmaf(hz, q.iz, q.noz);
+    const float t0x = fmaf(w.lo[0], q.ix, q.nox), t1x = fmaf(w.hi[0], q.ix, q.nox);
+    const float t0y = fmaf(w.lo[1], q.iy, q.noy), t1y = fmaf(w.hi[1], q.iy, q.noy);
+    const float t0z = fmaf(w.lo[2], q.iz, q.noz), t1z = fmaf(w.hi[2], q.iz, q.noz);
     *tn = fmaxf(fmaxf(fminf(t0x, t1x), fminf(t0y, t1y)), fmaxf(fminf(t0z, t1z), lo));
     *tf = fminf(fminf(fmaxf(t0x, t1x), fmaxf(t0y, t1y)), fminf(fmaxf(t0z, t1z), hi));
 }

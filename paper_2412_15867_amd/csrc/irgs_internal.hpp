@@ -130,6 +130,7 @@ struct FlatScratch {
     int* dbuf;                     // deferred-work lists: 2 * defer_cap ints per thread (BVH launches)
     unsigned long long* next_ray;  // ray-claim counter (BVH launches); the launch zeroes it
     const uint32_t* order;         // optional claim order (slot -> ray), BVH launches over one scene
+    int wide_depth;                // levels of the wide tree
     int defer_cap;                 // entries per half of a thread's deferred list
     // 0: ovf and dbuf are sized for trace_threads(R) threads at defer_cap.
     // Otherwise they share one area of this many ints (ovf first, dbuf
@@ -156,6 +157,12 @@ inline bool fixed_scratch_fits(size_t words, int ovf_slots, int block)
 // *order points into it afterwards.  Needs R <= 2^31 - 1 and a built scene.
 hipError_t ray_order_by_origin(const SceneView& sc, int64_t R, const float* ro, void* buf, const uint32_t** order,
                                hipStream_t st);
+
+// True when a forward launch runs with one wave per ray (no per-thread scratch:
+// only the claim counters); false for the plain tracer and the per-lane form
+// (work counters asked for, or a wide tree deeper than the wave's stack takes).
+bool use_wave_trace(bool bvh, bool counters, int wide_depth);
+constexpr int kWaveClaimBytes = 1024;  // the claim counters of a wave launch
 
 // Forward trace.  use_bvh = false tests every record (the plain tracer).
 hipError_t launch_trace(const SceneView& sc, const TraceParams& P, int k, bool use_bvh, int64_t R,

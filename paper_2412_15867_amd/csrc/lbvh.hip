@@ -495,7 +495,7 @@ __global__ void k_cluster_slabs(int nw, const WideNode* __restrict__ wn, SurfelR
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= 4 * nw) return;
-    const int ref = reinterpret_cast<const int*>(&wn[t >> 2].child)[t & 3];
+    const int ref = wn[t >> 2].c[t & 3].ref;
     if (ref == kNoChild || (ref & kLeafBit) == 0) return;
     const int first = (ref & ~kLeafBit) >> 4, cnt = (ref & 15) + 1;
     const float inf = __int_as_float(0x7f800000);
@@ -559,8 +559,10 @@ __device__ __forceinline__ float box_area(const float* b)
 
 __device__ __forceinline__ void set_wide_box(WideNode* w, int slot, const float* b)
 {
-    float* f = reinterpret_cast<float*>(w);
-    for (int k = 0; k < 6; ++k) f[k * 4 + slot] = b[k];
+    for (int k = 0; k < 3; ++k) {
+        w->c[slot].lo[k] = b[k];
+        w->c[slot].hi[k] = b[k + 3];
+    }
 }
 
 // One level of the top-down collapse: wide node w stands for binary node b;
@@ -615,13 +617,13 @@ __global__ void k_collapse(int nfront, const int* __restrict__ front_in, int* __
     WideNode node;
     int4 src = make_int4(-1, -1, -1, -1);
     int* srcp = reinterpret_cast<int*>(&src);
-    int* chp = reinterpret_cast<int*>(&node.child);
     const float inf = __int_as_float(0x7f800000);
     const float empty[6] = {inf, inf, inf, inf, inf, inf};
     for (int c = 0; c < 4; ++c) {
+        node.c[c].pad = 0;
         if (c >= m) {
             set_wide_box(&node, c, empty);
-            chp[c] = kNoChild;
+            node.c[c].ref = kNoChild;
             continue;
         }
         float bx[6];
@@ -630,17 +632,16 @@ __global__ void k_collapse(int nfront, const int* __restrict__ front_in, int* __
         srcp[c] = (par[c] << 1) | side[c];
         const int r = ref[c];
         if (r & kLeafBit) {
-            chp[c] = cluster_ref(r & ~kLeafBit, 1);
+            node.c[c].ref = cluster_ref(r & ~kLeafBit, 1);
         } else if (brange[r].y <= leaf_max) {
-            chp[c] = cluster_ref(brange[r].x, brange[r].y);
+            node.c[c].ref = cluster_ref(brange[r].x, brange[r].y);
         } else {
             const int nw = atomicAdd(&counts[0], 1);
             wide_src[nw] = r;
             front_out[atomicAdd(&counts[1], 1)] = nw;
-            chp[c] = nw;
+            node.c[c].ref = nw;
         }
     }
-    node.meta = make_int4(0, 0, 0, 0);
     wn[w] = node;
     wsrc[w] = src;
 }

@@ -145,31 +145,25 @@ __device__ __forceinline__ void collect_bvh(KBuf<K>& kb, const SceneView& sc, co
     int node = 0;
     while (true) {
         ++ct.nodes;
-        const float4* np = reinterpret_cast<const float4*>(sc.wnodes + node);
-        const float4 lx = np[0], ly = np[1], lz = np[2], hx = np[3], hy = np[4], hz = np[5];
-        const int4 ch = reinterpret_cast<const int4*>(np)[6];
         const float hi = kb.full() ? fminf(key_tau(kb.last()), tmax_c) : tmax_c;
-        float te[4];
-        bool h[4];
-        h[0] = box_hit(lx.x, ly.x, lz.x, hx.x, hy.x, hz.x, q, lo, hi, &te[0]);
-        h[1] = box_hit(lx.y, ly.y, lz.y, hx.y, hy.y, hz.y, q, lo, hi, &te[1]);
-        h[2] = box_hit(lx.z, ly.z, lz.z, hx.z, hy.z, hz.z, q, lo, hi, &te[2]);
-        h[3] = box_hit(lx.w, ly.w, lz.w, hx.w, hy.w, hz.w, q, lo, hi, &te[3]);
-        const int c4[4] = {ch.x, ch.y, ch.z, ch.w};
         float key[4];
-        int ref[4];
+        int ref[4], c4[4];
         int leaves = 0;  // bit c: cluster child c was hit
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const bool leaf = c4[c] < 0;  // cluster (kNoChild never passes the box test)
-            leaves |= (h[c] && leaf) ? (1 << c) : 0;
-            key[c] = (h[c] && !leaf) ? te[c] : inf;
-            ref[c] = c4[c];
+            const WideChild w = load_child(sc.wnodes, node, c);
+            float tn, tf;
+            box_span(w, q, lo, hi, &tn, &tf);
+            const bool h = tn <= tf;
+            const bool leaf = w.ref < 0;  // cluster (kNoChild never passes the box test)
+            leaves |= (h && leaf) ? (1 << c) : 0;
+            key[c] = (h && !leaf) ? tn : inf;
+            ref[c] = c4[c] = w.ref;
         }
         while (leaves) {
             const int c = __ffs(leaves) - 1;
             leaves &= leaves - 1;
-            const int r = c == 0 ? ch.x : (c == 1 ? ch.y : (c == 2 ? ch.z : ch.w));
+            const int r = c == 0 ? c4[0] : (c == 1 ? c4[1] : (c == 2 ? c4[2] : c4[3]));
             const int first = (r & ~kLeafBit) >> 4;
             const int cnt = (r & 15) + 1;
             for (int q = first; q < first + cnt; ++q)

@@ -1,4 +1,6 @@
-// Forward trace as a flat per-lane state machine (BVH path).
+// Forward trace as a flat per-lane state machine (BVH path): the launches that
+// ask for per-ray work counters, and trees too deep for the stack of the
+// wave-per-ray form (trace_wave.hpp), which takes every other launch.
 //
 // The k-buffer marching of Sec. 3.2 nests three loops per ray -- rounds,
 // traversal steps inside a round, and the composite of a round's buffer.
@@ -141,7 +143,7 @@ __device__ __forceinline__ bool pair_stores(const OutPtrs& out)
     return (out.H_cap & 3) == 0 && (a & 15) == 0;
 }
 
-template <int FM, int CM, bool CT, class Source>
+template <int FM, int CM, class Source>
 __device__ __forceinline__ void write_result(const Source& src, const LaneRay& lr, float O, float D, float T,
                                              const float* acc, int nh, const Counters& ct)
 {
@@ -156,7 +158,7 @@ __device__ __forceinline__ void write_result(const Source& src, const LaneRay& l
         if (c < FO) out.feat[r * FO + c] = acc[c];
     if (out.T) out.T[r] = T;
     if (out.n_hits) out.n_hits[r] = nh;
-    if (CT && out.counters)
+    if (out.counters)
         reinterpret_cast<int4*>(out.counters)[r] = make_int4(ct.nodes, ct.tests, ct.inserts, ct.rounds);
 }
 
@@ -266,9 +268,7 @@ struct Deferred {
     }
 };
 
-// CT: keep the per-ray work counters (launches that ask for them); without,
-// their registers stay free.
-template <int K, int FM, int CM, bool CT, class Source>
+template <int K, int FM, int CM, class Source>
 __device__ __forceinline__ void trace_flat(const Source& src, unsigned long long* next_ray, const TraceParams& P,
                                            Stack& st, Deferred<(K <= 16)> dq)
 {
@@ -306,7 +306,7 @@ __device__ __forceinline__ void trace_flat(const Source& src, unsigned long long
         if (__ballot(want_ins)) {
             const uint64_t ev = kb.insert_if(want_ins, pend);
             if (want_ins) {
-                if constexpr (CT) ++ct.inserts;
+                ++ct.inserts;
                 if (ev != kKeyNone) dq.put(cluster_ref(key_pos(ev), 1));  // pushed out of the buffer
                 pend = kKeyNone;
                 mode = kTrav;
@@ -340,21 +340,19 @@ __device__ __forceinline__ void trace_flat(const Source& src, unsigned long long
         constexpr int kOtherW = (CM == kColNormal || (CM == kColPlain && K >= 32)) ? 2 : 1;
         if (cn > 0 && 2 * cn >= cl && cn >= kOtherW * co) {
             if (want_node) {
-                if constexpr (CT) ++ct.nodes;
-                const float4* np = reinterpret_cast<const float4*>(src.view(lr).wnodes + cur);
-                const float4 lx = np[0], ly = np[1], lz = np[2], hx = np[3], hy = np[4], hz = np[5];
-                const int4 ch = reinterpret_cast<const int4*>(np)[6];
+                ++ct.nodes;
+                WideChild w[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) w[c] = load_child(src.view(lr).wnodes, cur, c);
                 const float lo = after == 0 ? P.t_min : fmaxf(P.t_min, key_tau(after));
                 const float tmax_c = fminf(P.t_max, 3.0e38f);
                 const float hi = kb.full() ? fminf(key_tau(kb.last()), tmax_c) : tmax_c;
                 float key[4], tn[4], tf[4];
-                int ref[4] = {ch.x, ch.y, ch.z, ch.w};
-                box_span(lx.x, ly.x, lz.x, hx.x, hy.x, hz.x, q, lo, tmax_c, &tn[0], &tf[0]);
-                box_span(lx.y, ly.y, lz.y, hx.y, hy.y, hz.y, q, lo, tmax_c, &tn[1], &tf[1]);
-                box_span(lx.z, ly.z, lz.z, hx.z, hy.z, hz.z, q, lo, tmax_c, &tn[2], &tf[2]);
-                box_span(lx.w, ly.w, lz.w, hx.w, hy.w, hz.w, q, lo, tmax_c, &tn[3], &tf[3]);
+                int ref[4];
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
+                    ref[c] = w[c].ref;
+                    box_span(w[c], q, lo, tmax_c, &tn[c], &tf[c]);
                     // an empty slot has an all +inf box, which is never crossed
                     const bool crossed = tn[c] <= tf[c];
                     const bool inside = crossed && tn[c] <= hi;
@@ -401,7 +399,7 @@ __device__ __forceinline__ void trace_flat(const Source& src, unsigned long long
                 const bool past = cluster_miss(s0, ray, lo, P.t_max);
                 const bool past1 = !past && cnt > 1 && cluster_miss(s1, ray, lo, P.t_max);
                 int used = past || past1 ? cnt : 1;
-                if constexpr (CT) ct.tests += past ? 0 : 1;
+                ct.tests += past ? 0 : 1;
                 float tau = 0.0f, rho2 = 0.0f;
                 bool hit = !past && hit_test(s0, ray, P.t_min, P.t_max, &tau, &rho2);
                 uint64_t key = hit_key(tau, first);
@@ -410,7 +408,7 @@ __device__ __forceinline__ void trace_flat(const Source& src, unsigned long long
                 if (above && !ins) dq.put(cluster_ref(first, 1));  // beyond this round's K-th key
                 if (!past && !past1 && !ins && cnt > 1) {
                     used = 2;
-                    if constexpr (CT) ++ct.tests;
+                    ++ct.tests;
                     hit = hit_test(s1, ray, P.t_min, P.t_max, &tau, &rho2);
                     key = hit_key(tau, first + 1);
                     above = hit && key > after;
@@ -437,12 +435,12 @@ __device__ __forceinline__ void trace_flat(const Source& src, unsigned long long
                     kb.clear();
                     dq.reset();
                     if (src.view(lr).n <= 0 || !ray_valid(ray)) {
-                        write_result<FM, CM, CT>(src, lr, O, D, T, acc, nh, ct);
+                        write_result<FM, CM>(src, lr, O, D, T, acc, nh, ct);
                     } else {
                         q = slab_ray(ray);
                         cur = 0;
                         st.sp = 0;
-                        if constexpr (CT) ++ct.rounds;
+                        ++ct.rounds;
                         mode = kTrav;
                     }
                 }
@@ -509,12 +507,12 @@ __device__ __forceinline__ void trace_flat(const Source& src, unsigned long long
                         if (out.hit_T) out.hit_T[b + 2] = pend_T2;
                     }
                 }
-                write_result<FM, CM, CT>(src, lr, O, D, T, acc, nh, ct);
+                write_result<FM, CM>(src, lr, O, D, T, acc, nh, ct);
                 mode = kFetch;
             } else {
                 kb.clear();  // `after` is the round's last (K-th) key
                 st.sp = 0;
-                if constexpr (CT) ++ct.rounds;
+                ++ct.rounds;
                 cur = dq.flip() ? next_item() : 0;  // deferred list, or the root after an overflow
                 mode = kTrav;
             }

@@ -14,6 +14,7 @@
 #include "irgs_internal.hpp"
 #include "march.hpp"
 #include "trace_flat.hpp"
+#include "trace_wave.hpp"
 
 namespace irgs {
 
@@ -88,7 +89,7 @@ __device__ __forceinline__ void trace_one(const SceneView& sc, const TraceParams
         reinterpret_cast<int4*>(out.counters)[r] = make_int4(ct.nodes, ct.tests, ct.inserts, ct.rounds);
 }
 
-template <int K, int FM, bool BVH, int CM, bool CT>
+template <int K, int FM, bool BVH, int CM>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(K <= 16 && FM <= 8 ? 4 : 1))) void k_trace(SceneView sc, TraceParams P, int64_t R,
                                                   const float* __restrict__ ro, const float* __restrict__ rd,
                                                   OutPtrs out, FlatScratch fs)
@@ -102,7 +103,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(K <= 16 
     if (BVH) {
         const PlainSource src{sc, out, ro, rd, R, fs.order};
         Deferred<(K <= 16)> dq{as_glb(fs.dbuf + gtid * 2 * fs.defer_cap), as_lds(lds_stage) + threadIdx.x, fs.defer_cap, 0, 0, 0, 0, 0};
-        trace_flat<K, FM, CM, CT>(src, fs.next_ray, P, st, dq);
+        trace_flat<K, FM, CM>(src, fs.next_ray, P, st, dq);
     } else {
         for (int64_t r = gtid; r < R; r += nthr) {
             const Ray ray = load_ray(ro, rd, r);
@@ -111,15 +112,15 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(K <= 16 
     }
 }
 
-template <int K, int FM, bool BVH, int CM, bool CT>
-hipError_t launch_kct(const SceneView& sc, const TraceParams& P, int64_t R, const float* ro, const float* rd,
+template <int K, int FM, bool BVH, int CM>
+hipError_t launch_kf(const SceneView& sc, const TraceParams& P, int64_t R, const float* ro, const float* rd,
                       const OutPtrs& out, const FlatScratch& fs, hipStream_t st)
 {
     if (BVH) {
         const hipError_t e = fill_u32(fs.next_ray, 2, 0u, st);
         if (e != hipSuccess) return e;
     }
-    unsigned grid = persistent_grid(trace_threads(R) / kBlock, resident_blocks(k_trace<K, FM, BVH, CM, CT>, kBlock));
+    unsigned grid = persistent_grid(trace_threads(R) / kBlock, resident_blocks(k_trace<K, FM, BVH, CM>, kBlock));
     FlatScratch f = fs;
     if (BVH && fs.fixed_words > 0) {
         // One fixed area: the stack overflow of every thread, then the
@@ -138,20 +139,8 @@ hipError_t launch_kct(const SceneView& sc, const TraceParams& P, int64_t R, cons
         f.dbuf = f.ovf + ovf_words;
         if (fs.ovf_slots == 0) f.ovf = nullptr;
     }
-    k_trace<K, FM, BVH, CM, CT><<<grid, kBlock, 0, st>>>(sc, P, R, ro, rd, out, f);
+    k_trace<K, FM, BVH, CM><<<grid, kBlock, 0, st>>>(sc, P, R, ro, rd, out, f);
     return hipGetLastError();
-}
-
-// BVH launches that do not ask for work counters run an instance without
-// them (their four registers free; the plain tracer keeps its own).
-template <int K, int FM, bool BVH, int CM>
-hipError_t launch_kf(const SceneView& sc, const TraceParams& P, int64_t R, const float* ro, const float* rd,
-                     const OutPtrs& out, const FlatScratch& fs, hipStream_t st)
-{
-    if constexpr (BVH) {
-        if (!out.counters) return launch_kct<K, FM, BVH, CM, false>(sc, P, R, ro, rd, out, fs, st);
-    }
-    return launch_kct<K, FM, BVH, CM, true>(sc, P, R, ro, rd, out, fs, st);
 }
 
 template <int K, bool BVH>
@@ -194,7 +183,7 @@ hipError_t launch_b(const SceneView& sc, const TraceParams& P, int k, int64_t R,
 // Packed persistent launch: lanes claim slots of the concatenation of every
 // work item's rays (an item is one request on one scene), so different
 // requests and scenes share one launch.
-template <int K, int FM, bool CT>
+template <int K, int FM>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(K == 32 && FM <= 8 ? 3 : 1))) void k_packed(const SceneView* __restrict__ scenes,
                                                    const WorkItem* __restrict__ items, int n_items,
                                                    int64_t n_rays, TraceParams P, FlatScratch fs)
@@ -207,44 +196,21 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(K == 32 
              static_cast<int>(threadIdx.x), 0, kStackLds};
     const PackedSource src{scenes, items, n_items, n_rays};
     Deferred<(K <= 16)> dq{as_glb(fs.dbuf + gtid * 2 * fs.defer_cap), as_lds(lds_stage) + threadIdx.x, fs.defer_cap, 0, 0, 0, 0, 0};
-    trace_flat<K, FM, kColPlain, CT>(src, fs.next_ray, P, st, dq);
-}
-
-template <int K, int FM, bool CT>
-hipError_t launch_packed_kct(const SceneView* scenes, const WorkItem* items, int n_items, int64_t n_rays,
-                             const TraceParams& P, const FlatScratch& fs, int grid_blocks, hipStream_t st)
-{
-    const hipError_t e = fill_u32(fs.next_ray, 2, 0u, st);
-    if (e != hipSuccess) return e;
-    const unsigned grid = persistent_grid(grid_blocks, resident_blocks(k_packed<K, FM, CT>, kBlock));
-    k_packed<K, FM, CT><<<grid, kBlock, 0, st>>>(scenes, items, n_items, n_rays, P, fs);
-    return hipGetLastError();
+    trace_flat<K, FM, kColPlain>(src, fs.next_ray, P, st, dq);
 }
 
 template <int K, int FM>
 hipError_t launch_packed_kf(const SceneView* scenes, const WorkItem* items, int n_items, int64_t n_rays,
-                            const TraceParams& P, const FlatScratch& fs, int grid_blocks, bool counters,
-                            hipStream_t st)
+                             const TraceParams& P, const FlatScratch& fs, int grid_blocks, hipStream_t st)
 {
-    return counters ? launch_packed_kct<K, FM, true>(scenes, items, n_items, n_rays, P, fs, grid_blocks, st)
-                    : launch_packed_kct<K, FM, false>(scenes, items, n_items, n_rays, P, fs, grid_blocks, st);
+    const hipError_t e = fill_u32(fs.next_ray, 2, 0u, st);
+    if (e != hipSuccess) return e;
+    const unsigned grid = persistent_grid(grid_blocks, resident_blocks(k_packed<K, FM>, kBlock));
+    k_packed<K, FM><<<grid, kBlock, 0, st>>>(scenes, items, n_items, n_rays, P, fs);
+    return hipGetLastError();
 }
 
 }  // namespace
-
-hipError_t launch_packed(const SceneView* scenes_dev, const WorkItem* items_dev, int n_items, int64_t n_rays,
-                         const TraceParams& P, int k, const FlatScratch& fs, int grid_blocks, bool counters,
-                         hipStream_t st)
-{
-    if (n_rays <= 0 || n_items <= 0) return hipSuccess;
-    const SceneView* sv = scenes_dev;
-    const WorkItem* it = items_dev;
-    if (k == 16 && P.F <= 8) return launch_packed_kf<16, 8>(sv, it, n_items, n_rays, P, fs, grid_blocks, counters, st);
-    if (k == 16 && P.F <= 64) return launch_packed_kf<16, 64>(sv, it, n_items, n_rays, P, fs, grid_blocks, counters, st);
-    if (k == 32 && P.F <= 8) return launch_packed_kf<32, 8>(sv, it, n_items, n_rays, P, fs, grid_blocks, counters, st);
-    if (k == 32 && P.F <= 64) return launch_packed_kf<32, 64>(sv, it, n_items, n_rays, P, fs, grid_blocks, counters, st);
-    return hipErrorInvalidValue;
-}
 
 namespace {
 
@@ -281,12 +247,81 @@ hipError_t ray_order_by_origin(const SceneView& sc, int64_t R, const float* ro, 
     return e;
 }
 
+namespace {
+
+// The SH instance holds the basis of its ray (16 registers) besides: 5 waves
+// per SIMD; the others fit the 64 registers of 8.
+template <int CM, class Source>
+__global__ __launch_bounds__(kWaveBlock) __attribute__((amdgpu_waves_per_eu(CM == kColSH ? 5 : 8)))
+void k_trace_wave(Source src, TraceParams P, unsigned long long* next, int reserve)
+{
+    __shared__ uint32_t lds[kWaveLdsWords];
+    trace_waves<CM>(src, next, P, (lds_u32*)lds, reserve);
+}
+
+template <int CM, class Source>
+hipError_t launch_wave(const Source& src, int64_t rays, const TraceParams& P, unsigned long long* next, int wide_depth,
+                       hipStream_t st)
+{
+    const int64_t resident = resident_blocks(k_trace_wave<CM, Source>, kWaveBlock);
+    const int64_t waves = resident > 0 ? resident : 256 * 16;
+    const int reserve = wave_stack_reserve(wide_depth);
+    if (rays <= waves) {  // every ray has a wave of its own: nothing to claim or clear
+        k_trace_wave<CM, Source><<<static_cast<unsigned>(rays), kWaveBlock, 0, st>>>(src, P, nullptr, reserve);
+        return hipGetLastError();
+    }
+    const hipError_t e = fill_u32(next, kWaveClaimBytes / 4, 0u, st);
+    if (e != hipSuccess) return e;
+    k_trace_wave<CM, Source><<<static_cast<unsigned>(waves), kWaveBlock, 0, st>>>(src, P, next, reserve);
+    return hipGetLastError();
+}
+
+// Feature counts a k-buffer size is offered for (the per-lane form's
+// instances; the wave form takes any, and refuses the same calls).
+bool features_offered(int k, int F, bool special)
+{
+    if (special) return k == 16 || k == 32 || k == 64;
+    return F <= 8 || k == 16 || k == 32;
+}
+
+}  // namespace
+
+bool use_wave_trace(bool bvh, bool counters, int wide_depth)
+{
+    return bvh && !counters && wave_stack_fits(wide_depth);
+}
+
 hipError_t launch_trace(const SceneView& sc, const TraceParams& P, int k, bool use_bvh, int64_t R,
                         const float* ro, const float* rd, const OutPtrs& out, const FlatScratch& fs,
                         hipStream_t st)
 {
     if (R <= 0) return hipSuccess;
+    if (use_wave_trace(use_bvh, out.counters != nullptr, fs.wide_depth)) {
+        if (!features_offered(k, P.F, P.sh_deg >= 0 || P.normals)) return hipErrorInvalidValue;
+        const WavePlain src{sc, out, ro, rd, R, fs.order};
+        if (P.sh_deg >= 0) return launch_wave<kColSH>(src, R, P, fs.next_ray, fs.wide_depth, st);
+        if (P.normals) return launch_wave<kColNormal>(src, R, P, fs.next_ray, fs.wide_depth, st);
+        return launch_wave<kColPlain>(src, R, P, fs.next_ray, fs.wide_depth, st);
+    }
     return use_bvh ? launch_b<true>(sc, P, k, R, ro, rd, out, fs, st) : launch_b<false>(sc, P, k, R, ro, rd, out, fs, st);
+}
+
+hipError_t launch_packed(const SceneView* scenes_dev, const WorkItem* items_dev, int n_items, int64_t n_rays,
+                         const TraceParams& P, int k, const FlatScratch& fs, int grid_blocks, bool counters,
+                         hipStream_t st)
+{
+    if (n_rays <= 0 || n_items <= 0) return hipSuccess;
+    const SceneView* sv = scenes_dev;
+    const WorkItem* it = items_dev;
+    if ((k != 16 && k != 32) || P.F > kMaxF) return hipErrorInvalidValue;
+    if (use_wave_trace(true, counters, fs.wide_depth)) {
+        const WavePacked src{sv, it, n_items, n_rays};
+        return launch_wave<kColPlain>(src, n_rays, P, fs.next_ray, fs.wide_depth, st);
+    }
+    if (k == 16 && P.F <= 8) return launch_packed_kf<16, 8>(sv, it, n_items, n_rays, P, fs, grid_blocks, st);
+    if (k == 16) return launch_packed_kf<16, 64>(sv, it, n_items, n_rays, P, fs, grid_blocks, st);
+    if (P.F <= 8) return launch_packed_kf<32, 8>(sv, it, n_items, n_rays, P, fs, grid_blocks, st);
+    return launch_packed_kf<32, 64>(sv, it, n_items, n_rays, P, fs, grid_blocks, st);
 }
 
 }  // namespace irgs

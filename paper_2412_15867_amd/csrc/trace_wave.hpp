@@ -1,0 +1,483 @@
+// Forward trace with one wave per ray (BVH path).
+//
+// The 64 lanes of a wave share one ray, so every step of the k-buffer marching
+// of Sec. 3.2 is done for many candidates at once and a ray waits for a few
+// dozen memory round trips instead of several hundred:
+//   NODE  up to 16 wide nodes are taken from the stack and their 64 child boxes
+//         tested, one per lane; crossed inner children go back on the stack
+//         (each node's nearest child on top), crossed clusters into a queue;
+//   LEAF  up to 64 records of the queued clusters are tested, one per lane
+//         (clusters are contiguous, so neighbouring lanes read neighbouring
+//         records); hits between the resume key and the buffer's last key
+//         collect in a pending list;
+//   MERGE 64 pending keys are sorted across the lanes and merged into the
+//         buffer of the 64 smallest keys, one per lane in ascending order;
+//   COMP  every lane re-evaluates its buffered hit; the transmittance runs
+//         through the lanes in hit order, and each composited channel is the
+//         running sum of one lane (O, D, then the features), so the operations
+//         and their order per ray are those of the nested form, bit for bit.
+// A round whose buffer is full and whose transmittance stays above the cutoff
+// is followed by another from the root, after the last key.
+//
+// What bounds it: the instruction issue (1M surfels, 4.2M rays: 4,250 VALU
+// and 2,190 scalar instructions per ray, the VALU busy 85% of the time at 8
+// waves per SIMD).  Against one ray per lane, whose waves stepped through 1,230
+// dependent iterations with 45% of their lanes active: 1M surfels, 4.2M rays
+// 70.3 -> 34.4 ms (122 Mrays/s); 200K surfels 36.6 -> 11.9 ms; launches smaller
+// than the chip, whose time is one ray's chain of round trips: 4,096 rays
+// 580 -> 33 us, 2^18 rays 13.9 -> 5 ms.
+//
+// The buffer content after a round is the 64 smallest keys above the resume
+// key whatever the visiting order, and results do not depend on the buffer's
+// size, so every requested k gives the same outputs as the per-lane form.
+#pragma once
+
+#include "irgs_internal.hpp"
+#include "march.hpp"
+
+namespace irgs {
+
+constexpr int kWaveBlock = 64;   // one wave per block: no barrier anywhere
+constexpr int kWaveNodes = 16;   // nodes taken from the stack per step (4 lanes each)
+constexpr int kWaveStack = 512;
+constexpr int kWaveQueue = 128;  // clusters: at most kLeafTrigger - 1 + 64 wait
+constexpr int kWavePend = 128;   // hit keys: at most 63 + 64 wait
+constexpr int kLeafTrigger = 8;  // clusters that start a leaf step (about 64 records)
+constexpr int kWaveLdsWords = kWaveStack + kWaveQueue + 2 * kWavePend;
+constexpr int kWaveParts = 8;         // claim counters, one per XCD ...
+constexpr int kWaveClaimStride = 16;  // ... 128 bytes apart
+constexpr int kWaveChunk = 256;       // consecutive slots of one part
+
+// A node step takes one node at a time (depth first) once fewer than the
+// reserve's entries are left above a full step: from any node on, depth-first
+// steps add at most 3 entries per level.
+inline int wave_stack_reserve(int wide_depth) { return 3 * wide_depth + 4; }
+inline bool wave_stack_fits(int wide_depth)
+{
+    return wave_stack_reserve(wide_depth) + 3 * kWaveNodes + 64 <= kWaveStack;
+}
+
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+typedef __attribute__((address_space(3))) float lds_f32;
+
+// Orders this wave's LDS accesses around it for the compiler (the hardware
+// executes one wave's LDS operations in order).
+__device__ __forceinline__ void lds_order()
+{
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+}
+
+__device__ __forceinline__ int wave_rank(uint64_t mask)  // set bits of mask below this lane
+{
+    return static_cast<int>(__builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
+                                                      __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(mask), 0u)));
+}
+
+__device__ __forceinline__ int bcast(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
+__device__ __forceinline__ float bcast(float v, int lane)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+__device__ __forceinline__ uint64_t bcast(uint64_t v, int lane)
+{
+    return (static_cast<uint64_t>(static_cast<uint32_t>(bcast(static_cast<int>(v >> 32), lane))) << 32) |
+           static_cast<uint32_t>(bcast(static_cast<int>(v), lane));
+}
+
+template <int Ctrl>
+__device__ __forceinline__ uint32_t dpp(uint32_t old, uint32_t v)
+{
+    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(static_cast<int>(old), static_cast<int>(v), Ctrl, 0xf, 0xf, false));
+}
+
+// Lane l's value of lane l ^ X, for the X a sort of 64 needs.
+template <int X>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v, int lane)
+{
+    if constexpr (X == 1) return dpp<0xB1>(v, v);        // quad_perm 1,0,3,2
+    else if constexpr (X == 2) return dpp<0x4E>(v, v);   // quad_perm 2,3,0,1
+    else if constexpr (X == 3) return dpp<0x1B>(v, v);   // quad_perm 3,2,1,0
+    else if constexpr (X == 7) return dpp<0x141>(v, v);  // row_half_mirror
+    else if constexpr (X == 8) return dpp<0x128>(v, v);  // row_ror:8
+    else if constexpr (X == 15) return dpp<0x140>(v, v); // row_mirror
+    else if constexpr (X == 4 || X == 16 || X == 31)
+        return static_cast<uint32_t>(__builtin_amdgcn_ds_swizzle(static_cast<int>(v), (X << 10) | 0x1f));
+    else
+        return static_cast<uint32_t>(__builtin_amdgcn_ds_bpermute((lane ^ X) << 2, static_cast<int>(v)));
+}
+
+template <int X>
+__device__ __forceinline__ uint64_t lane_xor(uint64_t v, int lane)
+{
+    return (static_cast<uint64_t>(lane_xor<X>(static_cast<uint32_t>(v >> 32), lane)) << 32) |
+           lane_xor<X>(static_cast<uint32_t>(v), lane);
+}
+
+// Keys read as doubles are in reverse order (see hit_key), and an FP64
+// compare runs at the FP32 rate.
+__device__ __forceinline__ bool key_less(uint64_t a, uint64_t b)
+{
+    return __longlong_as_double(static_cast<long long>(a)) > __longlong_as_double(static_cast<long long>(b));
+}
+
+// Compare-exchange with lane ^ X: the lower lane keeps the smaller key.
+template <int X>
+__device__ __forceinline__ void key_step(uint64_t& k, int lane)
+{
+    constexpr int top = X >= 32 ? 32 : X >= 16 ? 16 : X >= 8 ? 8 : X >= 4 ? 4 : X >= 2 ? 2 : 1;
+    const uint64_t y = lane_xor<X>(k, lane);
+    const bool upper = (lane & top) != 0;
+    k = key_less(y, k) != upper ? y : k;
+}
+
+// Ascending bitonic sort of one key per lane (mirrored first stages, so every
+// exchange has the same direction).
+__device__ __forceinline__ void sort_keys(uint64_t& k, int lane)
+{
+    key_step<1>(k, lane);
+    key_step<3>(k, lane), key_step<1>(k, lane);
+    key_step<7>(k, lane), key_step<2>(k, lane), key_step<1>(k, lane);
+    key_step<15>(k, lane), key_step<4>(k, lane), key_step<2>(k, lane), key_step<1>(k, lane);
+    key_step<31>(k, lane), key_step<8>(k, lane), key_step<4>(k, lane), key_step<2>(k, lane), key_step<1>(k, lane);
+    key_step<63>(k, lane), key_step<16>(k, lane), key_step<8>(k, lane), key_step<4>(k, lane), key_step<2>(k, lane),
+        key_step<1>(k, lane);
+}
+
+// The 64 smallest of the sorted buffer and the sorted keys x, sorted.
+__device__ __forceinline__ void merge_keys(uint64_t& kb, uint64_t x, int lane)
+{
+    const uint64_t xr = lane_xor<63>(x, lane);
+    kb = key_less(xr, kb) ? xr : kb;
+    key_step<32>(kb, lane), key_step<16>(kb, lane), key_step<8>(kb, lane), key_step<4>(kb, lane);
+    key_step<2>(kb, lane), key_step<1>(kb, lane);
+}
+
+// One scene, slots [0, R), taken in `order` when given.
+struct WavePlain {
+    SceneView sc;
+    OutPtrs o;
+    const float* ro;
+    const float* rd;
+    int64_t R;
+    const uint32_t* order;
+
+    __device__ __forceinline__ int64_t total() const { return R; }
+    __device__ __forceinline__ int64_t locate(int64_t slot, int lane, int* item) const
+    {
+        *item = 0;
+        return order ? static_cast<int64_t>(order[slot]) : slot;
+    }
+    __device__ __forceinline__ Ray ray(int64_t r, int) const { return load_ray(ro, rd, r); }
+    __device__ __forceinline__ const OutPtrs& out(int) const { return o; }
+    __device__ __forceinline__ const SceneView& view(int) const { return sc; }
+};
+
+// Several requests over several scenes: a slot indexes the concatenation of
+// the items' rays; the lanes look for the owning item 64 items at a time.
+struct WavePacked {
+    const SceneView* scenes;
+    const WorkItem* items;
+    int n_items;
+    int64_t n_rays;
+
+    __device__ __forceinline__ int64_t total() const { return n_rays; }
+    __device__ __forceinline__ int64_t locate(int64_t slot, int lane, int* item) const
+    {
+        int it = -1;
+        for (int b = 0; b < n_items; b += 64) {
+            const bool before = b + lane < n_items && items[b + lane].chunk_begin <= slot;
+            const int c = __popcll(__ballot(before));  // first slots ascend: the items at or before it lead
+            it += c;
+            if (c < 64) break;
+        }
+        *item = it;
+        return items[it].ray_begin + (slot - items[it].chunk_begin);
+    }
+    __device__ __forceinline__ Ray ray(int64_t r, int item) const { return load_ray(items[item].ro, items[item].rd, r); }
+    __device__ __forceinline__ const OutPtrs& out(int item) const { return items[item].out; }
+    __device__ __forceinline__ const SceneView& view(int item) const { return scenes[items[item].scene]; }
+};
+
+// Trace ray r of `sc` with the whole wave.  `lds`: kWaveLdsWords words of this
+// wave; `reserve`: stack entries kept for depth-first steps.
+template <int CM>
+__device__ __forceinline__ void trace_ray_wave(const SceneView& sc, const TraceParams& P, const Ray& ray, int64_t r,
+                                               const OutPtrs& out, lds_u32* lds, int reserve, int lane)
+{
+    lds_u32* stk = lds;
+    lds_u32* queue = lds + kWaveStack;
+    lds_u32* pend = queue + kWaveQueue;  // low words, then high words
+    lds_u32* pend_hi = pend + kWavePend;
+    lds_f32* rows = reinterpret_cast<lds_f32*>(lds);  // composite staging (the traversal's areas are idle then)
+    const int F = sc.F;
+    const int FO = CM == kColSH ? 3 : (CM == kColNormal ? F + 3 : F);
+    float T = 1.0f;
+    float acc = 0.0f;   // lane 0: O, lane 1: D, lane 2 + c: channel c
+    float acc2 = 0.0f;  // lane c: channel 62 + c
+    int nh = 0;
+    if (sc.n > 0 && ray_valid(ray)) {
+        const SlabRay q = slab_ray(ray);
+        const float tmax_c = fminf(P.t_max, 3.0e38f);
+        uint64_t after = 0;
+        while (true) {
+            uint64_t kb = kKeyNone;
+            uint64_t kth = kKeyNone;
+            const float lo = after == 0 ? P.t_min : fmaxf(P.t_min, key_tau(after));
+            float hi = tmax_c;
+            int sp = 1, qn = 0, pn = 0;
+            stk[0] = 0u;
+            lds_order();
+            while (true) {
+                if (qn >= kLeafTrigger || (sp == 0 && qn > 0)) {
+                    // whole clusters from the queue's end, at most 64 records
+                    const bool have = lane < qn;
+                    const int ref = have ? static_cast<int>(queue[qn - 1 - lane]) : 0;
+                    const int first = (ref & ~kLeafBit) >> 4;
+                    const int cnt = have ? (ref & 15) + 1 : 0;
+                    uint32_t incl = cnt;  // inclusive scan over the lanes
+                    incl += dpp<0x111>(0u, incl);
+                    incl += dpp<0x112>(0u, incl);
+                    incl += dpp<0x114>(0u, incl);
+                    incl += dpp<0x118>(0u, incl);
+                    incl += __builtin_amdgcn_update_dpp(0, static_cast<int>(incl), 0x142, 0xa, 0xf, false);
+                    incl += __builtin_amdgcn_update_dpp(0, static_cast<int>(incl), 0x143, 0xc, 0xf, false);
+                    const bool take = have && incl <= 64u;
+                    const int nt = __popcll(__ballot(take));
+                    const int excl = static_cast<int>(incl) - cnt;
+                    const int total = bcast(static_cast<int>(incl), nt - 1);
+                    // lane -> cluster: each taken cluster marks its first lane
+                    lds_u32* mark = pend + 64;  // at most 63 keys wait here
+                    mark[lane] = 0u;
+                    lds_order();
+                    if (take) mark[excl] = 1u;
+                    lds_order();
+                    const uint64_t starts = __ballot(mark[lane] != 0u);
+                    const int src = wave_rank(starts) - 1 + static_cast<int>((starts >> lane) & 1ull);
+                    const int pos = __builtin_amdgcn_ds_bpermute(src << 2, first - excl) + lane;
+                    qn -= nt;
+                    bool pass = false;
+                    uint64_t key = kKeyNone;
+                    if (lane < total) {
+                        const SurfelRec s = load_rec(sc.rec, pos);
+                        float tau, rho2;
+                        const bool hit = hit_test(s, ray, P.t_min, P.t_max, &tau, &rho2);
+                        key = hit_key(tau, pos);
+                        pass = hit && key > after && key < kth;
+                    }
+                    const uint64_t m = __ballot(pass);
+                    lds_order();
+                    if (pass) {
+                        const int at = pn + wave_rank(m);
+                        pend[at] = static_cast<uint32_t>(key);
+                        pend_hi[at] = static_cast<uint32_t>(key >> 32);
+                    }
+                    lds_order();
+                    pn += __popcll(m);
+                    if (pn >= 64) {
+                        pn -= 64;
+                        uint64_t x = (static_cast<uint64_t>(pend_hi[pn + lane]) << 32) | pend[pn + lane];
+                        sort_keys(x, lane);
+                        if (bcast(kb, 0) == kKeyNone)
+                            kb = x;
+                        else
+                            merge_keys(kb, x, lane);
+                        kth = bcast(kb, 63);
+                        if (kth != kKeyNone) hi = fminf(key_tau(kth), tmax_c);
+                    }
+                } else if (sp > 0) {
+                    int nn = min(sp, kWaveNodes);
+                    if (sp + 3 * kWaveNodes > kWaveStack - reserve) nn = 1;
+                    const int ni = lane >> 2;
+                    bool inner = false, leaf = false;
+                    float tn = 0.0f;
+                    int ref = 0;
+                    if (ni < nn) {
+                        const WideChild w = load_child(sc.wnodes, static_cast<int>(stk[sp - 1 - ni]), lane & 3);
+                        float tf;
+                        box_span(w, q, lo, hi, &tn, &tf);
+                        ref = w.ref;
+                        inner = tn <= tf && ref >= 0;
+                        leaf = tn <= tf && ref < 0;
+                    }
+                    sp -= nn;
+                    lds_order();
+                    const uint64_t ml = __ballot(leaf);
+                    if (leaf) queue[qn + wave_rank(ml)] = static_cast<uint32_t>(ref);
+                    qn += __popcll(ml);
+                    // each node's nearest child last, the nearest node's last among those
+                    const uint32_t kt = __float_as_uint(inner ? tn : __int_as_float(0x7f800000));
+                    const float k0 = __uint_as_float(kt);
+                    int rank = 0;
+                    {
+                        const float k1 = __uint_as_float(dpp<0xB1>(kt, kt)), k2 = __uint_as_float(dpp<0x4E>(kt, kt)),
+                                    k3 = __uint_as_float(dpp<0x1B>(kt, kt));
+                        const int c = lane & 3;
+                        rank += (k1 < k0 || (k1 == k0 && (c & 1))) ? 1 : 0;
+                        rank += (k2 < k0 || (k2 == k0 && (c & 2))) ? 1 : 0;
+                        rank += (k3 < k0 || (k3 == k0 && (c & 2))) ? 1 : 0;
+                    }
+#pragma unroll
+                    for (int c = 3; c >= 0; --c) {
+                        const bool mine = inner && rank == c;
+                        const uint64_t m = __ballot(mine);
+                        const int n = __popcll(m);
+                        if (mine) stk[sp + n - 1 - wave_rank(m)] = static_cast<uint32_t>(ref);
+                        sp += n;
+                    }
+                    lds_order();
+                } else {
+                    break;
+                }
+            }
+            if (pn > 0) {
+                uint64_t x = kKeyNone;
+                if (lane < pn) x = (static_cast<uint64_t>(pend_hi[lane]) << 32) | pend[lane];
+                sort_keys(x, lane);
+                if (bcast(kb, 0) == kKeyNone)
+                    kb = x;
+                else
+                    merge_keys(kb, x, lane);
+            }
+            lds_order();
+            // composite the buffered hits, lane i the i-th
+            const int m = __popcll(__ballot(kb != kKeyNone));
+            float tau = 0.0f, a = 0.0f;
+            int id = 0;
+            float4 nr = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (lane < m) {
+                const SurfelRec s = load_rec(sc.rec, key_pos(kb));
+                float rho2;
+                plane_hit(s, ray, &tau, &rho2);
+                a = alpha_of(s, rho2);
+                id = __float_as_int(s.c.w);
+                nr = s.b;
+            }
+            // T before lane i's hit: T runs one lane up per step, so that the
+            // products are those of the hit-by-hit form
+            const float om = 1.0f - a;
+            const float omp = __uint_as_float(dpp<0x138>(__float_as_uint(1.0f), __float_as_uint(om)));  // wave_shr:1
+            float Tl = T;
+            for (int i = 1; i < m; i += 8) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j)  // steps past the last hit change no lane that counts
+                    Tl = __uint_as_float(dpp<0x138>(__float_as_uint(T), __float_as_uint(Tl))) * omp;
+            }
+            const float Ta = Tl * om;
+            const uint64_t cut = __ballot(lane < m && Ta < P.T_min);
+            const int used = cut ? __ffsll(static_cast<unsigned long long>(cut)) : m;
+            const float w = Tl * a;
+            if (out.hit_ids && lane < used && nh + lane < out.H_cap) {
+                const int64_t at = r * out.H_cap + nh + lane;
+                __builtin_nontemporal_store(id, out.hit_ids + at);
+                if (out.hit_T) __builtin_nontemporal_store(Tl, out.hit_T + at);
+            }
+            // rows of (w, 1, tau, channels) in LDS; every lane then sums its
+            // own column in hit order
+            const int L = (3 + FO) | 1;  // odd: a column's words lie in different banks
+            const int nrows = min(64, (kWaveLdsWords / L) & ~7);
+            float Y[16];
+            if constexpr (CM == kColSH) sh_basis(ray.dx, ray.dy, ray.dz, P.sh_deg, Y);
+            for (int b = 0; b < used; b += nrows) {
+                const int i = lane - b;
+                if (i >= 0 && i < nrows) {
+                    lds_f32* row = rows + i * L;
+                    if (lane < used) {
+                        row[0] = w, row[1] = 1.0f, row[2] = tau;
+                        const float* f = sc.feat + static_cast<int64_t>(id) * F;
+                        if constexpr (CM == kColSH) {
+                            float raw[3];
+                            sh_raw(f, P.sh_deg, Y, raw);
+#pragma unroll
+                            for (int c = 0; c < 3; ++c) row[3 + c] = fmaxf(raw[c], 0.0f);
+                        } else {
+                            for (int c0 = 0; c0 < F; c0 += 8) {  // eight loads in flight
+                                float v[8];
+#pragma unroll
+                                for (int c = 0; c < 8; ++c) v[c] = c0 + c < F ? f[c0 + c] : 0.0f;
+#pragma unroll
+                                for (int c = 0; c < 8; ++c)
+                                    if (c0 + c < F) row[3 + c0 + c] = v[c];
+                            }
+                            if constexpr (CM == kColNormal) {
+                                const float s = dot3(nr.x, nr.y, nr.z, ray.dx, ray.dy, ray.dz) > 0.0f ? -1.0f : 1.0f;
+                                row[3 + F] = s * nr.x, row[4 + F] = s * nr.y, row[5 + F] = s * nr.z;
+                            }
+                        }
+                    } else {
+                        for (int c = 0; c < 3 + FO; ++c) row[c] = 0.0f;
+                    }
+                }
+                lds_order();
+                const int n = min(used - b, nrows);
+                const lds_f32* wr = rows;
+                const lds_f32* xr = rows + 1 + min(lane, FO + 1);
+                for (int i = 0; i < n; i += 8) {
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) acc = fmaf(wr[(i + j) * L], xr[(i + j) * L], acc);
+                }
+                if (FO > 62) {
+                    const lds_f32* x2 = rows + 3 + min(62 + lane, FO - 1);
+                    for (int i = 0; i < n; ++i) acc2 = fmaf(wr[i * L], x2[i * L], acc2);
+                }
+                lds_order();
+            }
+            nh += used;
+            if (used > 0) T = bcast(Ta, used - 1);
+            if (cut || m < 64) break;
+            after = bcast(kb, 63);
+        }
+    }
+    if (lane == 0) {
+        out.O[r] = acc;
+        if (out.T) out.T[r] = T;
+        if (out.n_hits) out.n_hits[r] = nh;
+    }
+    if (lane == 1) out.D[r] = acc;
+    if (lane >= 2 && lane < 2 + FO) out.feat[r * FO + lane - 2] = acc;
+    if (62 + lane < FO) out.feat[r * FO + 62 + lane] = acc2;
+}
+
+// Every wave of a launch runs this.  Without claim counters wave b traces slot
+// b.  With them (a persistent grid) the slots are dealt in chunks of
+// kWaveChunk to kWaveParts parts, and a wave claims one slot at a time from
+// the part of its XCD (blocks are handed to the XCDs in turn), then from the
+// other parts: rays next to each other in the caller's order are then traced
+// at about the same time on the CUs behind one L2, and eight counters share
+// the claims (a single counter takes one claim every 12 ns).  One million
+// surfels, 4.2M rays, 64 per origin: one counter and 8 slots per claim 61 ms,
+// this 34 ms; 2 / 4 slots per claim 40 / 46 ms; chunks of 64 to 1,024 alike.
+template <int CM, class Source>
+__device__ __forceinline__ void trace_waves(const Source& src, unsigned long long* next, const TraceParams& P,
+                                            lds_u32* lds, int reserve)
+{
+    const int lane = threadIdx.x;
+    const int64_t total = src.total();
+    int part = blockIdx.x & (kWaveParts - 1), left = kWaveParts;
+    int64_t slot = blockIdx.x;
+    while (true) {
+        if (next) {
+            unsigned long long b = 0;
+            if (lane == 0) b = atomicAdd(next + part * kWaveClaimStride, 1ull);
+            const int64_t i = static_cast<int64_t>(bcast(static_cast<uint64_t>(b), 0));
+            slot = (i / kWaveChunk * kWaveParts + part) * kWaveChunk + i % kWaveChunk;
+        }
+        if (slot >= total) {
+            if (!next || --left == 0) return;
+            part = (part + 1) & (kWaveParts - 1);  // this part is used up: help the next
+            continue;
+        }
+        int item;
+        int64_t r = src.locate(slot, lane, &item);
+        r = static_cast<int64_t>(bcast(static_cast<uint64_t>(r), 0));  // the same in every lane: into scalars
+        item = bcast(item, 0);
+        const Ray v = src.ray(r, item);
+        Ray ray;
+        ray.ox = bcast(v.ox, 0), ray.oy = bcast(v.oy, 0), ray.oz = bcast(v.oz, 0);
+        ray.dx = bcast(v.dx, 0), ray.dy = bcast(v.dy, 0), ray.dz = bcast(v.dz, 0);
+        trace_ray_wave<CM>(src.view(item), P, ray, r, src.out(item), lds, reserve, lane);
+        if (!next) return;
+    }
+}
+
+}  // namespace irgs
