@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -42,6 +43,11 @@ struct irgs_scene_s {
     int leaf_size = kLeafDefault;
     bool ploc = true;
     std::vector<int> levels;  // level offsets of the refit (host)
+    std::vector<int> wide_levels;
+    // The records' cluster bounds are set (per-lane launches queue the kernel
+    // that sets them; a record without them culls nothing, so a launch on
+    // another stream that overtakes it is only slower).
+    std::atomic<bool> bounds{false};
 };
 
 namespace {
@@ -151,6 +157,7 @@ BuildArgs build_args(irgs_scene s)
     a.counters = s->counters;
     a.level_nodes = reinterpret_cast<int*>(s->counters);
     a.levels = &s->levels;
+    a.wide_levels = &s->wide_levels;
     a.depth = s->depth;
     a.brange = s->brange;
     a.wnodes = s->wnodes;
@@ -172,6 +179,14 @@ SceneView view_of(irgs_scene s)
     v.n = static_cast<int32_t>(s->n);
     v.F = s->F;
     return v;
+}
+
+hipError_t need_cluster_bounds(irgs_scene s, hipStream_t st)
+{
+    if (s->bounds.load()) return hipSuccess;
+    const hipError_t e = lbvh_cluster_bounds(build_args(s), st);
+    if (e == hipSuccess) s->bounds.store(true);
+    return e;
 }
 
 // Entries a traversal stack can hold at most: every wide level above the
@@ -509,6 +524,7 @@ irgs_status irgs_scene_build(irgs_scene s, const irgs_params* p, void* stream)
     hipFree(scratch);
     if (e != hipSuccess) return hip_fail(e, "build");
     s->max_depth = depth;
+    s->bounds.store(false);
     s->built = true;
     return IRGS_OK;
 }
@@ -517,6 +533,7 @@ irgs_status irgs_scene_refit(irgs_scene s, void* stream)
 {
     if (!s) return fail(IRGS_E_INVALID, "scene is NULL");
     if (!s->built) return fail(IRGS_E_STATE, "scene is not built");
+    s->bounds.store(false);
     hipError_t e = lbvh_refit(build_args(s), static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "refit");
     return IRGS_OK;
@@ -543,6 +560,7 @@ irgs_status irgs_trace(irgs_scene s, const irgs_params* p, int64_t R, const floa
     hipError_t e = ovf.alloc(thr * slots * sizeof(int), hs);
     if (e == hipSuccess && bvh) e = dq.alloc(kClaimBytes + thr * 2 * kDeferCap * sizeof(int), hs);
     if (e == hipSuccess && sorted) e = srt.alloc(ray_sort_words(R) * sizeof(float), hs);
+    if (e == hipSuccess && bvh && lanes) e = need_cluster_bounds(s, hs);
     if (e != hipSuccess) return hip_fail(e, "trace scratch");
     const SceneView sv = view_of(s);
     FlatScratch fs = flat_scratch(ovf.p, slots, dq.p, s->wide_depth);
@@ -579,7 +597,11 @@ irgs_status irgs_trace_noalloc(irgs_scene s, const irgs_params* p, int64_t R, co
     FlatScratch fs = flat_scratch(base + kClaimBytes, slots, base, s->wide_depth);
     fs.dbuf = nullptr;  // placed by the launch after every thread's overflow slots
     fs.fixed_words = words;
-    const hipError_t e = launch_trace(view_of(s), trace_params(p, s->F), p->k, bvh, R, ro, rd, out_ptrs(out), fs,
+    hipError_t e = hipSuccess;
+    if (bvh && !use_wave_trace(bvh, out->counters != nullptr, s->wide_depth))
+        e = need_cluster_bounds(s, static_cast<hipStream_t>(stream));
+    if (e != hipSuccess) return hip_fail(e, "cluster bounds");
+    e = launch_trace(view_of(s), trace_params(p, s->F), p->k, bvh, R, ro, rd, out_ptrs(out), fs,
                                       static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return hip_fail(e, "trace launch");
     return IRGS_OK;
@@ -637,6 +659,7 @@ irgs_status irgs_trace_backward(irgs_scene s, const irgs_params* p, int64_t R, c
     if (e == hipSuccess && sorted) e = srt.alloc(ray_sort_words(B) * sizeof(float), hs);
     if (e == hipSuccess) e = ck.alloc(backward_scratch_words(B, s->n, s->F) * sizeof(float), hs);
     if (e == hipSuccess) e = lists.alloc(static_cast<size_t>(B) * per_ray, hs);
+    if (e == hipSuccess && lane_thr > 0) e = need_cluster_bounds(s, hs);
     if (e != hipSuccess) return hip_fail(e, "backward scratch");
     OutPtrs tmp{};
     tmp.hit_ids = static_cast<int32_t*>(lists.p);
@@ -721,6 +744,7 @@ irgs_status irgs_trace_packed(const irgs_scene* scenes, int32_t n_scenes, const 
     hipError_t e = meta.alloc(items_off + wb, hs);
     if (e == hipSuccess) e = ovf.alloc(thr * slots * sizeof(int), hs);
     if (e == hipSuccess) e = dq.alloc(kClaimBytes + thr * 2 * kDeferCap * sizeof(int), hs);
+    for (int i = 0; e == hipSuccess && thr > 0 && i < n_scenes; ++i) e = need_cluster_bounds(scenes[i], hs);
     if (e != hipSuccess) return hip_fail(e, "packed scratch");
     char* base = static_cast<char*>(meta.p);
     SceneView* dviews = reinterpret_cast<SceneView*>(base);

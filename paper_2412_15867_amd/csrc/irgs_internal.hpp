@@ -29,6 +29,7 @@ struct BuildArgs {
     uint32_t* counters;     // unused by the level refit (kept for the buffer layout)
     int* level_nodes;       // internal node ids grouped by depth
     std::vector<int>* levels;  // host: level offsets into level_nodes (depth + 2 entries)
+    std::vector<int>* wide_levels;  // host: first node of each level of the wide tree, then their number
     int* depth;             // device int: max number of internal ancestors of a leaf
     int2* brange;           // per binary node: first leaf, leaf count
     WideNode* wnodes;       // up to max(N - 1, 1) wide nodes
@@ -44,6 +45,9 @@ hipError_t lbvh_sort_scratch_bytes(int n, size_t* bytes);
 // Build: synchronises `st` (the wide collapse reads each level's size back).
 hipError_t lbvh_build(BuildArgs& a, void* scratch, hipStream_t st);
 hipError_t lbvh_refit(const BuildArgs& a, hipStream_t st);
+// The bounds of each leaf cluster's remaining records (k_cluster_slabs), which
+// only the per-lane forward reads: records are built without them (no culls).
+hipError_t lbvh_cluster_bounds(const BuildArgs& a, hipStream_t st);
 
 struct OutPtrs {
     float* O;

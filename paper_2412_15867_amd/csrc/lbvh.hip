@@ -529,6 +529,88 @@ __global__ void k_cluster_slabs(int nw, const WideNode* __restrict__ wn, SurfelR
     }
 }
 
+// Slabs of the children of wide nodes [begin, begin + count) (see Slab):  N
+// is the mean of the normals below, each turned to the first one's side,
+// rounded to integers; H is measured against the rounded N.  A cluster's comes
+// from its records; an inner child's from its own four children, whose
+// discs lie in box and slab alike: along N they reach at most the box's
+// extent, or their slab's thickness turned by the angle between the normals
+// plus the box's diagonal times its sine.
+__global__ void k_child_slabs(int begin, int count, WideNode* wn, const SurfelRec* __restrict__ rec)
+{
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= 4 * count) return;
+    WideChild* out = &wn[begin + (t >> 2)].c[t & 3];
+    WideChild w = *out;
+    const float inf = __int_as_float(0x7f800000);
+    if (w.ref == kNoChild || !(w.lo[0] < inf)) return;  // never crossed
+    const bool leaf = (w.ref & kLeafBit) != 0;
+    const int first = (w.ref & ~kLeafBit) >> 4, cnt = (w.ref & 15) + 1;
+    float n[3] = {0.0f, 0.0f, 0.0f};
+    for (int j = 0; j < (leaf ? cnt : 4); ++j) {
+        float m[3];
+        if (leaf) {
+            const SurfelRec s = rec[first + j];
+            if (s.b.w < 0.0f) continue;  // never hits
+            m[0] = s.b.x, m[1] = s.b.y, m[2] = s.b.z;
+        } else {
+            const WideChild c = wn[w.ref].c[j];
+            if (c.ref == kNoChild || !(c.lo[0] < inf)) continue;
+            const Slab s = child_slab(c);
+            const float inv = 1.0f / sqrtf(dot3(s.nx, s.ny, s.nz, s.nx, s.ny, s.nz));
+            m[0] = s.nx * inv, m[1] = s.ny * inv, m[2] = s.nz * inv;
+        }
+        const float sg = dot3(n[0], n[1], n[2], m[0], m[1], m[2]) < 0.0f ? -1.0f : 1.0f;
+        for (int a = 0; a < 3; ++a) n[a] += sg * m[a];
+    }
+    const float big = fmaxf(fmaxf(fabsf(n[0]), fabsf(n[1])), fabsf(n[2]));
+    w.slab = kSlabNone;
+    if (big > 0.0f && big < inf) {
+        uint32_t code = 0;
+        for (int a = 0; a < 3; ++a) code |= static_cast<uint32_t>(static_cast<int>(rintf(127.0f * n[a] / big)) + 128) << (8 * a);
+        w.slab = 0xff000000u | code;
+        const Slab me = child_slab(w);  // H = the box's extent
+        const float nn = sqrtf(dot3(me.nx, me.ny, me.nz, me.nx, me.ny, me.nz));
+        float need = 0.0f;
+        for (int j = 0; j < (leaf ? cnt : 4); ++j) {
+            float reach;
+            if (leaf) {
+                const SurfelRec s = rec[first + j];
+                if (s.b.w < 0.0f) continue;
+                const float ex = fmaf(2.0f, s.a.x, -me.cx), ey = fmaf(2.0f, s.a.y, -me.cy), ez = fmaf(2.0f, s.a.z, -me.cz);
+                const float uu = dot3(s.c.x, s.c.y, s.c.z, s.c.x, s.c.y, s.c.z);
+                const float vv = dot3(s.d.x, s.d.y, s.d.z, s.d.x, s.d.y, s.d.z);
+                const float cu = dot3(me.nx, me.ny, me.nz, s.c.x, s.c.y, s.c.z) / uu;
+                const float cv = dot3(me.nx, me.ny, me.nz, s.d.x, s.d.y, s.d.z) / vv;
+                reach = fabsf(dot3(me.nx, me.ny, me.nz, ex, ey, ez)) + 2.0f * sqrtf(s.b.w) * sqrtf(fmaf(cu, cu, cv * cv));
+            } else {
+                const WideChild c = wn[w.ref].c[j];
+                if (c.ref == kNoChild || !(c.lo[0] < inf)) continue;
+                const Slab s = child_slab(c);
+                const float ns = sqrtf(dot3(s.nx, s.ny, s.nz, s.nx, s.ny, s.nz));
+                const float cosd = fminf(fabsf(dot3(me.nx, me.ny, me.nz, s.nx, s.ny, s.nz)) / (nn * ns), 1.0f);
+                const float sind = sqrtf(fmaxf(0.0f, 1.0f - cosd * cosd)) + 1e-3f;
+                const float e[3] = {c.hi[0] - c.lo[0], c.hi[1] - c.lo[1], c.hi[2] - c.lo[2]};
+                const float box = fabsf(me.nx) * e[0] + fabsf(me.ny) * e[1] + fabsf(me.nz) * e[2];
+                const float thin = nn * (s.h / ns * cosd + sqrtf(dot3(e[0], e[1], e[2], e[0], e[1], e[2])) * sind);
+                reach = fabsf(dot3(me.nx, me.ny, me.nz, s.cx - me.cx, s.cy - me.cy, s.cz - me.cz)) + fminf(box, thin);
+            }
+            need = reach > need || reach != reach ? reach : need;
+        }
+        float far = 0.0f;
+        for (int a = 0; a < 3; ++a) far = fmaxf(far, fmaxf(fabsf(w.lo[a]), fabsf(w.hi[a])));
+        need = fmaf(need, 1.001f, 4.4e-4f * (1.0f + far));  // rounding of the sums above
+        const float part = need / me.h * 255.0f;
+        uint32_t q = part < 254.0f ? static_cast<uint32_t>(part) + 1u : 255u;  // NaN: 255
+        w.slab = q << 24 | code;
+        while (q < 255u && !(child_slab(w).h >= need)) {
+            ++q;
+            w.slab = q << 24 | code;
+        }
+    }
+    out->slab = w.slab;
+}
+
 __global__ void k_depth(int n, const int* __restrict__ leaf_parent, const BvhNode* __restrict__ nodes,
                         int* __restrict__ depth_out)
 {
@@ -620,7 +702,7 @@ __global__ void k_collapse(int nfront, const int* __restrict__ front_in, int* __
     const float inf = __int_as_float(0x7f800000);
     const float empty[6] = {inf, inf, inf, inf, inf, inf};
     for (int c = 0; c < 4; ++c) {
-        node.c[c].pad = 0;
+        node.c[c].slab = kSlabNone;
         if (c >= m) {
             set_wide_box(&node, c, empty);
             node.c[c].ref = kNoChild;
@@ -998,6 +1080,21 @@ static hipError_t refit_boxes(const BuildArgs& a, hipStream_t st)
     return e;
 }
 
+// Slabs of the wide tree's children, deepest level first (an inner child's
+// come from its own children's).
+static hipError_t child_slabs(const BuildArgs& a, hipStream_t st)
+{
+    const std::vector<int>& off = *a.wide_levels;
+    hipError_t e = hipSuccess;
+    for (int d = static_cast<int>(off.size()) - 2; e == hipSuccess && d >= 0; --d) {
+        const int cnt = off[d + 1] - off[d];
+        if (cnt <= 0) continue;
+        k_child_slabs<<<blocks_for(4 * static_cast<int64_t>(cnt), 256), 256, 0, st>>>(off[d], cnt, a.wnodes, a.rec);
+        e = hipGetLastError();
+    }
+    return e;
+}
+
 // Internal nodes grouped by depth (root = depth 0): a.level_nodes holds their
 // ids level after level and *a.levels the level offsets (depth + 2 entries).
 // Uses the build scratch and reads the level sizes back (synchronises st).
@@ -1109,7 +1206,10 @@ hipError_t lbvh_build(BuildArgs& a, void* scratch, hipStream_t st)
         int* counts = a.wscratch + 3 * nmax;
         k_collapse_init<<<1, 1, 0, st>>>(wide_src, fa, counts);
         int nfront = 1, levels = 0;
+        std::vector<int>& off = *a.wide_levels;
+        off.assign(1, 0);
         while (nfront > 0) {
+            off.push_back(off.back() + nfront);  // a level's nodes are numbered together
             e = fill_u32(counts + 1, 1, 0u, st);
             if (e != hipSuccess) return e;
             k_collapse<<<blocks_for(nfront, 128), 128, 0, st>>>(nfront, fa, fb, counts, wide_src, a.nodes,
@@ -1130,12 +1230,8 @@ hipError_t lbvh_build(BuildArgs& a, void* scratch, hipStream_t st)
         a.n_wide = nw;
         a.wide_depth = levels;
     }
-    if (a.n_wide > 0) {
-        k_cluster_slabs<<<blocks_for(4 * static_cast<int64_t>(a.n_wide), 256), 256, 0, st>>>(a.n_wide, a.wnodes,
-                                                                                            a.rec);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
+    e = child_slabs(a, st);
+    if (e != hipSuccess) return e;
     e = fill_u32(a.depth, 1, 0u, st);
     if (e != hipSuccess) return e;
     k_depth<<<blocks_for(n, 256), 256, 0, st>>>(n, a.leaf_parent, a.nodes, a.depth);
@@ -1149,6 +1245,13 @@ hipError_t lbvh_refit(const BuildArgs& a, hipStream_t st)
     if (e != hipSuccess) return e;
     if (a.n_wide <= 0) return hipGetLastError();
     k_wide_refit<<<blocks_for(a.n_wide, 256), 256, 0, st>>>(a.n_wide, a.wsrc, a.nodes, a.wnodes);
+    e = hipGetLastError();
+    return e == hipSuccess ? child_slabs(a, st) : e;
+}
+
+hipError_t lbvh_cluster_bounds(const BuildArgs& a, hipStream_t st)
+{
+    if (a.n <= 0 || a.n_wide <= 0) return hipSuccess;
     k_cluster_slabs<<<blocks_for(4 * static_cast<int64_t>(a.n_wide), 256), 256, 0, st>>>(a.n_wide, a.wnodes, a.rec);
     return hipGetLastError();
 }

@@ -4,8 +4,8 @@
 // of Sec. 3.2 is done for many candidates at once and a ray waits for a few
 // dozen memory round trips instead of several hundred:
 //   NODE  up to 16 wide nodes are taken from the stack and their 64 child boxes
-//         tested, one per lane; crossed inner children go back on the stack
-//         (each node's nearest child on top), crossed clusters into a queue;
+//         and slabs tested, one per lane; crossed inner children go back on the
+//         stack (each node's nearest child on top), crossed clusters into a queue;
 //   LEAF  up to 64 records of the queued clusters are tested, one per lane
 //         (clusters are contiguous, so neighbouring lanes read neighbouring
 //         records); hits between the resume key and the buffer's last key
@@ -19,13 +19,17 @@
 // A round whose buffer is full and whose transmittance stays above the cutoff
 // is followed by another from the root, after the last key.
 //
-// What bounds it: the instruction issue (1M surfels, 4.2M rays: 4,250 VALU
-// and 2,190 scalar instructions per ray, the VALU busy 85% of the time at 8
-// waves per SIMD).  Against one ray per lane, whose waves stepped through 1,230
-// dependent iterations with 45% of their lanes active: 1M surfels, 4.2M rays
-// 70.3 -> 34.4 ms (122 Mrays/s); 200K surfels 36.6 -> 11.9 ms; launches smaller
-// than the chip, whose time is one ray's chain of round trips: 4,096 rays
-// 580 -> 33 us, 2^18 rays 13.9 -> 5 ms.
+// What bounds it: VALU issue (1M surfels, 4.2M rays: 4,220 VALU and 1,880
+// scalar instructions per ray, a VALU instruction in every issue slot of 4
+// cycles; 53% L2 hits, 20 KB per ray past L2).  Against one ray per lane,
+// whose waves stepped through 1,230 dependent iterations with 45% of their
+// lanes active: 1M surfels, 4.2M rays 70.3 -> 34.4 ms; 200K surfels 36.6 -> 11.9
+// ms; launches smaller than the chip, whose time is one ray's chain of round
+// trips: 4,096 rays 580 -> 33 us, 2^18 rays 13.9 -> 5 ms.  The children's slabs
+// then cull what only crosses the fat boxes of tilted patches: records tested
+// per ray 1,206 -> 718, leaf steps 21 -> 12.7, node steps 20.5 -> 18.4; 1M
+// surfels 34.4 -> 25.3 ms, 5M surfels 232 -> 128 ms (random surfels in a cube,
+// which no slab holds, pay the test: 4,096 rays 33 -> 38 us).
 //
 // The buffer content after a round is the 64 smallest keys above the resume
 // key whatever the visiting order, and results do not depend on the buffer's
@@ -296,6 +300,7 @@ __device__ __forceinline__ void trace_ray_wave(const SceneView& sc, const TraceP
                         const WideChild w = load_child(sc.wnodes, static_cast<int>(stk[sp - 1 - ni]), lane & 3);
                         float tf;
                         box_span(w, q, lo, hi, &tn, &tf);
+                        slab_span(w, ray, &tn, &tf);
                         ref = w.ref;
                         inner = tn <= tf && ref >= 0;
                         leaf = tn <= tf && ref < 0;

@@ -99,3 +99,30 @@ def test_chain_of_growing_surfels(n, ratio):
     got = trace(s, ro, rd, TraceConfig(k=16))
     same(got, trace(s, ro, rd, TraceConfig(k=16, brute_force=True)))
     assert int(got.n_hits.sum()) > 100
+
+
+@pytest.mark.parametrize("size", [0.02, 1.0, 300.0])
+@pytest.mark.parametrize("offset", [0.0, 40.0])
+@pytest.mark.parametrize("flip", [False, True])
+def test_slabs_lose_no_hit(size, offset, flip):
+    """Rays that skim their own surface and Monte Carlo rays, on scenes of
+    different size and distance from the origin, with the surfels' normals as
+    generated or turned to random sides: the slabs of the tree's children cull
+    nothing that the plain tracer hits."""
+    sc = synth.surface_scene(4000, F=3, seed=21)
+    g = np.random.Generator(np.random.PCG64(4))
+    quat = sc.quat.copy()
+    if flip:  # half a turn about t_u: the same disc, its normal on the other side
+        w, x, y, z = quat.T
+        half = np.stack([-x, w, z, -y], 1)
+        quat = np.where(g.random((4000, 1)) < 0.5, half, quat).astype(np.float32)
+    shift = np.float32(offset * size)
+    s = make_scene(synth.Surfels(sc.mu * np.float32(size) + shift, quat, sc.scale * np.float32(4 * size), sc.opac, sc.feat))
+    ro, rd = (np.concatenate(p) for p in zip(synth.grazing_rays(6000), synth.mc_rays(100, 61, seed=8)))
+    ro = torch.from_numpy(ro * np.float32(size) + shift).cuda()
+    rd = torch.from_numpy(rd).cuda()
+    got = trace(s, ro, rd, TraceConfig(k=32))
+    same(got, trace(s, ro, rd, TraceConfig(k=32, brute_force=True)))
+    assert float(got.n_hits.float().mean()) > 5
+    s.refit()
+    same(trace(s, ro, rd, TraceConfig(k=32)), got)
