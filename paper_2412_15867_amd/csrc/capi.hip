@@ -178,6 +178,17 @@ SceneView view_of(irgs_scene s)
     v.feat = s->p.feat;
     v.n = static_cast<int32_t>(s->n);
     v.F = s->F;
+    // A level whose parents all have four inner children stands for the whole
+    // tree: the wave-per-ray form starts at the deepest such level of at most
+    // 16 nodes, whose 64 boxes are one step.
+    const std::vector<int>& off = s->wide_levels;
+    v.start = 0;
+    v.n_start = 1;
+    for (size_t d = 1, full = 4; d + 1 < off.size() && full <= 16 && off[d + 1] - off[d] == static_cast<int>(full);
+         ++d, full *= 4) {
+        v.start = off[d];
+        v.n_start = static_cast<int32_t>(full);
+    }
     return v;
 }
 

@@ -49,9 +49,12 @@ struct __align__(16) BvhNode {
 // 16-byte loads and four neighbouring lanes read one 128-byte line.  A child
 // reference r >= 0 is a wide node; r with kLeafBit set is a cluster of
 // ((r & 15) + 1) surfels starting at leaf position ((r & ~kLeafBit) >> 4);
-// kNoChild is an empty slot (its box is all +inf).
+// kNoChild is an empty slot.  The box is kept as the sum of its corners
+// (twice the centre) and its extent: box and slab test share the centre.  An
+// empty box has the extent -inf, which no ray crosses; one that is not finite
+// is taken as all of space (centre 0, extent +inf).
 struct __align__(16) WideChild {
-    float lo[3], hi[3];
+    float c2[3], ext[3];
     int32_t ref;
     uint32_t slab;  // a slab that holds the child's discs (see slab_span)
 };
@@ -64,22 +67,23 @@ __device__ __forceinline__ WideChild load_child(const WideNode* __restrict__ nod
     const float4* p = reinterpret_cast<const float4*>(&nodes[node].c[slot]);
     const float4 a = p[0], b = p[1];
     WideChild w;
-    w.lo[0] = a.x, w.lo[1] = a.y, w.lo[2] = a.z;
-    w.hi[0] = a.w, w.hi[1] = b.x, w.hi[2] = b.y;
+    w.c2[0] = a.x, w.c2[1] = a.y, w.c2[2] = a.z;
+    w.ext[0] = a.w, w.ext[1] = b.x, w.ext[2] = b.y;
     w.ref = __float_as_int(b.z);
     w.slab = __float_as_uint(b.w);
     return w;
 }
 
+__device__ __forceinline__ bool child_empty(const WideChild& w) { return !(w.ext[0] >= 0.0f); }
+
 // A child's slab: bytes 0-2 are an integer normal N (N_i + 128, largest
-// component 127 in size), byte 3 its half-thickness H in 1/255 of the box's own
+// component 127 in size), byte 3 its thickness H in 1/255 of the box's own
 // extent along N; every disc below the child lies in the box and in
-// |N.(2 x - (lo + hi))| <= H.  Surfels of one surface patch share a plane, so
+// |N.(2 x - c2)| <= H.  Surfels of one surface patch share a plane, so
 // the slab is thin where the box of a tilted patch is fat.
 struct Slab {
     float nx, ny, nz;
-    float h;   // twice the half-thickness, in units of |N|
-    float cx, cy, cz;  // lo + hi: twice the centre
+    float h;  // H
 };
 
 __device__ __forceinline__ Slab child_slab(const WideChild& w)
@@ -88,10 +92,8 @@ __device__ __forceinline__ Slab child_slab(const WideChild& w)
     s.nx = static_cast<float>(w.slab & 0xffu) - 128.0f;
     s.ny = static_cast<float>((w.slab >> 8) & 0xffu) - 128.0f;
     s.nz = static_cast<float>((w.slab >> 16) & 0xffu) - 128.0f;
-    const float ext = fmaf(fabsf(s.nx), w.hi[0] - w.lo[0],
-                           fmaf(fabsf(s.ny), w.hi[1] - w.lo[1], fabsf(s.nz) * (w.hi[2] - w.lo[2])));
+    const float ext = fmaf(fabsf(s.nx), w.ext[0], fmaf(fabsf(s.ny), w.ext[1], fabsf(s.nz) * w.ext[2]));
     s.h = ext * (static_cast<float>(w.slab >> 24) * (1.0f / 255.0f));
-    s.cx = w.lo[0] + w.hi[0], s.cy = w.lo[1] + w.hi[1], s.cz = w.lo[2] + w.hi[2];
     return s;
 }
 constexpr uint32_t kSlabNone = 0xff000000u | 0xff8080u;  // N = (0, 0, 127), H = the box's extent: culls nothing
@@ -110,6 +112,7 @@ struct SceneView {
     const float* feat;      // N x F, caller layout (original ids)
     int32_t n;
     int32_t F;
+    int32_t start, n_start; // wide nodes [start, start + n_start) hold every leaf below them: a traversal's first nodes
 };
 
 // How the composited channels are formed from a hit (template argument of
@@ -232,10 +235,10 @@ __device__ __forceinline__ void root_box(const WideNode* __restrict__ root, floa
     }
     for (int c = 0; c < 4; ++c) {
         const WideChild& w = root->c[c];
-        if (w.lo[0] == inf) continue;  // empty slot
+        if (child_empty(w)) continue;
         for (int a = 0; a < 3; ++a) {
-            lo[a] = fminf(lo[a], w.lo[a]);
-            hi[a] = fmaxf(hi[a], w.hi[a]);
+            lo[a] = fminf(lo[a], 0.5f * (w.c2[a] - w.ext[a]));
+            hi[a] = fmaxf(hi[a], 0.5f * (w.c2[a] + w.ext[a]));
         }
     }
 }
@@ -259,51 +262,40 @@ __device__ __forceinline__ uint32_t morton30(const float x[3], const float lo[3]
     return code;
 }
 
-// Slab tests take the ray as (inverse direction i, no = -o * i) so that each
-// slab distance is one fma: (l - o) / d == l * i + no.  The fused form
-// rounds differently from (l - o) * i by less than an ulp of o * i, far
-// inside the padding every leaf box carries (at least 1e-5 (1 + |mu|) per
-// axis), so a box never loses a hit it contains.
-struct SlabRay {
-    float ix, iy, iz, nox, noy, noz;
+// A ray as the box tests take it: half the inverse direction and twice the
+// origin.  Per axis the ray is at the box's centre for t = (c2 - 2 o) i and
+// within it for t +- ext |i|: the difference is taken before the product, so
+// these depths are rounded by a few 1e-7 of the distance along the axis, far
+// inside the padding every leaf box carries (at least 1e-5 (1 + |mu|)).
+struct BoxRay {
+    float ix, iy, iz;
+    float ox2, oy2, oz2;
 };
 
-// Slab test of a ray against a box, returning the entry distance; the box is
-// accepted when it overlaps [lo, hi] along the ray.  `hi` must be finite.
-// An empty box is stored with every coordinate = +inf, which this test
-// always rejects (the +inf slab of an axis with positive inverse direction
-// pushes the entry to +inf, and with all inverse directions negative the
-// exit drops to -inf).
-// box_span gives the entry and exit distance clamped to [lo, hi]: the box is
-// crossed inside the window when *tn <= *tf.
-__device__ __forceinline__ void box_span(const WideChild& w, const SlabRay& q, float lo, float hi, float* tn,
-                                         float* tf)
+// Entry and exit of a ray in a child's box, clamped to [lo, hi], then narrowed
+// to its slab, which the ray crosses for 2 t in (num -+ H) / den: the child is
+// crossed inside the window when *tn <= *tf.  The pad on H covers the FP32
+// rounding of these depths and of a hit's (both stay within a few 1e-7 of the
+// distances involved off the plane; 1e-5 (1 + |w|) is taken, times twice |N| <
+// 220).  A ray parallel to the plane gives infinities, which are a miss
+// outside the slab and narrow nothing inside; a NaN narrows nothing.
+__device__ __forceinline__ void child_span(const WideChild& w, const Ray& r, const BoxRay& q, float lo, float hi,
+                                           float* tn, float* tf)
 {
-    const float t0x = fmaf(w.lo[0], q.ix, q.nox), t1x = fmaf(w.hi[0], q.ix, q.nox);
-    const float t0y = fmaf(w.lo[1], q.iy, q.noy), t1y = fmaf(w.hi[1], q.iy, q.noy);
-    const float t0z = fmaf(w.lo[2], q.iz, q.noz), t1z = fmaf(w.hi[2], q.iz, q.noz);
-    *tn = fmaxf(fmaxf(fminf(t0x, t1x), fminf(t0y, t1y)), fmaxf(fminf(t0z, t1z), lo));
-    *tf = fminf(fminf(fmaxf(t0x, t1x), fmaxf(t0y, t1y)), fminf(fmaxf(t0z, t1z), hi));
-}
-
-// Narrow the span (tn, tf) of a ray in a child's box to its slab, which the
-// ray crosses for t in (num -+ h) / den.  The pad covers the FP32 rounding of
-// these depths and of a hit's (off the plane, both stay within a few 1e-7 of
-// the distances involved; 1e-5 (1 + |w|) is taken, times twice |N| < 220).
-// A ray parallel to the plane gives infinities, outside the slab a legitimate
-// miss; a NaN narrows nothing.
-__device__ __forceinline__ void slab_span(const WideChild& w, const Ray& r, float* tn, float* tf)
-{
+    const float wx = w.c2[0] - q.ox2, wy = w.c2[1] - q.oy2, wz = w.c2[2] - q.oz2;
+    const float tx = wx * q.ix, ty = wy * q.iy, tz = wz * q.iz;
+    const float ax = fabsf(q.ix), ay = fabsf(q.iy), az = fabsf(q.iz);
+    const float bn = fmaxf(fmaxf(fmaf(-w.ext[0], ax, tx), fmaf(-w.ext[1], ay, ty)), fmaf(-w.ext[2], az, tz));
+    const float bf = fminf(fminf(fmaf(w.ext[0], ax, tx), fmaf(w.ext[1], ay, ty)), fmaf(w.ext[2], az, tz));
     const Slab s = child_slab(w);
-    const float wx = fmaf(-2.0f, r.ox, s.cx), wy = fmaf(-2.0f, r.oy, s.cy), wz = fmaf(-2.0f, r.oz, s.cz);
     const float num = dot3(s.nx, s.ny, s.nz, wx, wy, wz);
     const float den = dot3(s.nx, s.ny, s.nz, r.dx, r.dy, r.dz);
     const float far = fmaxf(fmaxf(fabsf(wx), fabsf(wy)), fabsf(wz));
     const float h = fmaf(far, 4.4e-3f, s.h + 4.4e-3f);
     const float inv = 0.5f * __builtin_amdgcn_rcpf(den);
     const float ta = (num - h) * inv, tb = (num + h) * inv;
-    *tn = fmaxf(*tn, fminf(ta, tb));
-    *tf = fminf(*tf, fmaxf(ta, tb));
+    *tn = fmaxf(fmaxf(bn, lo), fminf(ta, tb));
+    *tf = fminf(fminf(bf, hi), fmaxf(ta, tb));
 }
 
 // View-dependent colour (Sec. 3.1: each surfel's colour is modelled by
@@ -364,11 +356,11 @@ __device__ __forceinline__ float safe_inv(float d)
     return 1.0f / dd;
 }
 
-__device__ __forceinline__ SlabRay slab_ray(const Ray& r)
+__device__ __forceinline__ BoxRay box_ray(const Ray& r)
 {
-    SlabRay q;
-    q.ix = safe_inv(r.dx), q.iy = safe_inv(r.dy), q.iz = safe_inv(r.dz);
-    q.nox = -(r.ox * q.ix), q.noy = -(r.oy * q.iy), q.noz = -(r.oz * q.iz);
+    BoxRay q;
+    q.ix = 0.5f * safe_inv(r.dx), q.iy = 0.5f * safe_inv(r.dy), q.iz = 0.5f * safe_inv(r.dz);
+    q.ox2 = 2.0f * r.ox, q.oy2 = 2.0f * r.oy, q.oz2 = 2.0f * r.oz;
     return q;
 }
 

@@ -543,7 +543,7 @@ __global__ void k_child_slabs(int begin, int count, WideNode* wn, const SurfelRe
     WideChild* out = &wn[begin + (t >> 2)].c[t & 3];
     WideChild w = *out;
     const float inf = __int_as_float(0x7f800000);
-    if (w.ref == kNoChild || !(w.lo[0] < inf)) return;  // never crossed
+    if (w.ref == kNoChild || child_empty(w)) return;  // never crossed
     const bool leaf = (w.ref & kLeafBit) != 0;
     const int first = (w.ref & ~kLeafBit) >> 4, cnt = (w.ref & 15) + 1;
     float n[3] = {0.0f, 0.0f, 0.0f};
@@ -555,7 +555,7 @@ __global__ void k_child_slabs(int begin, int count, WideNode* wn, const SurfelRe
             m[0] = s.b.x, m[1] = s.b.y, m[2] = s.b.z;
         } else {
             const WideChild c = wn[w.ref].c[j];
-            if (c.ref == kNoChild || !(c.lo[0] < inf)) continue;
+            if (c.ref == kNoChild || child_empty(c)) continue;
             const Slab s = child_slab(c);
             const float inv = 1.0f / sqrtf(dot3(s.nx, s.ny, s.nz, s.nx, s.ny, s.nz));
             m[0] = s.nx * inv, m[1] = s.ny * inv, m[2] = s.nz * inv;
@@ -577,7 +577,8 @@ __global__ void k_child_slabs(int begin, int count, WideNode* wn, const SurfelRe
             if (leaf) {
                 const SurfelRec s = rec[first + j];
                 if (s.b.w < 0.0f) continue;
-                const float ex = fmaf(2.0f, s.a.x, -me.cx), ey = fmaf(2.0f, s.a.y, -me.cy), ez = fmaf(2.0f, s.a.z, -me.cz);
+                const float ex = fmaf(2.0f, s.a.x, -w.c2[0]), ey = fmaf(2.0f, s.a.y, -w.c2[1]),
+                            ez = fmaf(2.0f, s.a.z, -w.c2[2]);
                 const float uu = dot3(s.c.x, s.c.y, s.c.z, s.c.x, s.c.y, s.c.z);
                 const float vv = dot3(s.d.x, s.d.y, s.d.z, s.d.x, s.d.y, s.d.z);
                 const float cu = dot3(me.nx, me.ny, me.nz, s.c.x, s.c.y, s.c.z) / uu;
@@ -585,20 +586,20 @@ __global__ void k_child_slabs(int begin, int count, WideNode* wn, const SurfelRe
                 reach = fabsf(dot3(me.nx, me.ny, me.nz, ex, ey, ez)) + 2.0f * sqrtf(s.b.w) * sqrtf(fmaf(cu, cu, cv * cv));
             } else {
                 const WideChild c = wn[w.ref].c[j];
-                if (c.ref == kNoChild || !(c.lo[0] < inf)) continue;
+                if (c.ref == kNoChild || child_empty(c)) continue;
                 const Slab s = child_slab(c);
                 const float ns = sqrtf(dot3(s.nx, s.ny, s.nz, s.nx, s.ny, s.nz));
                 const float cosd = fminf(fabsf(dot3(me.nx, me.ny, me.nz, s.nx, s.ny, s.nz)) / (nn * ns), 1.0f);
                 const float sind = sqrtf(fmaxf(0.0f, 1.0f - cosd * cosd)) + 1e-3f;
-                const float e[3] = {c.hi[0] - c.lo[0], c.hi[1] - c.lo[1], c.hi[2] - c.lo[2]};
+                const float* e = c.ext;
                 const float box = fabsf(me.nx) * e[0] + fabsf(me.ny) * e[1] + fabsf(me.nz) * e[2];
                 const float thin = nn * (s.h / ns * cosd + sqrtf(dot3(e[0], e[1], e[2], e[0], e[1], e[2])) * sind);
-                reach = fabsf(dot3(me.nx, me.ny, me.nz, s.cx - me.cx, s.cy - me.cy, s.cz - me.cz)) + fminf(box, thin);
+                reach = fabsf(dot3(me.nx, me.ny, me.nz, c.c2[0] - w.c2[0], c.c2[1] - w.c2[1], c.c2[2] - w.c2[2])) + fminf(box, thin);
             }
             need = reach > need || reach != reach ? reach : need;
         }
         float far = 0.0f;
-        for (int a = 0; a < 3; ++a) far = fmaxf(far, fmaxf(fabsf(w.lo[a]), fabsf(w.hi[a])));
+        for (int a = 0; a < 3; ++a) far = fmaxf(far, 0.5f * (fabsf(w.c2[a]) + w.ext[a]));
         need = fmaf(need, 1.001f, 4.4e-4f * (1.0f + far));  // rounding of the sums above
         const float part = need / me.h * 255.0f;
         uint32_t q = part < 254.0f ? static_cast<uint32_t>(part) + 1u : 255u;  // NaN: 255
@@ -641,9 +642,19 @@ __device__ __forceinline__ float box_area(const float* b)
 
 __device__ __forceinline__ void set_wide_box(WideNode* w, int slot, const float* b)
 {
+    const float inf = __int_as_float(0x7f800000);
+    WideChild& c = w->c[slot];
+    bool finite = true;
     for (int k = 0; k < 3; ++k) {
-        w->c[slot].lo[k] = b[k];
-        w->c[slot].hi[k] = b[k + 3];
+        const float c2 = b[k] + b[k + 3];
+        c.c2[k] = c2;
+        c.ext[k] = fmaxf(fmaf(2.0f, b[k + 3], -c2), fmaf(-2.0f, b[k], c2)) * 1.000001f;  // both corners, rounded out
+        finite = finite && isfinite(c2) && isfinite(c.ext[k]);
+    }
+    if (finite && !box_empty(b)) return;
+    for (int k = 0; k < 3; ++k) {
+        c.c2[k] = 0.0f;
+        c.ext[k] = box_empty(b) ? -inf : inf;
     }
 }
 

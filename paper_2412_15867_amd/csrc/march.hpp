@@ -133,7 +133,7 @@ __device__ __forceinline__ glb_int* as_glb(int* p) { return (glb_int*)p; }
 // cluster leaves are tested on the spot, inner children are visited nearest
 // first (the others are pushed farthest first).
 template <int K>
-__device__ __forceinline__ void collect_bvh(KBuf<K>& kb, const SceneView& sc, const Ray& ray, const SlabRay& q,
+__device__ __forceinline__ void collect_bvh(KBuf<K>& kb, const SceneView& sc, const Ray& ray, const BoxRay& q,
                                             float t_min, float t_max, uint64_t after, Stack& st,
                                             Counters& ct)
 {
@@ -153,7 +153,7 @@ __device__ __forceinline__ void collect_bvh(KBuf<K>& kb, const SceneView& sc, co
         for (int c = 0; c < 4; ++c) {
             const WideChild w = load_child(sc.wnodes, node, c);
             float tn, tf;
-            box_span(w, q, lo, hi, &tn, &tf);
+            child_span(w, ray, q, lo, hi, &tn, &tf);
             const bool h = tn <= tf;
             const bool leaf = w.ref < 0;  // cluster (kNoChild never passes the box test)
             leaves |= (h && leaf) ? (1 << c) : 0;

@@ -323,7 +323,7 @@ __device__ __forceinline__ void bwd_remarch(const SceneView& sc, const RawSurfel
 {
     float S = 0.0f;
     Counters ct;
-    const SlabRay q = slab_ray(ray);
+    const BoxRay q = box_ray(ray);
     uint64_t after = 0;
     float T = 1.0f;
     int nh = 0;

@@ -276,7 +276,7 @@ __device__ __forceinline__ void trace_flat(const Source& src, unsigned long long
     const float inf = __int_as_float(0x7f800000);
     LaneRay lr;
     Ray ray;
-    SlabRay q{};
+    BoxRay q{};
     float T = 1.0f, O = 0.0f, D = 0.0f;
     float acc[FM];
 #pragma unroll
@@ -352,7 +352,7 @@ __device__ __forceinline__ void trace_flat(const Source& src, unsigned long long
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     ref[c] = w[c].ref;
-                    box_span(w[c], q, lo, tmax_c, &tn[c], &tf[c]);
+                    child_span(w[c], ray, q, lo, tmax_c, &tn[c], &tf[c]);
                     // an empty slot has an all +inf box, which is never crossed
                     const bool crossed = tn[c] <= tf[c];
                     const bool inside = crossed && tn[c] <= hi;
@@ -437,7 +437,7 @@ __device__ __forceinline__ void trace_flat(const Source& src, unsigned long long
                     if (src.view(lr).n <= 0 || !ray_valid(ray)) {
                         write_result<FM, CM>(src, lr, O, D, T, acc, nh, ct);
                     } else {
-                        q = slab_ray(ray);
+                        q = box_ray(ray);
                         cur = 0;
                         st.sp = 0;
                         ++ct.rounds;

@@ -40,7 +40,7 @@ __device__ __forceinline__ void trace_one(const SceneView& sc, const TraceParams
     int nh = 0;
     Counters ct;
     if (sc.n > 0 && ray_valid(ray)) {
-        const SlabRay q = slab_ray(ray);
+        const BoxRay q = box_ray(ray);
         uint64_t after = 0;  // resume key: hits strictly above it (0 = from the start)
         bool done = false;
         while (!done) {
