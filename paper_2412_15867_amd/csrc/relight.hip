@@ -75,83 +75,137 @@ __device__ __forceinline__ int texel_of(float x, float y, float z, int E)
     return (face * E + row) * E + col;
 }
 
-// GGX D of the unit vectors c, h (alpha = r^2), with q = (c.h)^2 (alpha^2 - 1) + 1
-// evaluated as |c x h|^2 + (c.h)^2 alpha^2 (no cancellation near the peak).
-__device__ __forceinline__ float ggx(const float* c, const float* h, float r)
-{
-    const float a2 = (r * r) * (r * r);
-    const float ch = c[0] * h[0] + c[1] * h[1] + c[2] * h[2];
-    const float x = c[1] * h[2] - c[2] * h[1], y = c[2] * h[0] - c[0] * h[2], z = c[0] * h[1] - c[1] * h[0];
-    const float q = fmaf(ch * ch, a2, x * x + y * y + z * z);
-    return a2 / (kPiR * q * q);
-}
-
 __device__ __forceinline__ float smith(float l, float v, float r)
 {
     const float k = (r + 1.0f) * (r + 1.0f) * 0.125f;
     return l / (l * (1.0f - k) + k) * (v / (v * (1.0f - k) + k));
 }
 
-// One output texel per thread, every input texel summed (FP32 accumulate of
-// at most 6 E^2 terms).
-__global__ void k_irradiance(int E, const float* __restrict__ env, float* __restrict__ irr)
+// Sums over all input texels for kSkyOut output texels per block.  The
+// threads of a block split the input texels kSkySplit ways (a lane's output is
+// lane & 15, its part of each input tile the rest of its index), so a sky of
+// 6 x 32^2 texels fills the chip where one output texel per thread left 98% of
+// it idle, and the FP32 running sums are 64 times shorter.  A tile's
+// directions, solid angles and radiances are put in LDS once per block.  With
+// the unit half vector h of c and w, |c x h|^2 = |w - c|^2 / 4 and (c . h)^2 =
+// |w + c|^2 / 4, so the lobe needs neither h nor a square root, and keeps its
+// accuracy near the peak (q = |c x h|^2 + (c . h)^2 alpha^2).  VALU-bound:
+// about 12 instructions per pair of texels and level; E = 32, 8 levels:
+// 3,816 + 2,473 us (prefilter and irradiance, texel directions recomputed for
+// every pair) -> 122 us together.
+constexpr int kSkyOut = 16;
+constexpr int kSkyThreads = 512;
+constexpr int kSkySplit = kSkyThreads / kSkyOut;
+constexpr int kSkyTile = 512;
+
+// Levels [l0, l0 + MC) (those below M are stored) and, with IRR, the irradiance.
+template <int MC, bool IRR>
+__global__ __launch_bounds__(kSkyThreads) void k_sky(int E, int M, int l0, const float* __restrict__ env,
+                                                     float* __restrict__ irr, float* __restrict__ pref)
 {
+    constexpr int kSums = 4 * MC + (IRR ? 3 : 0);
+    __shared__ float4 dirs[kSkyTile];  // w, solid angle
+    __shared__ float4 light[kSkyTile];
+    __shared__ float red[kSkyThreads / 64][kSkyOut][kSums + 1];
     const int n = 6 * E * E;
-    const int o = blockIdx.x * blockDim.x + threadIdx.x;
-    if (o >= n) return;
+    const int tid = threadIdx.x;
+    const int o = blockIdx.x * kSkyOut + (tid & (kSkyOut - 1));
+    const int part = tid / kSkyOut;
     float c[3], dwo;
-    texel_dir(o, E, c, &dwo);
-    float acc[3] = {0, 0, 0};
-    for (int i = 0; i < n; ++i) {
-        float w[3], dw;
-        texel_dir(i, E, w, &dw);
-        const float cs = w[0] * c[0] + w[1] * c[1] + w[2] * c[2];
-        if (cs <= 0.0f) continue;
-        const float f = cs * dw;
+    texel_dir(min(o, n - 1), E, c, &dwo);
+    float a2[MC > 0 ? MC : 1];
 #pragma unroll
-        for (int ch = 0; ch < 3; ++ch) acc[ch] = fmaf(f, env[3 * i + ch], acc[ch]);
+    for (int l = 0; l < MC; ++l) {
+        const float rough = static_cast<float>(min(l0 + l, M - 1) + 1) / M;
+        a2[l] = (rough * rough) * (rough * rough);
     }
+    float sum[kSums];
 #pragma unroll
-    for (int ch = 0; ch < 3; ++ch) irr[3 * o + ch] = acc[ch];
+    for (int k = 0; k < kSums; ++k) sum[k] = 0.0f;
+    for (int t0 = 0; t0 < n; t0 += kSkyTile) {
+        __syncthreads();
+        if (t0 + tid < n) {
+            float w[3], dw;
+            texel_dir(t0 + tid, E, w, &dw);
+            dirs[tid] = make_float4(w[0], w[1], w[2], dw);
+            const float* L = env + 3 * static_cast<int64_t>(t0 + tid);
+            light[tid] = make_float4(L[0], L[1], L[2], 0.0f);
+        }
+        __syncthreads();
+        const int cnt = min(kSkyTile, n - t0);
+        for (int i = part; i < cnt; i += kSkySplit) {
+            const float4 w = dirs[i];
+            const float cs = w.x * c[0] + w.y * c[1] + w.z * c[2];
+            if (cs <= 0.0f) continue;
+            const float4 L = light[i];
+            const float f = cs * w.w;
+            if constexpr (IRR) {
+                sum[4 * MC] = fmaf(f, L.x, sum[4 * MC]);
+                sum[4 * MC + 1] = fmaf(f, L.y, sum[4 * MC + 1]);
+                sum[4 * MC + 2] = fmaf(f, L.z, sum[4 * MC + 2]);
+            }
+            if constexpr (MC > 0) {
+                const float dx = w.x - c[0], dy = w.y - c[1], dz = w.z - c[2];
+                const float sx = w.x + c[0], sy = w.y + c[1], sz = w.z + c[2];
+                const float s2 = 0.25f * fmaf(dx, dx, fmaf(dy, dy, dz * dz));  // |c x h|^2
+                const float h2 = 0.25f * fmaf(sx, sx, fmaf(sy, sy, sz * sz));  // (c . h)^2
+#pragma unroll
+                for (int l = 0; l < MC; ++l) {
+                    const float q = fmaf(h2, a2[l], s2);
+                    // D up to its constant, which the quotient drops; a2 / q in
+                    // [a2, 1 / a2] keeps it in range
+                    const float d = a2[l] * __builtin_amdgcn_rcpf(q);
+                    const float wt = d * d * f;
+                    sum[4 * l] += wt;
+                    sum[4 * l + 1] = fmaf(wt, L.x, sum[4 * l + 1]);
+                    sum[4 * l + 2] = fmaf(wt, L.y, sum[4 * l + 2]);
+                    sum[4 * l + 3] = fmaf(wt, L.z, sum[4 * l + 3]);
+                }
+            }
+        }
+    }
+    // the four parts of a wave, then the waves
+#pragma unroll
+    for (int k = 0; k < kSums; ++k) {
+        sum[k] += __shfl_xor(sum[k], 16);
+        sum[k] += __shfl_xor(sum[k], 32);
+        if ((tid & 63) < kSkyOut) red[tid >> 6][tid & 63][k] = sum[k];
+    }
+    __syncthreads();
+    for (int t = tid; t < kSkyOut * kSums; t += kSkyThreads) {
+        const int oo = t / kSums, k = t - oo * kSums;
+        float v = 0.0f;
+        for (int w = 0; w < kSkyThreads / 64; ++w) v += red[w][oo][k];
+        red[0][oo][k] = v;
+    }
+    __syncthreads();
+    for (int t = tid; t < kSkyOut * kSums; t += kSkyThreads) {
+        const int oo = t / kSums, k = t - oo * kSums;
+        const int64_t out = static_cast<int64_t>(blockIdx.x) * kSkyOut + oo;
+        if (out >= n) continue;
+        if (k >= 4 * MC) {
+            if (IRR) irr[3 * out + k - 4 * MC] = red[0][oo][k];
+        } else if ((k & 3) != 0 && l0 + k / 4 < M) {
+            pref[3 * ((l0 + k / 4) * static_cast<int64_t>(n) + out) + (k & 3) - 1] = red[0][oo][k] / red[0][oo][k & ~3];
+        }
+    }
 }
 
-__global__ void k_prefilter(int E, int M, const float* __restrict__ env, float* __restrict__ pref)
-{
-    const int n = 6 * E * E;
-    const int64_t g = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (g >= static_cast<int64_t>(n) * M) return;
-    const int l = static_cast<int>(g / n), o = static_cast<int>(g - static_cast<int64_t>(l) * n);
-    const float r = static_cast<float>(l + 1) / M;
-    float c[3], dwo;
-    texel_dir(o, E, c, &dwo);
-    float acc[3] = {0, 0, 0}, wsum = 0.0f;
-    for (int i = 0; i < n; ++i) {
-        float w[3], dw;
-        texel_dir(i, E, w, &dw);
-        const float cs = w[0] * c[0] + w[1] * c[1] + w[2] * c[2];
-        if (cs <= 0.0f) continue;
-        float h[3] = {w[0] + c[0], w[1] + c[1], w[2] + c[2]};
-        const float hn = 1.0f / sqrtf(h[0] * h[0] + h[1] * h[1] + h[2] * h[2]);
-        h[0] *= hn, h[1] *= hn, h[2] *= hn;
-        const float wt = ggx(c, h, r) * cs * dw;
-        wsum += wt;
-#pragma unroll
-        for (int k = 0; k < 3; ++k) acc[k] = fmaf(wt, env[3 * i + k], acc[k]);
-    }
-#pragma unroll
-    for (int k = 0; k < 3; ++k) pref[3 * g + k] = acc[k] / wsum;
-}
+// One cell per kTableLanes lanes, which split the 256 samples: the latency of
+// 256 dependent samples per thread took 82 us at S = 32, this 5 us.
+constexpr int kTableLanes = 32;
 
 __global__ void k_brdf_table(int S, float* __restrict__ table)
 {
-    const int cell = blockIdx.x * blockDim.x + threadIdx.x;
-    if (cell >= S * S) return;
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    const int cell = t / kTableLanes, sub = t % kTableLanes;
+    if (cell >= S * S) return;  // whole groups leave together
     const int i = cell / S, j = cell - i * S;
     const float nv = (i + 0.5f) / S, r = (j + 0.5f) / S;
     const float vx = sqrtf(1.0f - nv * nv), vz = nv;  // view in the xz plane, normal +z
     const float a2 = (r * r) * (r * r);
     float A = 0.0f, B = 0.0f;
-    for (int k = 0; k < kHammersley; ++k) {
+    for (int k = sub; k < kHammersley; k += kTableLanes) {
         const float x = (k + 0.5f) / kHammersley;
         const float y = static_cast<float>(__brev(static_cast<unsigned>(k))) * 2.3283064365386963e-10f;  // 2^-32
         // cos^2 and sin^2 of the sampled half vector over one exact
@@ -170,8 +224,15 @@ __global__ void k_brdf_table(int S, float* __restrict__ table)
         A = fmaf(1.0f - fc, g, A);
         B = fmaf(fc, g, B);
     }
-    table[2 * cell] = A / kHammersley;
-    table[2 * cell + 1] = B / kHammersley;
+#pragma unroll
+    for (int off = kTableLanes / 2; off > 0; off >>= 1) {
+        A += __shfl_xor(A, off);
+        B += __shfl_xor(B, off);
+    }
+    if (sub == 0) {
+        table[2 * cell] = A / kHammersley;
+        table[2 * cell + 1] = B / kHammersley;
+    }
 }
 
 __global__ void k_relight_lind(RelightArgs a, float* __restrict__ lind)
@@ -233,8 +294,17 @@ __global__ __launch_bounds__(kCdfBlock) void k_env_cdf(int E, const float* __res
     const int n = 6 * E * E;
     const int per = (n + kCdfBlock - 1) / kCdfBlock;
     const int b = min(static_cast<int>(threadIdx.x) * per, n), e = min(b + per, n);
+    constexpr int kKept = 8;  // weights of a run held in registers (E <= 36), not computed twice
+    double kept[kKept];
     double run = 0.0;
-    for (int i = b; i < e; ++i) run += texel_weight(i, E, env);
+#pragma unroll
+    for (int j = 0; j < kKept; ++j) kept[j] = b + j < e ? texel_weight(b + j, E, env) : 0.0;
+    if (per <= kKept) {
+#pragma unroll
+        for (int j = 0; j < kKept; ++j) run += kept[j];
+    } else {
+        for (int i = b; i < e; ++i) run += texel_weight(i, E, env);
+    }
     part[threadIdx.x] = run;
     __syncthreads();
     for (int off = 1; off < kCdfBlock; off <<= 1) {
@@ -244,6 +314,14 @@ __global__ __launch_bounds__(kCdfBlock) void k_env_cdf(int E, const float* __res
         __syncthreads();
     }
     run = threadIdx.x > 0 ? part[threadIdx.x - 1] : 0.0;
+    if (per <= kKept) {
+#pragma unroll
+        for (int j = 0; j < kKept; ++j) {
+            run += kept[j];
+            if (b + j < e) cdf[b + j] = static_cast<float>(run);
+        }
+        return;
+    }
     for (int i = b; i < e; ++i) {
         run += texel_weight(i, E, env);
         cdf[i] = static_cast<float>(run);
@@ -305,17 +383,34 @@ unsigned grid_for(int64_t n, int block)
 hipError_t launch_env_prefilter(int E, const float* env, int M, float* irr, float* pref, hipStream_t st)
 {
     const int n = 6 * E * E;
-    if (irr) k_irradiance<<<grid_for(n, 128), 128, 0, st>>>(E, env, irr);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !pref || M <= 0) return e;
-    const int64_t total = static_cast<int64_t>(n) * M;
-    k_prefilter<<<static_cast<unsigned>((total + 127) / 128), 128, 0, st>>>(E, M, env, pref);
+    const unsigned grid = static_cast<unsigned>((n + kSkyOut - 1) / kSkyOut);
+    if (!pref) M = 0;
+    // eight levels per pass over the sky (four for a short rest), the
+    // irradiance with the first
+    int l0 = 0;
+    bool first = irr != nullptr;
+    while (l0 < M || first) {
+        const int left = M - l0;
+        if (left > 4) {
+            if (first) k_sky<8, true><<<grid, kSkyThreads, 0, st>>>(E, M, l0, env, irr, pref);
+            else k_sky<8, false><<<grid, kSkyThreads, 0, st>>>(E, M, l0, env, irr, pref);
+            l0 += 8;
+        } else if (left > 0) {
+            if (first) k_sky<4, true><<<grid, kSkyThreads, 0, st>>>(E, M, l0, env, irr, pref);
+            else k_sky<4, false><<<grid, kSkyThreads, 0, st>>>(E, M, l0, env, irr, pref);
+            l0 += 4;
+        } else {
+            k_sky<0, true><<<grid, kSkyThreads, 0, st>>>(E, 1, 0, env, irr, pref);
+        }
+        first = false;
+    }
     return hipGetLastError();
 }
 
 hipError_t launch_brdf_table(int S, float* table, hipStream_t st)
 {
-    k_brdf_table<<<grid_for(static_cast<int64_t>(S) * S, 128), 128, 0, st>>>(S, table);
+    const int64_t threads = static_cast<int64_t>(S) * S * kTableLanes;
+    k_brdf_table<<<static_cast<unsigned>((threads + 127) / 128), 128, 0, st>>>(S, table);
     return hipGetLastError();
 }
 

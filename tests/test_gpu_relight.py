@@ -344,3 +344,33 @@ def test_relight_chain_and_errors():
     with pytest.raises(_lib.IrgsError):       # cube resolution out of range
         env_rays(x, n, u3, dev(np.zeros(6 * 300 * 300, F32)), 300)
     scene.close()
+
+
+@pytest.mark.parametrize("E,M", [(1, 1), (2, 0), (3, 4), (5, 5), (7, 8), (9, 9), (10, 13), (12, 32)])
+def test_sky_sizes_and_level_counts(E, M):
+    """Skies around the tiles of the summing kernel (16 output and 512 input
+    texels) and level counts around its passes of 8 and 4."""
+    from paper_2412_15867_amd import env_prefilter
+    env = np.random.default_rng(E * 100 + M).uniform(0, 3, (6, E, E, 3)).astype(F32)
+    irr, pref = env_prefilter(dev(env), M)
+    np.testing.assert_allclose(irr.cpu().numpy(), orl.irradiance(env), rtol=2e-5)
+    assert pref.shape[0] == M
+    if M:
+        # FP32 weighted means of at most 864 texels against FP64
+        np.testing.assert_allclose(pref.cpu().numpy(), orl.prefilter(env, M), rtol=1e-4)
+
+
+@pytest.mark.parametrize("S", [1, 3, 17])
+def test_table_sizes(S):
+    from paper_2412_15867_amd import brdf_table
+    np.testing.assert_allclose(brdf_table(S).cpu().numpy(), orl.brdf_table(S), atol=2e-6)
+
+
+@pytest.mark.parametrize("E", [1, 13, 36, 37, 60])
+def test_cdf_sizes(E):
+    """Runs of texels held in registers (up to E = 36) and computed twice (above)."""
+    from paper_2412_15867_amd import env_cdf
+    env = np.random.default_rng(E).uniform(0, 3, (6, E, E, 3)).astype(F32)
+    want = np.asarray(orl.env_cdf(env), dtype=np.float64).reshape(-1)
+    # FP64 sums in another order, rounded once to FP32
+    np.testing.assert_allclose(env_cdf(dev(env)).cpu().numpy(), want, rtol=1.2e-7)
