@@ -44,6 +44,7 @@
 
 #include "irgs_internal.hpp"
 #include "march.hpp"
+#include "wave_ops.hpp"
 
 namespace irgs {
 
@@ -94,13 +95,6 @@ __device__ __forceinline__ uint64_t bcast(uint64_t v, int lane)
 {
     return (static_cast<uint64_t>(static_cast<uint32_t>(bcast(static_cast<int>(v >> 32), lane))) << 32) |
            static_cast<uint32_t>(bcast(static_cast<int>(v), lane));
-}
-
-template <int Ctrl>
-__device__ __forceinline__ uint32_t dpp(uint32_t old, uint32_t v)
-{
-    return static_cast<uint32_t>(
-        __builtin_amdgcn_update_dpp(static_cast<int>(old), static_cast<int>(v), Ctrl, 0xf, 0xf, false));
 }
 
 // Lane l's value of lane l ^ X, for the X a sort of 64 needs.
@@ -156,18 +150,6 @@ __device__ __forceinline__ uint64_t wave_key(float tau, int pos, float a)
 {
     const uint32_t q = static_cast<uint32_t>(fminf(fmaf(a, 0.5f * a, a) * kDepthUnits, 15.0f));
     return hit_key(tau, static_cast<int>(static_cast<uint32_t>(pos) << 4 | q));
-}
-
-// Inclusive sum over the lanes.
-__device__ __forceinline__ uint32_t wave_scan(uint32_t v)
-{
-    v += dpp<0x111>(0u, v);
-    v += dpp<0x112>(0u, v);
-    v += dpp<0x114>(0u, v);
-    v += dpp<0x118>(0u, v);
-    v += static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x142, 0xa, 0xf, false));
-    v += static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), 0x143, 0xc, 0xf, false));
-    return v;
 }
 
 // Ascending bitonic sort of one key per lane (mirrored first stages, so every
@@ -321,10 +303,10 @@ __device__ __forceinline__ float sum_rows(float acc, const lds_f32* rows, int x,
     return acc;
 }
 
-// Trace ray r of `sc` with the whole wave.  `lds`: kWaveLdsWords words of this
+// Trace ray r of `sc` with the whole wave; returns its hits.  `lds`: kWaveLdsWords words of this
 // wave; `reserve`: stack entries kept for depth-first steps.
 template <int CM>
-__device__ __forceinline__ void trace_ray_wave(const SceneView& sc, const TraceParams& P, const Ray& ray, int64_t r,
+__device__ __forceinline__ int trace_ray_wave(const SceneView& sc, const TraceParams& P, const Ray& ray, int64_t r,
                                                const OutPtrs& out, lds_u32* lds, int reserve, int lane)
 {
     lds_u32* stk = lds;
@@ -549,6 +531,7 @@ __device__ __forceinline__ void trace_ray_wave(const SceneView& sc, const TraceP
     if (lane == 1) out.D[r] = acc;
     if (lane >= 2 && lane < 2 + FO) out.feat[r * FO + lane - 2] = acc;
     if (62 + lane < FO) out.feat[r * FO + 62 + lane] = acc2;
+    return nh;
 }
 
 // Every wave of a launch runs this.  Without claim counters wave b traces slot

@@ -126,3 +126,14 @@ def test_slabs_lose_no_hit(size, offset, flip):
     assert float(got.n_hits.float().mean()) > 5
     s.refit()
     same(trace(s, ro, rd, TraceConfig(k=32)), got)
+
+
+@pytest.mark.parametrize("R", [32_767, 32_768, 32_769, 70_001, 600_000])
+def test_sorted_launch_sizes(R):
+    """Ray sorts whose tile counters fill one, just over one and many spans of
+    the counters' scan (4,096 counters = 16 tiles of 2,048 rays)."""
+    s = make_scene(synth.surface_scene(3000, F=3, seed=3))
+    g = torch.Generator(device="cuda").manual_seed(R)
+    ro = torch.rand(R, 3, generator=g, device="cuda") * 4 - 2
+    rd = -ro / ro.norm(dim=1, keepdim=True)
+    same(trace(s, ro, rd, TraceConfig(k=16, sort_rays=True)), trace(s, ro, rd, TraceConfig(k=16)))
