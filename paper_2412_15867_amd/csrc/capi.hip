@@ -456,7 +456,7 @@ size_t irgs_trace_bytes(int64_t R, int32_t F, uint32_t flags)
         const size_t per_ray = static_cast<size_t>(kRetraceCap) * 8 + (3 + fo) * sizeof(float);
         const int64_t bmax = std::max<int64_t>(1, static_cast<int64_t>(kRetraceBytes / per_ray));
         const int64_t nb = (R + bmax - 1) / bmax;
-        b += static_cast<size_t>((R + nb - 1) / nb) * per_ray + remarch_words(R) * sizeof(float);
+        b += static_cast<size_t>((R + nb - 1) / nb) * per_ray + plan_backward((R + nb - 1) / nb, 0, F, 64).bytes;
     }
     return b;  // plus, for a backward, 4 * (ceil32(10 + F) + ceil32(12 + F)) bytes per surfel
 }
@@ -629,10 +629,9 @@ irgs_status irgs_trace_backward(irgs_scene s, const irgs_params* p, int64_t R, c
     const bool use_saved = !(p->flags & IRGS_FLAG_RECOMPUTE) && saved->hit_ids && saved->hit_T && saved->H_cap > 0;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     const TraceParams tp = trace_params(p, s->F);
-    RawSurfels raw{s->p.mu, s->p.quat, s->p.scale, s->p.opacity, s->p.feat, nullptr, pack_stride(s->F)};
+    RawSurfels raw{s->p.mu, s->p.quat, s->p.scale, s->p.opacity, s->p.feat, nullptr, pack_stride(s->F), pack_features(s->F)};
     GradIn g{gin->g_opacity, gin->g_feat, gin->g_depth};
     GradOut go{grads->mu, grads->quat, grads->scale, grads->opacity, grads->feat};
-    const int slots = stack_need(s);  // the backward keeps its whole re-march stack in global memory
     // the parameters packed one row per surfel, read by every hit's gradient
     AsyncBuf pk;
     hipError_t pe = pk.alloc(static_cast<size_t>(s->n) * raw.ps * sizeof(float), hs);
@@ -640,13 +639,11 @@ irgs_status irgs_trace_backward(irgs_scene s, const irgs_params* p, int64_t R, c
     if (pe != hipSuccess) return hip_fail(pe, "backward parameter pack");
     raw.pk = static_cast<const float*>(pk.p);
     if (use_saved) {
-        const size_t thr = static_cast<size_t>(trace_threads(R));
-        AsyncBuf ovf, ck;
-        hipError_t e = ovf.alloc(thr * slots * sizeof(int), hs);
-        if (e == hipSuccess) e = ck.alloc(backward_scratch_words(R, s->n, s->F) * sizeof(float), hs);
+        AsyncBuf ck;
+        hipError_t e = ck.alloc(plan_backward(R, s->n, s->F, s->wide_depth).bytes, hs);
         if (e != hipSuccess) return hip_fail(e, "backward scratch");
-        e = launch_backward(view_of(s), raw, tp, p->k, R, ro, rd, out_ptrs(saved), true, g, go,
-                            static_cast<int*>(ovf.p), slots, static_cast<float*>(ck.p), hs);
+        e = launch_backward(view_of(s), raw, tp, p->k, R, ro, rd, out_ptrs(saved), g, go, s->wide_depth,
+                            static_cast<char*>(ck.p), hs);
         if (e != hipSuccess) return hip_fail(e, "backward launch");
         return IRGS_OK;
     }
@@ -664,11 +661,12 @@ irgs_status irgs_trace_backward(irgs_scene s, const irgs_params* p, int64_t R, c
     const size_t thr = static_cast<size_t>(trace_threads(B));
     const bool sorted = bvh && (p->flags & IRGS_FLAG_SORT_RAYS) && ray_sort_words(B) > 0;
     AsyncBuf ovf, dq, ck, lists, srt;
-    hipError_t e = ovf.alloc(thr * slots * sizeof(int), hs);
     const size_t lane_thr = use_wave_trace(bvh, false, s->wide_depth) ? 0 : thr;  // of the retrace
+    const int slots = bvh ? ovf_slots_of(s) : 0;
+    hipError_t e = ovf.alloc(lane_thr * slots * sizeof(int), hs);
     if (e == hipSuccess && bvh) e = dq.alloc(kClaimBytes + lane_thr * 2 * kDeferCap * sizeof(int), hs);
     if (e == hipSuccess && sorted) e = srt.alloc(ray_sort_words(B) * sizeof(float), hs);
-    if (e == hipSuccess) e = ck.alloc(backward_scratch_words(B, s->n, s->F) * sizeof(float), hs);
+    if (e == hipSuccess) e = ck.alloc(plan_backward(B, s->n, s->F, s->wide_depth).bytes, hs);
     if (e == hipSuccess) e = lists.alloc(static_cast<size_t>(B) * per_ray, hs);
     if (e == hipSuccess && lane_thr > 0) e = need_cluster_bounds(s, hs);
     if (e != hipSuccess) return hip_fail(e, "backward scratch");
@@ -681,7 +679,7 @@ irgs_status irgs_trace_backward(irgs_scene s, const irgs_params* p, int64_t R, c
     tmp.feat = reinterpret_cast<float*>(tmp.n_hits + B);
     tmp.H_cap = kRetraceCap;
     const SceneView sv = view_of(s);
-    FlatScratch fs = flat_scratch(ovf.p, bvh ? ovf_slots_of(s) : 0, dq.p, s->wide_depth);
+    FlatScratch fs = flat_scratch(ovf.p, slots, dq.p, s->wide_depth);
     for (int64_t b0 = 0; b0 < R; b0 += B) {
         const int64_t nb = std::min(B, R - b0);
         const float* bro = ro + 3 * b0;
@@ -693,8 +691,7 @@ irgs_status irgs_trace_backward(irgs_scene s, const irgs_params* p, int64_t R, c
         e = launch_trace(sv, tp, p->k, bvh, nb, bro, brd, tmp, fs, hs);
         if (e != hipSuccess) return hip_fail(e, "backward retrace");
         const GradIn gb{g.gO ? g.gO + b0 : nullptr, g.gF ? g.gF + b0 * fo : nullptr, g.gD ? g.gD + b0 : nullptr};
-        e = launch_backward(sv, raw, tp, p->k, nb, bro, brd, tmp, true, gb, go, static_cast<int*>(ovf.p), slots,
-                            static_cast<float*>(ck.p), hs);
+        e = launch_backward(sv, raw, tp, p->k, nb, bro, brd, tmp, gb, go, s->wide_depth, static_cast<char*>(ck.p), hs);
         if (e != hipSuccess) return hip_fail(e, "backward launch");
     }
     return IRGS_OK;

@@ -82,15 +82,18 @@ struct RawSurfels {
     const float* opac;
     const float* feat;
     // The backward's copy of the same parameters, one row of `ps` floats per
-    // surfel id: (mu, o), q, (s_u, s_v, -, -), then the F features.  A hit
-    // then reads one 128-byte line (F <= 20) instead of five scattered ones.
+    // surfel id: (mu, o), q, (s_u, s_v, -, -), then the F features if they
+    // fit one 128-byte line with these (F <= 20; a hit then reads that line
+    // instead of five scattered ones); wider features stay in `feat`.
     const float* pk;
     int ps;
+    bool feat_packed;
 };
 
-// Floats per packed row: 12 + F rounded up to a multiple of 32.
-inline int pack_stride(int F) { return ((12 + F + 31) / 32) * 32; }
-// Fill pk (n rows of pack_stride(F) floats) from the raw arrays.
+inline bool pack_features(int F) { return F <= 20; }
+// Floats per packed row.
+inline int pack_stride(int F) { return pack_features(F) ? 32 : 16; }
+// Fill pk (n rows of raw.ps floats) from the raw arrays.
 hipError_t pack_surfels(const RawSurfels& raw, int64_t n, int F, float* pk, hipStream_t st);
 
 // Largest k-buffer / feature count the kernels are instantiated for.
@@ -173,53 +176,42 @@ hipError_t launch_trace(const SceneView& sc, const TraceParams& P, int k, bool u
                         const float* ro, const float* rd, const OutPtrs& out, const FlatScratch& fs,
                         hipStream_t st);
 
-// Backward.  Store mode reads saved ids and T (rays with n_hits > H_cap are
-// re-marched); recompute mode re-marches every ray.  `ck` is scratch of
-// backward_scratch_words(R, N, F) floats: the re-march lanes' checkpoints and
-// private hit lists, the interleaved per-surfel gradient accumulator, then a
-// chunk-claim counter.
+// True when the trace takes F features with a k-buffer of k (`special`: SH
+// colour or normal channels).
+bool features_offered(int k, int F, bool special);
+
+// Backward over saved hit lists (ids and T).  Rays with n_hits > H_cap are
+// traced again: by at most kRemarchWaves waves with lists of kRemarchList hits
+// and, with more hits (or a tree too deep for the wave form), by at most
+// kRemarchLanes lanes.
 constexpr int kBwdCheckpoints = 16;
-constexpr int kBwdClaimWords = 64;
-// Re-march lanes keep each ray's first kRemarchList hits (id and
-// transmittance) in a private list and walk it back to front; the re-march
-// launch uses at most kRemarchThreads lanes, which sizes those lists.
-constexpr int kRemarchList = 512;
-constexpr int64_t kRemarchThreads = 131072;
-inline int64_t remarch_threads(int64_t R)
-{
-    const int64_t t = trace_threads(R);
-    return t < kRemarchThreads ? t : kRemarchThreads;
-}
-// floats of the re-march area: checkpoints (4 per entry), then ids and T
-inline size_t remarch_words(int64_t R)
-{
-    return static_cast<size_t>(remarch_threads(R)) * (kBwdCheckpoints * 4 + 2 * kRemarchList);
-}
+constexpr int kRemarchList = 2048;
+constexpr int64_t kRemarchWaves = 4096;
+constexpr int64_t kRemarchLanes = 16384;
+// Rays from which on the walk takes them in the order of where they land.
+constexpr int64_t kSortWalkRays = 16384;
+// Byte offsets in the backward's scratch: the interleaved per-surfel
+// accumulator, then these.
+struct BackwardPlan {
+    size_t claims, rm_list, rest, sort, lists, stacks, checkpoints, bytes;
+    int64_t waves, lane_blocks;  // that re-march
+};
+BackwardPlan plan_backward(int64_t R, int64_t N, int F, int wide_depth);
 inline int grad_stride(int F) { return ((10 + F + 31) / 32) * 32; }
 size_t sort_pairs_count_bytes(int n);
 hipError_t sort_pairs(int n, uint64_t* k0, uint32_t* v0, uint64_t* k1, uint32_t* v1, uint32_t* counts, int passes,
                       hipStream_t st);
-// Ray order of the backward for gradients wider than its LDS table (rays
-// sorted by where they land): two key and two value buffers plus the sort's
-// tile counters, in words; none for launches too large for 32-bit indices.
+// Ray order of a launch: two key and two value buffers plus the sort's tile
+// counters, in words; none for launches too large for 32-bit indices.
 inline size_t ray_sort_words(int64_t R)
 {
     if (R <= 0 || R > 0x7fffffffLL) return 0;
     return (static_cast<size_t>(R) * (2 * sizeof(uint64_t) + 2 * sizeof(uint32_t)) +
             sort_pairs_count_bytes(static_cast<int>(R))) / sizeof(float) + 64;
 }
-inline size_t backward_scratch_words(int64_t R, int64_t N, int F)
-{
-    // the ray order is used only for gradients wider than the LDS table (the
-    // backward sorts exactly when F > 8: keep the two conditions the same)
-    // (then the list of rays to re-march, R ints, and alignment slack)
-    return remarch_words(R) + static_cast<size_t>(N) * grad_stride(F) + kBwdClaimWords + static_cast<size_t>(R) +
-           128 + (F > 8 ? ray_sort_words(R) : 0);
-}
 hipError_t launch_backward(const SceneView& sc, const RawSurfels& raw, const TraceParams& P, int k, int64_t R,
-                           const float* ro, const float* rd, const OutPtrs& saved, bool use_saved,
-                           const GradIn& gin, const GradOut& gout, int* ovf, int ovf_slots, float* ck,
-                           hipStream_t st);
+                           const float* ro, const float* rd, const OutPtrs& saved, const GradIn& gin,
+                           const GradOut& gout, int wide_depth, char* scratch, hipStream_t st);
 
 // Packed launch over work items of several scenes (serving).  Item i owns
 // the slots [chunk_begin, chunk_begin + ray_count) of the concatenation of

@@ -12,35 +12,26 @@
 // the centre, the raw quaternion (through its normalisation), the scales and
 // the opacity; per-surfel sums use FP32 global atomics.
 //
-// The hit list of a ray is either read back from the forward pass (ids and
-// the transmittance before each hit) or re-marched: a first pass records the
-// state at the start of each k-buffer round, a second pass re-collects the
-// rounds last to first and walks each one back to front.
+// The hit list of a ray is read back from the forward pass (ids and the
+// transmittance before each hit) and walked by bwd_wave.hpp.  A ray whose list
+// was cut is traced again by one wave; what does not fit that wave's list
+// either (or a tree its stack does not take) is re-marched by one lane: a first
+// pass records the state at the start of k-buffer rounds, a second re-collects
+// the rounds last to first and walks each one back to front.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "irgs_internal.hpp"
+#include "bwd_wave.hpp"
 #include "march.hpp"
 
 namespace irgs {
 
 namespace {
 
-constexpr int kBwdBlock = 64;    // one wave per block: one table per 64 consecutive rays
-constexpr int kHashProbes = 8;
-constexpr int kLdsFeat = 8;      // feature gradients pre-reduced in LDS (the rest go straight to global)
-constexpr int kLdsComp = 10 + kLdsFeat;
-// The LDS table's slots and the hits of a ray that use it (only its first
-// hits, shared by neighbouring rays).  The table is sized so that LDS allows
-// the walk's 3 waves per SIMD: 96 slots with at most 8 features staged
-// (12.3 KB per one-wave block), 64 with more (at 1M surfels, F = 8: 64 slots
-// and 24 near hits 19.2 ms, 96 and 32 18.2 ms, 96 and 40 18.4 ms, 104 and
-// 32 18.7 ms).
-template <int FM>
-struct TableShape {
-    static constexpr int slots = FM <= 8 ? 96 : 64;
-    static constexpr int near_hits = FM <= 8 ? 32 : 24;
-    static constexpr int val_row = slots + 1;
-};
+constexpr int kBwdBlock = 64;
+constexpr int kMarchK = 16;  // the re-march's k-buffer (results do not depend on it)
 
 // Per-surfel gradient components of one hit: mu (3), raw quaternion (4),
 // scales (2), opacity (1), features (F).
@@ -49,25 +40,12 @@ struct HitGrad {
     float g[10 + FM];
 };
 
-// Block-local pre-reduction: rays of one surface point share most of their
-// near hits, so their per-surfel gradients are summed in an LDS hash table
-// (LDS float atomics) and written to global memory once per chunk of rays.
-// A surfel that finds no slot within kHashProbes probes goes straight to the
-// global atomics.
-template <int kSlots>
+// The interleaved per-surfel accumulator: gbuf[id * gs + c].
 struct GradAcc {
-    static constexpr int kFill = kSlots * 3 / 4;  // no new keys once this many slots are taken
-    static constexpr int kValRow = kSlots + 1;    // value rows padded by a word: lanes reading one slot hit different banks
-    int* keys;     // kSlots, -1 = empty
-    float* vals;   // [kLdsComp][kValRow]
-    int* filled;   // slots taken in this chunk
-    float* gbuf;   // per-surfel interleaved accumulator: gbuf[id * gs + c]
-    int gs;        // stride of gbuf in floats (a multiple of 32: one 128 B line per surfel at F <= 22)
+    float* gbuf;
+    int gs;  // stride in floats (a multiple of 32: one 128 B line per surfel at F <= 22)
     int F;
 
-    __device__ __forceinline__ int ncomp() const { return 10 + F; }
-
-    // Direct accumulation of one hit (used by the re-march path).
     template <int FM>
     __device__ __forceinline__ void direct(int id, const HitGrad<FM>& h) const
     {
@@ -75,61 +53,6 @@ struct GradAcc {
 #pragma unroll
         for (int c = 0; c < 10 + FM; ++c)
             if (c < 10 + F && h.g[c] != 0.0f) atomicAdd(g + c, h.g[c]);
-    }
-
-    // Try the LDS table; on success the components below kLdsComp are
-    // accumulated there and zeroed in h (the rest stay for the caller).
-    template <int FM>
-    __device__ __forceinline__ bool table(int id, HitGrad<FM>& h) const
-    {
-        uint32_t slot = __umulhi(static_cast<uint32_t>(id) * 2654435761u, static_cast<uint32_t>(kSlots));
-        const bool may_insert = *filled < kFill;
-        int found = -1;
-        for (int p = 0; p < kHashProbes; ++p) {
-            const int k = keys[slot];
-            if (k == id) {
-                found = static_cast<int>(slot);
-                break;
-            }
-            if (k == -1) {
-                if (!may_insert) break;
-                const int prev = atomicCAS(&keys[slot], -1, id);
-                if (prev == -1) atomicAdd(filled, 1);
-                if (prev == -1 || prev == id) {
-                    found = static_cast<int>(slot);
-                    break;
-                }
-            }
-            slot = slot + 1 == kSlots ? 0 : slot + 1;
-        }
-        if (found < 0) return false;
-#pragma unroll
-        for (int c = 0; c < kLdsComp && c < 10 + FM; ++c) {
-            if (c < 10 + F) atomicAdd(vals + c * kValRow + found, h.g[c]);
-            h.g[c] = 0.0f;
-        }
-        return true;
-    }
-
-    // Table to gbuf: consecutive lanes take consecutive components of one
-    // entry, so each atomic instruction touches few cache lines.
-    __device__ __forceinline__ void flush(int tid) const
-    {
-        const int nc = 10 + (F < kLdsFeat ? F : kLdsFeat);
-        for (int flat = tid; flat < kSlots * nc; flat += kBwdBlock) {
-            const int slot = flat / nc, c = flat - slot * nc;
-            const int id = keys[slot];
-            if (id < 0) continue;
-            const float v = vals[c * kValRow + slot];
-            if (v != 0.0f) atomicAdd(gbuf + static_cast<int64_t>(id) * gs + c, v);
-        }
-    }
-
-    __device__ __forceinline__ void clear(int tid) const
-    {
-        if (tid == 0) *filled = 0;
-        for (int i = tid; i < kSlots; i += kBwdBlock) keys[i] = -1;
-        for (int i = tid; i < kLdsComp * kValRow; i += kBwdBlock) vals[i] = 0.0f;
     }
 };
 
@@ -180,7 +103,7 @@ __device__ __forceinline__ void grad_hit(const RawSurfels& raw, const TraceParam
     const double S = S_f;
 
     double c = gO + gD * tau;
-    const float* f = row + 12;
+    const float* f = raw.feat_packed ? row + 12 : raw.feat + i * F;
     const double wgt = Ti * alpha;
     if constexpr (SH) {
         float Y[16], col[3];
@@ -305,21 +228,16 @@ __device__ __forceinline__ LaneUp<FU> load_upstream(const GradIn& gin, int64_t r
     return u;
 }
 
-// Re-march one ray (no saved list, or more hits than were saved).  Pass 1
-// marches the k-buffer rounds again (the forward's arithmetic, so T is
-// reproduced bit for bit), recording each composited hit (id and the
-// transmittance before it) in the lane's private list while it fits, and
-// the state at the start of rounds as checkpoints.  Pass 2 walks the
-// private list back to front or, for a ray longer than the list,
-// re-collects the rounds last to first from the nearest checkpoint.
-// Checkpoints are kept for every stride-th round: once all kBwdCheckpoints
-// are taken every other one is dropped and the stride doubles, so pass 2
-// re-collects at most stride - 1 extra rounds per round (instead of
-// re-marching from the last checkpoint for every round past them).
+// Re-march one ray.  Pass 1 marches the k-buffer rounds again (the forward's
+// arithmetic, so T is reproduced bit for bit), recording the state at the
+// start of rounds as checkpoints.  Pass 2 re-collects the rounds last to first
+// from the nearest checkpoint.  Checkpoints are kept for every stride-th round:
+// once all kBwdCheckpoints are taken every other one is dropped and the stride
+// doubles, so pass 2 re-collects at most stride - 1 extra rounds per round.
 template <int K, int FM, int FU, bool SH, bool NRM, class Acc>
 __device__ __forceinline__ void bwd_remarch(const SceneView& sc, const RawSurfels& raw, const TraceParams& P,
                                             const Ray& ray, const LaneUp<FU>& up, const Acc& acc, Stack& st,
-                                            float4* ck, int64_t ck_stride, int* pid, float* pT)
+                                            float4* ck, int64_t ck_stride)
 {
     float S = 0.0f;
     Counters ct;
@@ -349,12 +267,7 @@ __device__ __forceinline__ void bwd_remarch(const SceneView& sc, const RawSurfel
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             if (j < kb.cnt && !done) {
-                const int pos = kb.pos(j);
-                if (nh < kRemarchList) {
-                    pid[nh] = __float_as_int(sc.rec[pos].c.w);
-                    pT[nh] = T;
-                }
-                T = T * (1.0f - entry_alpha(sc, ray, pos));
+                T = T * (1.0f - entry_alpha(sc, ray, kb.pos(j)));
                 ++nh;
                 if (T < P.T_min) done = true;
             }
@@ -366,15 +279,6 @@ __device__ __forceinline__ void bwd_remarch(const SceneView& sc, const RawSurfel
         ++rounds;
     }
     const int total = nh;
-    if (total <= kRemarchList) {
-        for (int h = total - 1; h >= 0; --h) {
-            const int id = pid[h];
-            HitGrad<FM> hg;
-            grad_hit<FM, FU, SH, NRM>(raw, P, id, ray, pT[h], S, up.gO, up.gF, up.gD, hg);
-            acc.template direct<FM>(id, hg);
-        }
-        return;
-    }
     for (int rr = rounds - 1; rr >= 0; --rr) {
         const int base = rr / stride;
         float4 c4 = ck[base * ck_stride];
@@ -411,172 +315,33 @@ __device__ __forceinline__ void bwd_remarch(const SceneView& sc, const RawSurfel
     }
 }
 
-// RM = false: rays whose stored hit list is complete, walked back to front
-// (the re-march code is compiled out, which keeps the register count low);
-// RM = true: the other rays (no stored lists, or a list cut at H_cap),
-// re-marched.  A backward runs the first over every ray when lists are
-// stored, then the second.
-// The walk over stored lists is latency-bound: it is held to the registers
-// of 3 waves per SIMD (no spills for F <= 16), and the LDS table is sized so
-// that LDS allows as many (measured at 1M surfels, F = 8: 256 slots and 2
-// waves 33.3 ms; 64 slots and 3 waves 24.5 ms; no table 28.0 ms).
-template <int K, int FM, int FU, bool SH, bool NRM, bool RM>
-__global__ __launch_bounds__(kBwdBlock) __attribute__((amdgpu_waves_per_eu(!RM && FM <= 16 ? 3 : 1)))
-void k_backward(SceneView sc, RawSurfels raw, TraceParams P, int64_t R,
-                                                        const float* __restrict__ ro, const float* __restrict__ rd,
-                                                        OutPtrs saved, bool use_saved, GradIn gin, float* gbuf,
-                                                        int gs, int* ovf, int ovf_slots, float4* ck, int* plist,
-                                                        unsigned long long* next_chunk,
-                                                        const uint32_t* __restrict__ order, int* rm_list,
-                                                        unsigned long long* rm_count)
+// The rays of `list` re-marched by one lane each.
+template <int K, int FM, int FU, bool SH, bool NRM>
+__global__ __launch_bounds__(kBwdBlock) void k_remarch_lanes(SceneView sc, RawSurfels raw, TraceParams P,
+                                                             const float* __restrict__ ro, const float* __restrict__ rd,
+                                                             GradIn gin, float* gbuf, int gs, int* ovf, float4* ck,
+                                                             const int* __restrict__ list,
+                                                             const unsigned long long* list_count,
+                                                             unsigned long long* next)
 {
-    using Shape = TableShape<FM>;
-    __shared__ int hkeys[Shape::slots];
-    __shared__ float hvals[kLdsComp * Shape::val_row];
-    __shared__ int hfilled;
-    __shared__ long long claimed;
-    __shared__ int stage_id[kBwdBlock];
-    // staged gradients, one row per component; rows padded by one word so
-    // that the scatter's reads (consecutive lanes: consecutive components
-    // of one hit) fall in different banks
-    constexpr int kRow = kBwdBlock + 1;
-    __shared__ float stage[(10 + FM) * kRow];
     const int tid = threadIdx.x;
     const int64_t gtid = static_cast<int64_t>(blockIdx.x) * kBwdBlock + tid;
     const int64_t nthr = static_cast<int64_t>(gridDim.x) * kBwdBlock;
-    // the re-march stack lives entirely in the global area (0 LDS slots)
-    Stack st{nullptr, as_glb(ovf_slots > 0 ? ovf + gtid : nullptr), static_cast<int>(nthr), tid, 0, 0};
-    // re-march lanes (gtid < kRemarchThreads): checkpoints slot-major, the
-    // private list contiguous per lane (ids, then T)
-    float4* myck = RM ? ck + gtid : nullptr;
-    int* my_ids = RM ? plist + gtid * (2 * kRemarchList) : nullptr;
-    float* my_T = RM ? reinterpret_cast<float*>(my_ids + kRemarchList) : nullptr;
-    const GradAcc<Shape::slots> acc{hkeys, hvals, &hfilled, gbuf, gs, P.F};
-    const int nc = 10 + P.F;
-    // The scatter below hands lane l the elements l, l + 64, ... of a
-    // block's hits x components: its first (hit, component) pair and the step
-    // between pairs, so that no element needs an integer division.
-    const int sc_h0 = tid / nc, sc_c0 = tid - sc_h0 * nc;
-    const int sc_dh = kBwdBlock / nc, sc_dc = kBwdBlock - sc_dh * nc;
-    // With stored lists the walk instance collects the rays it leaves (lists
-    // cut at H_cap) in rm_list; the re-march instance then claims chunks of
-    // that list only, instead of scanning every ray.
-    const bool listed = RM && use_saved && rm_list;
-    const int64_t Rw = listed ? static_cast<int64_t>(*rm_count) : R;
-    const int64_t chunks = (Rw + kBwdBlock - 1) / kBwdBlock;
-    // chunks of kBwdBlock rays are claimed from a global counter as blocks
-    // free up, so the launch drains evenly
+    // the stack lives entirely in the global area (0 LDS slots)
+    Stack st{nullptr, as_glb(ovf + gtid), static_cast<int>(nthr), tid, 0, 0};
+    const GradAcc acc{gbuf, gs, P.F};
+    const int64_t count = static_cast<int64_t>(*list_count);
     while (true) {
-        if (tid == 0) claimed = static_cast<long long>(atomicAdd(next_chunk, 1ull));
-        // the re-march accumulates with direct atomics only: its instance
-        // neither clears nor flushes the table (most of its chunks hold no
-        // ray to re-march, and the table pass would be its whole cost)
-        if constexpr (!RM) acc.clear(tid);
-        __syncthreads();
-        const int64_t c = claimed;
-        if (c >= chunks) break;
-        // a chunk takes the next 64 rays of `order` or of the launch
-        const int64_t slot = c * kBwdBlock + tid;
-        const int64_t r = listed ? (slot < Rw ? static_cast<int64_t>(rm_list[slot]) : R)
-                                 : (slot < R && order ? static_cast<int64_t>(order[slot]) : slot);
-        Ray ray{};
-        LaneUp<FU> up{};
-        int nh = 0;
-        bool stored = false;
-        bool cut = false;  // walk instance: a ray left to the re-march
-        if (r < R) {
-            // each instance loads only the rays it owns
-            const int nh_saved = saved.n_hits ? saved.n_hits[r] : -1;
-            const bool complete = use_saved && nh_saved > 0 && nh_saved <= saved.H_cap;
-            cut = !RM && !complete && nh_saved != 0;
-            if (RM ? (!complete && nh_saved != 0) : complete) {
-                ray = load_ray(ro, rd, r);
-                up = load_upstream<FU>(gin, r, SH ? 3 : (NRM ? P.F + 3 : P.F));
-                if (up.any && sc.n > 0 && ray_valid(ray)) {
-                    if constexpr (!RM) {
-                        stored = true;
-                        nh = nh_saved;
-                    } else {
-                        bwd_remarch<K, FM, FU, SH, NRM>(sc, raw, P, ray, up, acc, st, myck, nthr, my_ids, my_T);
-                    }
-                }
-            }
+        unsigned long long c = 0;
+        if (tid == 0) c = atomicAdd(next, 1ull);
+        const int64_t base = static_cast<int64_t>(bcast(static_cast<uint64_t>(c), 0)) * kBwdBlock;
+        if (base >= count) return;
+        if (base + tid < count) {
+            const int64_t r = list[base + tid];
+            const Ray ray = load_ray(ro, rd, r);
+            const LaneUp<FU> up = load_upstream<FU>(gin, r, SH ? 3 : (NRM ? P.F + 3 : P.F));
+            if (up.any && ray_valid(ray)) bwd_remarch<K, FM, FU, SH, NRM>(sc, raw, P, ray, up, acc, st, ck + gtid, nthr);
         }
-        if constexpr (!RM) {
-            if (rm_list) {  // one atomic per wave for the rays it leaves
-                const uint64_t m = __ballot(cut);
-                if (m) {
-                    const int rank = __popcll(m & __lanemask_lt());
-                    const int leader = __ffsll(static_cast<unsigned long long>(m)) - 1;
-                    unsigned long long base = 0;
-                    if (cut && rank == 0) base = atomicAdd(rm_count, static_cast<unsigned long long>(__popcll(m)));
-                    base = __shfl(base, leader);
-                    if (cut) rm_list[base + rank] = static_cast<int>(r);
-                }
-            }
-        }
-        // Saved lists: all lanes step together, back to front, so that the
-        // wave can hand every hit's gradient to the scatter below.
-        int hmax = nh;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) hmax = max(hmax, __shfl_xor(hmax, off));
-        const int* ids = saved.hit_ids + (stored ? r * saved.H_cap : 0);
-        const float* Ts = saved.hit_T + (stored ? r * saved.H_cap : 0);
-        float S = 0.0f;
-        for (int step = 0; step < hmax; ++step) {
-            const int h = nh - 1 - step;
-            const bool valid = stored && h >= 0;
-            HitGrad<FM> hg;
-            int id = -1;
-            if (valid) {
-                id = ids[h];
-                grad_hit<FM, FU, SH, NRM>(raw, P, id, ray, Ts[h], S, up.gO, up.gF, up.gD, hg);
-                if (h < Shape::near_hits) acc.template table<FM>(id, hg);
-            } else {
-#pragma unroll
-                for (int k = 0; k < 10 + FM; ++k) hg.g[k] = 0.0f;
-            }
-            // What the table did not take goes to global memory; a step whose
-            // hits the table took whole (a block is one wave: the branch is
-            // uniform) skips the staging.
-            bool left = false;
-#pragma unroll
-            for (int k = 0; k < 10 + FM; ++k) left = left || hg.g[k] != 0.0f;
-            const uint64_t lm = __ballot(left);
-            if (lm) {
-                // only the hits with something left are staged, packed into
-                // the first rows
-                const int n_left = __popcll(lm);
-                if (left) {
-                    const int row = __popcll(lm & __lanemask_lt());
-                    stage_id[row] = id;
-#pragma unroll
-                    for (int k = 0; k < 10 + FM; ++k) stage[k * kRow + row] = hg.g[k];
-                }
-                __syncthreads();
-                // Transposed scatter: lane l takes component (q*64 + l) % nc
-                // of staged hit (q*64 + l) / nc, so consecutive lanes add
-                // consecutive components of one surfel -- a few cache lines per
-                // instruction.
-                for (int hit = sc_h0, comp = sc_c0; hit < n_left;) {
-                    const int sid = stage_id[hit];
-                    const float v = stage[comp * kRow + hit];
-                    if (sid >= 0 && v != 0.0f) atomicAdd(gbuf + static_cast<int64_t>(sid) * gs + comp, v);
-                    hit += sc_dh;
-                    comp += sc_dc;
-                    if (comp >= nc) {
-                        comp -= nc;
-                        ++hit;
-                    }
-                }
-                __syncthreads();
-            }
-        }
-        if constexpr (!RM) {
-            __syncthreads();
-            acc.flush(tid);
-        }
-        __syncthreads();
     }
 }
 
@@ -603,21 +368,31 @@ __global__ void k_ray_keys(int64_t R, const float* __restrict__ ro, const float*
     vals[r] = static_cast<uint32_t>(r);
 }
 
-// One packed row per surfel (see RawSurfels): consecutive threads take
-// consecutive surfels and write their rows whole.
-__global__ void k_pack(int64_t n, int F, int ps, const float* __restrict__ mu, const float* __restrict__ quat,
-                       const float* __restrict__ scale, const float* __restrict__ opac,
+// One packed row per surfel (see RawSurfels).  A thread writes 16 bytes of a
+// row, so that a wave writes whole lines.
+__global__ void k_pack(int64_t n, int F, int ps, bool feats, const float* __restrict__ mu,
+                       const float* __restrict__ quat, const float* __restrict__ scale, const float* __restrict__ opac,
                        const float* __restrict__ feat, float* __restrict__ pk)
 {
-    const int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
+    const int parts = ps / 4;
+    const int64_t t = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x;
+    const int64_t i = t / parts;
+    const int c = static_cast<int>(t - i * parts);
     if (i >= n) return;
-    float4* row = reinterpret_cast<float4*>(pk + i * ps);
-    row[0] = make_float4(mu[3 * i], mu[3 * i + 1], mu[3 * i + 2], opac[i]);
-    row[1] = *reinterpret_cast<const float4*>(quat + 4 * i);
-    const float2 s = *reinterpret_cast<const float2*>(scale + 2 * i);
-    row[2] = make_float4(s.x, s.y, 0.0f, 0.0f);
-    float* f = pk + i * ps + 12;
-    for (int c = 0; c < F; ++c) f[c] = feat[i * F + c];
+    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (c == 0) {
+        v = make_float4(mu[3 * i], mu[3 * i + 1], mu[3 * i + 2], opac[i]);
+    } else if (c == 1) {
+        v = make_float4(quat[4 * i], quat[4 * i + 1], quat[4 * i + 2], quat[4 * i + 3]);
+    } else if (c == 2) {
+        v.x = scale[2 * i], v.y = scale[2 * i + 1];
+    } else if (feats) {
+        const int f0 = 4 * (c - 3);
+        const float* f = feat + i * F;
+        v.x = f0 < F ? f[f0] : 0.0f, v.y = f0 + 1 < F ? f[f0 + 1] : 0.0f;
+        v.z = f0 + 2 < F ? f[f0 + 2] : 0.0f, v.w = f0 + 3 < F ? f[f0 + 3] : 0.0f;
+    }
+    reinterpret_cast<float4*>(pk)[t] = v;
 }
 
 // gbuf (interleaved per surfel) added into the caller's gradient arrays.
@@ -644,96 +419,91 @@ __global__ void k_grad_out(int64_t n, int F, int gs, const float* __restrict__ g
     }
 }
 
-template <int K, int FM, int FU, bool SH, bool NRM = false>
-hipError_t launch_kf(const SceneView& sc, const RawSurfels& raw, const TraceParams& P, int64_t R, const float* ro,
-                     const float* rd, const OutPtrs& saved, bool use_saved, const GradIn& gin, const GradOut& go,
-                     int* ovf, int ovf_slots, float* ck, hipStream_t st)
+// Rays ordered by where they land (see k_ray_keys); *order stays null when the
+// forward's O and D are not there or the launch is too large to sort.
+hipError_t landing_order(const SceneView& sc, int64_t R, const float* ro, const float* rd, const OutPtrs& saved,
+                         char* p, const uint32_t** order, hipStream_t st)
 {
-    const int64_t nthr = trace_threads(R);
-    const int64_t rm_thr = remarch_threads(R);
+    uint64_t* k0 = reinterpret_cast<uint64_t*>(p);
+    uint64_t* k1 = k0 + R;
+    uint32_t* v0 = reinterpret_cast<uint32_t*>(k1 + R);
+    uint32_t* v1 = v0 + R;
+    uint32_t* counts = v1 + R;
+    k_ray_keys<<<static_cast<unsigned>((R + 255) / 256), 256, 0, st>>>(R, ro, rd, saved.O, saved.D, sc.wnodes, k0, v0);
+    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = sort_pairs(static_cast<int>(R), k0, v0, k1, v1, counts, 4, st);
+    if (e == hipSuccess) *order = v0;
+    return e;
+}
+
+template <int FM, int CM>
+hipError_t launch_f(const SceneView& sc, const RawSurfels& raw, const TraceParams& P, int64_t R, const float* ro,
+                    const float* rd, const OutPtrs& saved, const GradIn& gin, const GradOut& go, int wide_depth,
+                    char* scratch, hipStream_t st)
+{
+    using Sh = WalkShape<FM>;
+    const BackwardPlan pl = plan_backward(R, sc.n, P.F, wide_depth);
     const int gs = grad_stride(P.F);
-    int* plist = reinterpret_cast<int*>(ck + static_cast<size_t>(rm_thr) * kBwdCheckpoints * 4);
-    float* gbuf = ck + remarch_words(R);
-    unsigned long long* next_chunk =
-        reinterpret_cast<unsigned long long*>(gbuf + static_cast<size_t>(sc.n) * gs);
-    unsigned long long* rm_count = next_chunk + 2;  // zeroed with the claim counters
-    char* after_claims = reinterpret_cast<char*>(next_chunk) + kBwdClaimWords * sizeof(float);
-    int* rm_list = reinterpret_cast<int*>((reinterpret_cast<uintptr_t>(after_claims) + 255) & ~static_cast<uintptr_t>(255));
-    // zero the accumulator and the claim counter behind it
-    hipError_t e = fill_u32(gbuf, static_cast<int64_t>(sc.n) * gs + kBwdClaimWords, 0u, st);
+    float* gbuf = reinterpret_cast<float*>(scratch);
+    unsigned long long* claims = reinterpret_cast<unsigned long long*>(scratch + pl.claims);
+    unsigned long long *next_chunk = claims, *rm_count = claims + 1, *next_rm = claims + 2, *rest_count = claims + 3,
+                       *next_rest = claims + 4;
+    int* rm_list = reinterpret_cast<int*>(scratch + pl.rm_list);
+    int* rest = reinterpret_cast<int*>(scratch + pl.rest);
+    // zero the accumulator and the claim counters behind it
+    hipError_t e = fill_u32(gbuf, static_cast<int64_t>(pl.rm_list / 4), 0u, st);
     if (e != hipSuccess) return e;
-    // Gradients wider than the LDS table (SH coefficients, F > 8) send most
-    // components straight to global atomics; their chunks then take rays in
-    // the order of where they land (stored lists with O and D), so that the
-    // surfels a block updates stay in L2 (at 1M surfels, SH degree 3: 95.6
-    // -> 81.6 ms; for F <= 8 the sort costs more than it saves).
     const uint32_t* order = nullptr;
-    // (the condition on P.F is the one the scratch is sized by)
-    if (P.F > kLdsFeat && use_saved && saved.O && saved.D && ray_sort_words(R) > 0 && sc.n > 0) {
-        char* p = reinterpret_cast<char*>(rm_list + R);
-        p = reinterpret_cast<char*>((reinterpret_cast<uintptr_t>(p) + 255) & ~static_cast<uintptr_t>(255));
-        uint64_t* k0 = reinterpret_cast<uint64_t*>(p);
-        uint64_t* k1 = k0 + R;
-        uint32_t* v0 = reinterpret_cast<uint32_t*>(k1 + R);
-        uint32_t* v1 = v0 + R;
-        uint32_t* counts = v1 + R;
-        k_ray_keys<<<static_cast<unsigned>((R + 255) / 256), 256, 0, st>>>(R, ro, rd, saved.O, saved.D, sc.wnodes, k0,
-                                                                             v0);
-        e = hipGetLastError();
-        if (e == hipSuccess) e = sort_pairs(static_cast<int>(R), k0, v0, k1, v1, counts, 4, st);
+    if (R >= kSortWalkRays && saved.O && saved.D && ray_sort_words(R) > 0) {
+        e = landing_order(sc, R, ro, rd, saved, scratch + pl.sort, &order, st);
         if (e != hipSuccess) return e;
-        order = v0;
     }
-    if (use_saved) {
-        const unsigned grid =
-            persistent_grid(nthr / kBwdBlock, resident_blocks(k_backward<K, FM, FU, SH, NRM, false>, kBwdBlock));
-        k_backward<K, FM, FU, SH, NRM, false><<<grid, kBwdBlock, 0, st>>>(sc, raw, P, R, ro, rd, saved, use_saved, gin,
-                                                                     gbuf, gs, ovf, ovf_slots,
-                                                                     reinterpret_cast<float4*>(ck), plist, next_chunk,
-                                                                     order, rm_list, rm_count);
+    {
+        const int64_t resident = resident_blocks(k_walk<FM, CM>, Sh::waves * 64);
+        const int64_t waves = (resident > 0 ? resident : 256) * Sh::waves;
+        // groups of full size once every wave gets several, chunks of a few
+        // groups per wave; smaller launches spread over all waves
+        int64_t group = R / (2 * waves);
+        group = group < 1 ? 1 : (group > Sh::group ? Sh::group : group);
+        const int groups = group == Sh::group ? 2 * Sh::waves : Sh::waves;
+        const int64_t chunks = (R + group * groups - 1) / (group * groups);
+        k_walk<FM, CM><<<persistent_grid(chunks, resident), Sh::waves * 64, 0, st>>>(
+            raw, P, R, ro, rd, saved, gin, gbuf, gs, next_chunk, order, static_cast<int>(group), groups, rm_list, rm_count);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    // rays without a complete stored list (all of them without stored lists)
-    // (at most rm_thr lanes: the checkpoints and private lists are sized for them)
-    const unsigned grid =
-        persistent_grid(rm_thr / kBwdBlock, resident_blocks(k_backward<K, FM, FU, SH, NRM, true>, kBwdBlock));
-    k_backward<K, FM, FU, SH, NRM, true><<<grid, kBwdBlock, 0, st>>>(sc, raw, P, R, ro, rd, saved, use_saved, gin, gbuf,
-                                                                gs, ovf, ovf_slots, reinterpret_cast<float4*>(ck),
-                                                                plist, next_chunk + 1, nullptr, rm_list, rm_count);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (sc.n > saved.H_cap) {  // a list can have been cut
+        const bool wave = wave_stack_fits(wide_depth);
+        if (wave) {
+            OutPtrs lists{};
+            lists.hit_ids = reinterpret_cast<int32_t*>(scratch + pl.lists);
+            lists.hit_T = reinterpret_cast<float*>(lists.hit_ids + pl.waves * kRemarchList);
+            lists.O = lists.hit_T + pl.waves * kRemarchList;
+            lists.D = lists.O + pl.waves;
+            lists.feat = lists.D + pl.waves;
+            lists.H_cap = kRemarchList;
+            const unsigned grid = persistent_grid(pl.waves, resident_blocks(k_remarch<FM, CM>, kWaveBlock));
+            k_remarch<FM, CM><<<grid, kWaveBlock, 0, st>>>(sc, raw, P, ro, rd, gin, gbuf, gs, lists,
+                                                           wave_stack_reserve(wide_depth), rm_list, rm_count, next_rm,
+                                                           rest, rest_count);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        if (!wave || sc.n > kRemarchList) {
+            constexpr int FU = CM == kColSH ? 4 : FM;
+            k_remarch_lanes<kMarchK, FM, FU, CM == kColSH, CM == kColNormal>
+                <<<static_cast<unsigned>(pl.lane_blocks), kBwdBlock, 0, st>>>(
+                    sc, raw, P, ro, rd, gin, gbuf, gs, reinterpret_cast<int*>(scratch + pl.stacks),
+                    reinterpret_cast<float4*>(scratch + pl.checkpoints), wave ? rest : rm_list,
+                    wave ? rest_count : rm_count, next_rest);
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+    }
     const int64_t work = static_cast<int64_t>(sc.n) * (10 + P.F);
     const int blocks = static_cast<int>(work < 2048 * 256 ? (work + 255) / 256 : 2048);
     k_grad_out<<<blocks > 0 ? blocks : 1, 256, 0, st>>>(sc.n, P.F, gs, gbuf, go);
     return hipGetLastError();
-}
-
-template <int K>
-hipError_t launch_k(const SceneView& sc, const RawSurfels& raw, const TraceParams& P, int64_t R, const float* ro,
-                    const float* rd, const OutPtrs& saved, bool use_saved, const GradIn& gin, const GradOut& go,
-                    int* ovf, int ovf_slots, float* ck, hipStream_t st)
-{
-    if constexpr (K == 16 || K == 32 || K == 64) {  // SH: 48 coefficient gradients, 3 upstream channels
-        if (P.sh_deg >= 0)
-            return launch_kf<K, 48, 4, true>(sc, raw, P, R, ro, rd, saved, use_saved, gin, go, ovf, ovf_slots, ck, st);
-        // relighting blend: F <= 5 features and 3 normal channels upstream
-        if (P.normals && P.F <= 5)
-            return launch_kf<K, 8, 8, false, true>(sc, raw, P, R, ro, rd, saved, use_saved, gin, go, ovf, ovf_slots,
-                                                   ck, st);
-    }
-    if (P.sh_deg >= 0 || P.normals) return hipErrorInvalidValue;
-    if (P.F <= 4)
-        return launch_kf<K, 4, 4, false>(sc, raw, P, R, ro, rd, saved, use_saved, gin, go, ovf, ovf_slots, ck, st);
-    if (P.F <= 8)
-        return launch_kf<K, 8, 8, false>(sc, raw, P, R, ro, rd, saved, use_saved, gin, go, ovf, ovf_slots, ck, st);
-    if constexpr (K == 16 || K == 32) {
-        if (P.F <= 16)
-            return launch_kf<K, 16, 16, false>(sc, raw, P, R, ro, rd, saved, use_saved, gin, go, ovf, ovf_slots, ck, st);
-        if (P.F <= 64)
-            return launch_kf<K, 64, 64, false>(sc, raw, P, R, ro, rd, saved, use_saved, gin, go, ovf, ovf_slots, ck, st);
-    }
-    return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -741,27 +511,53 @@ hipError_t launch_k(const SceneView& sc, const RawSurfels& raw, const TraceParam
 hipError_t pack_surfels(const RawSurfels& raw, int64_t n, int F, float* pk, hipStream_t st)
 {
     if (n <= 0) return hipSuccess;
-    k_pack<<<static_cast<unsigned>((n + 255) / 256), 256, 0, st>>>(n, F, pack_stride(F), raw.mu, raw.quat, raw.scale,
-                                                                   raw.opac, raw.feat, pk);
+    const int64_t t = n * (raw.ps / 4);
+    k_pack<<<static_cast<unsigned>((t + 255) / 256), 256, 0, st>>>(n, F, raw.ps, raw.feat_packed, raw.mu, raw.quat,
+                                                                   raw.scale, raw.opac, raw.feat, pk);
     return hipGetLastError();
 }
 
+BackwardPlan plan_backward(int64_t R, int64_t N, int F, int wide_depth)
+{
+    BackwardPlan pl{};
+    size_t at = 0;
+    auto take = [&](size_t bytes) {
+        const size_t here = at;
+        at += (bytes + 255) & ~static_cast<size_t>(255);
+        return here;
+    };
+    take(static_cast<size_t>(N) * grad_stride(F) * sizeof(float));
+    pl.claims = take(256);
+    pl.rm_list = take(static_cast<size_t>(R) * sizeof(int));
+    pl.rest = take(static_cast<size_t>(R) * sizeof(int));
+    pl.sort = take(R >= kSortWalkRays ? ray_sort_words(R) * sizeof(float) : 0);
+    // (few rays are cut: a wave per 64 rays of the launch is plenty)
+    pl.waves = std::min<int64_t>((R + 63) / 64, kRemarchWaves);
+    const int64_t blocks = (R + kBwdBlock - 1) / kBwdBlock;
+    pl.lane_blocks = blocks < kRemarchLanes / kBwdBlock ? blocks : kRemarchLanes / kBwdBlock;
+    const size_t lanes = static_cast<size_t>(pl.lane_blocks) * kBwdBlock;
+    pl.lists = take(static_cast<size_t>(pl.waves) * (2 * kRemarchList + 2 + kMaxF + 3) * sizeof(float));
+    pl.stacks = take(lanes * (3 * wide_depth + 1) * sizeof(int));
+    pl.checkpoints = take(lanes * kBwdCheckpoints * sizeof(float4));
+    pl.bytes = at;
+    return pl;
+}
+
 hipError_t launch_backward(const SceneView& sc, const RawSurfels& raw, const TraceParams& P, int k, int64_t R,
-                           const float* ro, const float* rd, const OutPtrs& saved, bool use_saved,
-                           const GradIn& gin, const GradOut& go, int* ovf, int ovf_slots, float* ck,
-                           hipStream_t st)
+                           const float* ro, const float* rd, const OutPtrs& saved, const GradIn& gin,
+                           const GradOut& go, int wide_depth, char* scratch, hipStream_t st)
 {
     if (R <= 0) return hipSuccess;
-    switch (k) {
-        case 1: return launch_k<1>(sc, raw, P, R, ro, rd, saved, use_saved, gin, go, ovf, ovf_slots, ck, st);
-        case 2: return launch_k<2>(sc, raw, P, R, ro, rd, saved, use_saved, gin, go, ovf, ovf_slots, ck, st);
-        case 4: return launch_k<4>(sc, raw, P, R, ro, rd, saved, use_saved, gin, go, ovf, ovf_slots, ck, st);
-        case 8: return launch_k<8>(sc, raw, P, R, ro, rd, saved, use_saved, gin, go, ovf, ovf_slots, ck, st);
-        case 16: return launch_k<16>(sc, raw, P, R, ro, rd, saved, use_saved, gin, go, ovf, ovf_slots, ck, st);
-        case 32: return launch_k<32>(sc, raw, P, R, ro, rd, saved, use_saved, gin, go, ovf, ovf_slots, ck, st);
-        case 64: return launch_k<64>(sc, raw, P, R, ro, rd, saved, use_saved, gin, go, ovf, ovf_slots, ck, st);
-        default: return hipErrorInvalidValue;
+    const bool special = P.sh_deg >= 0 || P.normals;
+    if (!features_offered(k, P.F, special)) return hipErrorInvalidValue;
+    if (P.sh_deg >= 0) return launch_f<48, kColSH>(sc, raw, P, R, ro, rd, saved, gin, go, wide_depth, scratch, st);
+    if (P.normals) {  // F <= 5 features and 3 normal channels upstream
+        if (P.F > 5) return hipErrorInvalidValue;
+        return launch_f<8, kColNormal>(sc, raw, P, R, ro, rd, saved, gin, go, wide_depth, scratch, st);
     }
+    if (P.F <= 8) return launch_f<8, kColPlain>(sc, raw, P, R, ro, rd, saved, gin, go, wide_depth, scratch, st);
+    if (P.F <= 16) return launch_f<16, kColPlain>(sc, raw, P, R, ro, rd, saved, gin, go, wide_depth, scratch, st);
+    return launch_f<64, kColPlain>(sc, raw, P, R, ro, rd, saved, gin, go, wide_depth, scratch, st);
 }
 
 }  // namespace irgs

@@ -276,6 +276,8 @@ hipError_t launch_wave(const Source& src, int64_t rays, const TraceParams& P, un
     return hipGetLastError();
 }
 
+}  // namespace
+
 // Feature counts a k-buffer size is offered for (the per-lane form's
 // instances; the wave form takes any, and refuses the same calls).
 bool features_offered(int k, int F, bool special)
@@ -283,8 +285,6 @@ bool features_offered(int k, int F, bool special)
     if (special) return k == 16 || k == 32 || k == 64;
     return F <= 8 || k == 16 || k == 32;
 }
-
-}  // namespace
 
 bool use_wave_trace(bool bvh, bool counters, int wide_depth)
 {

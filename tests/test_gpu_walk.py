@@ -1,0 +1,82 @@
+"""The backward's walk over hit lists at the sizes where it can go wrong: rays
+around its groups and chunks, feature counts around its instances, lists cut at
+their capacity (traced again by a wave) and hits past the wave's own list
+(re-marched by a lane).  Reference: FP64 autograd over the GPU's own hit lists."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import dev, make_scene
+from oracle import grad as ograd
+from paper_2412_15867_amd import TraceConfig, synth, trace, trace_backward
+
+pytestmark = pytest.mark.gpu
+KEYS = (("mu", "mu"), ("quat", "quat"), ("scale", "scale"), ("opacity", "opac"), ("feat", "feat"))
+
+
+def stack(n, F, alpha, R, seed=5):
+    """n tilted, faint surfels along z and R rays near the axis."""
+    g = np.random.Generator(np.random.PCG64(seed))
+    mu = np.concatenate([g.uniform(-0.1, 0.1, (n, 2)), (g.permutation(n) * 0.01)[:, None]], 1)
+    quat = np.concatenate([np.ones((n, 1)), g.uniform(-0.05, 0.05, (n, 3))], 1)
+    sc = synth.Surfels(mu.astype(np.float32), quat.astype(np.float32),
+                       g.uniform(0.4, 0.7, (n, 2)).astype(np.float32), np.full(n, alpha, np.float32),
+                       g.uniform(0, 1, (n, F)).astype(np.float32))
+    ro = np.concatenate([g.uniform(-0.3, 0.3, (R, 2)), np.full((R, 1), -1.0)], 1).astype(np.float32)
+    d = np.concatenate([g.uniform(-0.02, 0.02, (R, 2)), np.ones((R, 1))], 1)
+    rd = (d / np.linalg.norm(d, axis=1, keepdims=True)).astype(np.float32)
+    return sc, ro, rd
+
+
+def check(sc, ro, rd, cfg, cap, mask=None, full=256):
+    s = make_scene(sc)
+    R = ro.shape[0]
+    gO, gF, gD, _ = synth.upstream(R, sc.F, seed=3)
+    if mask is not None:
+        gO[~mask], gF[~mask], gD[~mask] = 0, 0, 0
+    whole = trace(s, dev(ro), dev(rd), cfg, hit_cap=full)
+    res = trace(s, dev(ro), dev(rd), cfg, hit_cap=cap)
+    got = trace_backward(s, dev(ro), dev(rd), res, dev(gO), dev(gF), dev(gD), cfg=cfg)
+    n = whole.n_hits.cpu().numpy()
+    assert n.max() <= full
+    ids = np.where(np.arange(full)[None] < n[:, None], whole.hit_ids.cpu().numpy(), -1)[:, :max(int(n.max()), 1)]
+    want = ograd.grad_given_hits(sc.astuple(), ro, rd, ids, gO, gF, gD)
+    for a, b in KEYS:
+        g, w = got[a].cpu().numpy().reshape(want[b].shape), want[b]
+        assert np.all(np.abs(g - w) <= 1e-3 * (np.abs(w) + np.abs(w).mean() + 1e-12)), a
+    return n
+
+
+@pytest.mark.parametrize("R", [1, 15, 17, 191, 193, 3001])
+@pytest.mark.parametrize("F", [3, 9])
+def test_ray_counts(R, F):
+    sc, ro, rd = stack(40, F, 0.2, R)
+    check(sc, ro, rd, TraceConfig(k=16), 64)
+
+
+@pytest.mark.parametrize("F", [1, 8, 16, 17, 20, 21, 54, 55, 64])
+def test_feature_counts(F):
+    sc, ro, rd = stack(70, F, 0.1, 50)
+    check(sc, ro, rd, TraceConfig(k=16), 256)
+
+
+def test_rays_in_landing_order():
+    """Enough rays to be taken in the order of where they land, many of them
+    without hits or without an upstream gradient."""
+    sc, ro, rd = stack(30, 4, 0.3, 16_500)
+    rd[::5] *= -1
+    check(sc, ro, rd, TraceConfig(k=16), 64, mask=np.arange(16_500) % 3 != 0)
+
+
+@pytest.mark.parametrize("cap", [1, 40, 63, 64, 65, 200])
+@pytest.mark.parametrize("F", [3, 12])
+def test_cut_lists_are_traced_again(cap, F):
+    sc, ro, rd = stack(230, F, 0.03, 130)
+    n = check(sc, ro, rd, TraceConfig(k=16, T_min=0.0), cap)
+    assert n.max() > cap
+
+
+def test_hits_past_the_wave_list():
+    sc, ro, rd = stack(2600, 3, 0.006, 5)
+    n = check(sc, ro, rd, TraceConfig(k=16, T_min=0.0), 256, full=2600)
+    assert n.max() > 2048
