@@ -33,7 +33,6 @@ struct irgs_scene_s {
     uint32_t* order = nullptr;
     float* leafbox = nullptr;
     uint32_t* counters = nullptr;
-    int* depth = nullptr;
     int2* brange = nullptr;
     WideNode* wnodes = nullptr;
     int4* wsrc = nullptr;
@@ -88,7 +87,6 @@ void free_scene_buffers(irgs_scene s)
     hipFree(s->order);
     hipFree(s->leafbox);
     hipFree(s->counters);
-    hipFree(s->depth);
     hipFree(s->brange);
     hipFree(s->wnodes);
     hipFree(s->wsrc);
@@ -103,7 +101,6 @@ void free_scene_buffers(irgs_scene s)
     s->order = nullptr;
     s->leafbox = nullptr;
     s->counters = nullptr;
-    s->depth = nullptr;
     s->built = false;
 }
 
@@ -158,7 +155,6 @@ BuildArgs build_args(irgs_scene s)
     a.level_nodes = reinterpret_cast<int*>(s->counters);
     a.levels = &s->levels;
     a.wide_levels = &s->wide_levels;
-    a.depth = s->depth;
     a.brange = s->brange;
     a.wnodes = s->wnodes;
     a.wsrc = s->wsrc;
@@ -505,7 +501,7 @@ irgs_status irgs_scene_build(irgs_scene s, const irgs_params* p, void* stream)
         if ((e = dalloc(&s->rec, n)) != hipSuccess || (e = dalloc(&s->nodes, n_internal(n))) != hipSuccess ||
             (e = dalloc(&s->leaf_parent, n)) != hipSuccess || (e = dalloc(&s->order, n)) != hipSuccess ||
             (e = dalloc(&s->leafbox, 6 * n)) != hipSuccess || (e = dalloc(&s->counters, n_internal(n))) != hipSuccess ||
-            (e = dalloc(&s->depth, 1)) != hipSuccess || (e = dalloc(&s->brange, n_internal(n))) != hipSuccess ||
+            (e = dalloc(&s->brange, n_internal(n))) != hipSuccess ||
             (e = dalloc(&s->wnodes, n_internal(n))) != hipSuccess ||
             (e = dalloc(&s->wsrc, n_internal(n))) != hipSuccess ||
             (e = dalloc(&s->wscratch, 3 * n_internal(n) + 4)) != hipSuccess) {
@@ -523,18 +519,15 @@ irgs_status irgs_scene_build(irgs_scene s, const irgs_params* p, void* stream)
     }
     size_t sort_bytes = 0;
     lbvh_sort_scratch_bytes(static_cast<int>(n), &sort_bytes);
-    void* scratch = nullptr;
-    if ((e = hipMalloc(&scratch, sort_bytes)) != hipSuccess) return hip_fail(e, "build scratch");
+    AsyncBuf scratch;
+    if ((e = scratch.alloc(sort_bytes, st)) != hipSuccess) return hip_fail(e, "build scratch");
     BuildArgs ba = build_args(s);
-    e = lbvh_build(ba, scratch, st);
+    e = lbvh_build(ba, scratch.p, st);
     s->n_wide = ba.n_wide;
     s->wide_depth = ba.wide_depth;
-    int depth = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&depth, s->depth, sizeof(int), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
-    hipFree(scratch);
     if (e != hipSuccess) return hip_fail(e, "build");
-    s->max_depth = depth;
+    s->max_depth = ba.max_depth;
     s->bounds.store(false);
     s->built = true;
     return IRGS_OK;

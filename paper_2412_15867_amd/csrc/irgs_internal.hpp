@@ -30,15 +30,15 @@ struct BuildArgs {
     int* level_nodes;       // internal node ids grouped by depth
     std::vector<int>* levels;  // host: level offsets into level_nodes (depth + 2 entries)
     std::vector<int>* wide_levels;  // host: first node of each level of the wide tree, then their number
-    int* depth;             // device int: max number of internal ancestors of a leaf
     int2* brange;           // per binary node: first leaf, leaf count
     WideNode* wnodes;       // up to max(N - 1, 1) wide nodes
     int4* wsrc;             // per wide node and slot: (binary parent << 1 | side), -1 = empty
-    int* wscratch;          // 2 * max(N - 1, 1) + 4 ints: frontiers and counters
+    int* wscratch;          // 3 * max(N - 1, 1) + 4 ints: collapse sources and level sizes
     int leaf_size;          // surfels per cluster leaf (1..16)
     bool ploc;              // binary tree by PLOC (else the Morton radix tree)
     int n_wide;             // out (host): wide nodes built; also the refit input
     int wide_depth;         // out (host): levels of the wide tree
+    int max_depth;          // out (host): most internal ancestors of a leaf
 };
 
 hipError_t lbvh_sort_scratch_bytes(int n, size_t* bytes);

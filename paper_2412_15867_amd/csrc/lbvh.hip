@@ -19,7 +19,9 @@
 // Refit repeats 1 (in the existing leaf order) and 5 with the topology kept.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
+#include <utility>
 
 #include "irgs_device.hpp"
 #include "irgs_internal.hpp"
@@ -180,7 +182,8 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_sums(const uint32_t* __re
 }
 
 __global__ __launch_bounds__(kScanThreads) void k_scan_exclusive(uint32_t* __restrict__ data, int len,
-                                                                 const uint32_t* __restrict__ sums)
+                                                                 const uint32_t* __restrict__ sums,
+                                                                 uint32_t* __restrict__ total_out)
 {
     __shared__ uint32_t red[kScanThreads / 64];
     uint32_t run = 0;
@@ -208,6 +211,7 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_exclusive(uint32_t* __res
         const uint32_t x = wave_scan(v[j]);
         const int i = base + j * 64 + lane;
         if (i < len) data[i] = run + x - v[j];
+        if (i == len - 1 && total_out) *total_out = run + x;
         run += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(x), 63));
     }
 }
@@ -439,10 +443,12 @@ __global__ void k_node_depth(int nint, const BvhNode* __restrict__ nodes, int* _
 // fall into a few dozen bins, whose global atomics would serialise).
 constexpr int kLevelBins = 1024;
 
-__global__ void k_level_hist(int nint, int nbins, const int* __restrict__ ndepth, int* __restrict__ hist)
+__global__ void k_level_hist(int nint, int nbins, const int* __restrict__ maxd, const int* __restrict__ ndepth,
+                             int* __restrict__ hist)
 {
     __shared__ int h[kLevelBins];
     const int x = blockIdx.x * blockDim.x + threadIdx.x;
+    if (*maxd >= nbins) return;  // deeper than the caller assumed: it counts again
     if (nbins > kLevelBins) {
         if (x < nint) atomicAdd(&hist[ndepth[x]], 1);
         return;
@@ -654,20 +660,6 @@ __global__ void k_child_slabs(int begin, int count, WideNode* wn, const SurfelRe
     out->slab = w.slab;
 }
 
-__global__ void k_depth(int n, const int* __restrict__ leaf_parent, const BvhNode* __restrict__ nodes,
-                        int* __restrict__ depth_out)
-{
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    int d = 0;
-    int node = leaf_parent[p];
-    while (node >= 0) {
-        ++d;
-        node = nodes[node].ch.z;
-    }
-    atomicMax(depth_out, d);
-}
-
 __global__ void k_fill_u32(uint32_t* __restrict__ p, int64_t n, uint32_t v)
 {
     for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < n;
@@ -705,15 +697,21 @@ __device__ __forceinline__ void set_wide_box(WideNode* w, int slot, const float*
 // the largest box area, as long as that candidate holds more than leaf_max
 // surfels.  Candidates with at most leaf_max surfels become cluster leaves
 // (their surfels are contiguous in leaf order); larger ones become new wide
-// nodes of the next level.
-__global__ void k_collapse(int nfront, const int* __restrict__ front_in, int* __restrict__ front_out,
-                           int* __restrict__ counts, int* __restrict__ wide_src, const BvhNode* __restrict__ bn,
-                           const int2* __restrict__ brange, WideNode* __restrict__ wn, int4* __restrict__ wsrc,
-                           int leaf_max)
+// nodes of the next level.  counts[l] nodes make up level l, numbered from the
+// sum of the levels above, so levels can be queued without reading their size
+// back; a wave takes its nodes' numbers with one atomic.
+__global__ void k_collapse(int level, int* __restrict__ counts, int* __restrict__ wide_src,
+                           const BvhNode* __restrict__ bn, const int2* __restrict__ brange, WideNode* __restrict__ wn,
+                           int4* __restrict__ wsrc, int leaf_max)
 {
+    int begin = 0;
+    for (int l = 0; l < level; ++l) begin += counts[l];
+    const int nfront = counts[level];
+    const int next = begin + nfront;
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= nfront) return;
-    const int w = front_in[t];
+    if (blockIdx.x * static_cast<int>(blockDim.x) >= nfront) return;  // whole blocks
+    const bool live = t < nfront;
+    const int w = begin + (live ? t : 0);
     const int b = wide_src[w];
     int ref[4], par[4], side[4];
     float area[4];
@@ -749,6 +747,15 @@ __global__ void k_collapse(int nfront, const int* __restrict__ front_in, int* __
         ref[m] = r1, par[m] = open, side[m] = 1, area[m] = box_area(bx);
         ++m;
     }
+    int inner = 0;
+    for (int c = 0; c < m; ++c) inner += (ref[c] & kLeafBit) == 0 && brange[ref[c]].y > leaf_max ? 1 : 0;
+    inner = live ? inner : 0;
+    const uint32_t incl = wave_scan(static_cast<uint32_t>(inner));
+    const uint32_t total = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
+    int base = 0;
+    if (total > 0 && (threadIdx.x & 63) == 0) base = atomicAdd(&counts[level + 1], static_cast<int>(total));
+    int nw = next + __builtin_amdgcn_readfirstlane(base) + static_cast<int>(incl) - inner;
+    if (!live) return;
     WideNode node;
     int4 src = make_int4(-1, -1, -1, -1);
     int* srcp = reinterpret_cast<int*>(&src);
@@ -771,10 +778,8 @@ __global__ void k_collapse(int nfront, const int* __restrict__ front_in, int* __
         } else if (brange[r].y <= leaf_max) {
             node.c[c].ref = cluster_ref(brange[r].x, brange[r].y);
         } else {
-            const int nw = atomicAdd(&counts[0], 1);
             wide_src[nw] = r;
-            front_out[atomicAdd(&counts[1], 1)] = nw;
-            node.c[c].ref = nw;
+            node.c[c].ref = nw++;
         }
     }
     wn[w] = node;
@@ -810,6 +815,8 @@ inline int blocks_for(int64_t n, int t) { return static_cast<int>((n + t - 1) / 
 // merges.  Node ids count down from n - 2: the last merge is the root, 0.
 constexpr int kPlocRadius = 8;
 constexpr int kPlocBlock = 256;
+constexpr int kPlocGroup = 8;  // iterations queued per read-back of the clusters left
+constexpr int kPlocFinish = 1024;
 
 __device__ __forceinline__ void box_union(const float* a, const float* b, float* u)
 {
@@ -840,8 +847,13 @@ __global__ void k_ploc_init(int n, const float* __restrict__ leafbox, int* __res
     for (int k = 0; k < 6; ++k) box[6 * static_cast<int64_t>(i) + k] = leafbox[6 * static_cast<int64_t>(i) + k];
 }
 
-__global__ __launch_bounds__(kPlocBlock) void k_ploc_nn(int m, const float* __restrict__ box, int* __restrict__ nn)
+// The kernels of an iteration take the clusters left from device memory
+// (survivors[iter]), so that iterations can be queued without reading it back.
+__global__ __launch_bounds__(kPlocBlock) void k_ploc_nn(const uint32_t* __restrict__ left,
+                                                         const float* __restrict__ box, int* __restrict__ nn)
 {
+    const int m = static_cast<int>(*left);
+    if (static_cast<int>(blockIdx.x) * kPlocBlock >= m) return;
     constexpr int kSpan = kPlocBlock + 2 * kPlocRadius;
     __shared__ float sb[kSpan * 6];
     const int base = blockIdx.x * kPlocBlock - kPlocRadius;
@@ -867,40 +879,23 @@ __global__ __launch_bounds__(kPlocBlock) void k_ploc_nn(int m, const float* __re
     nn[i] = bj;
 }
 
-// Mutual pairs merge (the lower position leads and keeps the new cluster in
-// place; pairs are disjoint, so no slot is read and written by two threads);
-// keep[i] flags the survivors and each block adds its count to *total.
-__global__ __launch_bounds__(kPlocBlock) void k_ploc_merge(int m, int* __restrict__ ref, float* __restrict__ box,
-                                                            const int* __restrict__ nn, BvhNode* __restrict__ nodes,
-                                                            uint32_t* __restrict__ keep,
-                                                            uint32_t* __restrict__ block_counts,
-                                                            int* __restrict__ node_counter, int top,
-                                                            uint32_t* __restrict__ total)
+// Clusters of mutual pairs merge into the lower position; the upper one goes.
+// keep[i] flags the survivors, block_counts their number per block.
+__global__ __launch_bounds__(kPlocBlock) void k_ploc_flags(const uint32_t* __restrict__ left,
+                                                            const int* __restrict__ nn, uint32_t* __restrict__ keep,
+                                                            uint32_t* __restrict__ block_counts)
 {
     __shared__ uint32_t wave_cnt[kPlocBlock / 64];
+    const int m = static_cast<int>(*left);
+    if (static_cast<int>(blockIdx.x) * kPlocBlock >= m) {  // the counts are scanned up to the launch's size
+        if (threadIdx.x == 0) block_counts[blockIdx.x] = 0;
+        return;
+    }
     const int i = blockIdx.x * kPlocBlock + threadIdx.x;
     bool kept = false;
     if (i < m) {
         const int j = nn[i];
-        const bool mutual = j >= 0 && nn[j] == i;
-        kept = !(mutual && j < i);
-        if (mutual && i < j) {
-            const int id = top - atomicAdd(node_counter, 1);
-            const int a = ref[i], b = ref[j];
-            const int ca = (a & kLeafBit) ? 1 : nodes[a].ch.w;
-            const int cb = (b & kLeafBit) ? 1 : nodes[b].ch.w;
-            nodes[id].ch = make_int4(a, b, -1, ca + cb);
-            if (!(a & kLeafBit)) nodes[a].ch.z = id;
-            if (!(b & kLeafBit)) nodes[b].ch.z = id;
-            float bi[6], bj[6], u[6];
-            for (int k = 0; k < 6; ++k) {
-                bi[k] = box[6 * static_cast<int64_t>(i) + k];
-                bj[k] = box[6 * static_cast<int64_t>(j) + k];
-            }
-            box_union(bi, bj, u);
-            for (int k = 0; k < 6; ++k) box[6 * static_cast<int64_t>(i) + k] = u[k];
-            ref[i] = id;
-        }
+        kept = !(j >= 0 && j < i && nn[j] == i);
         keep[i] = kept ? 1u : 0u;
     }
     const uint64_t bal = __ballot(kept);
@@ -910,36 +905,145 @@ __global__ __launch_bounds__(kPlocBlock) void k_ploc_merge(int m, int* __restric
         uint32_t c = 0;
         for (int w = 0; w < kPlocBlock / 64; ++w) c += wave_cnt[w];
         block_counts[blockIdx.x] = c;
-        atomicAdd(total, c);
     }
 }
 
-// Survivors to their compacted positions, in order (block offsets from the
-// exclusive scan of the block counts, ranks inside the block by ballots).
-__global__ __launch_bounds__(kPlocBlock) void k_ploc_scatter(int m, const uint32_t* __restrict__ keep,
-                                                              const uint32_t* __restrict__ offsets,
-                                                              const int* __restrict__ ref_in,
-                                                              const float* __restrict__ box_in,
-                                                              int* __restrict__ ref_out, float* __restrict__ box_out)
+__device__ __forceinline__ int ref_count(const BvhNode* nodes, int r)
+{
+    return (r & kLeafBit) ? 1 : nodes[r].ch.w;
+}
+
+// Node `id` over clusters a and b (leaf counts ca, cb).
+__device__ __forceinline__ void ploc_node(BvhNode* nodes, int id, int a, int b, int ca, int cb)
+{
+    nodes[id].ch = make_int4(a, b, -1, ca + cb);
+    if (!(a & kLeafBit)) nodes[a].ch.z = id;
+    if (!(b & kLeafBit)) nodes[b].ch.z = id;
+}
+
+// Survivors to their compacted positions, in order (block offsets from the scan
+// of the counts, ranks inside a block by ballots).  The upper cluster of a
+// pair makes the node and writes it at the lower one's new position; it is
+// the rank-th to go, so with m clusters left its node's number is m - 2 - rank:
+// no counter is shared (one atomic per merge and one per block on two counters
+// made up most of the build: 12 ns each).
+__global__ __launch_bounds__(kPlocBlock) void k_ploc_merge(const uint32_t* __restrict__ left,
+                                                            const uint32_t* __restrict__ keep,
+                                                            const uint32_t* __restrict__ offsets,
+                                                            const int* __restrict__ nn, const int* __restrict__ ref_in,
+                                                            const float* __restrict__ box_in,
+                                                            int* __restrict__ ref_out, float* __restrict__ box_out,
+                                                            BvhNode* __restrict__ nodes)
 {
     __shared__ uint32_t wave_cnt[kPlocBlock / 64];
+    const int m = static_cast<int>(*left);
+    if (static_cast<int>(blockIdx.x) * kPlocBlock >= m) return;
     const int i = blockIdx.x * kPlocBlock + threadIdx.x;
     const bool kept = i < m && keep[i] != 0;
     const uint64_t bal = __ballot(kept);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (lane == 0) wave_cnt[wave] = static_cast<uint32_t>(__popcll(bal));
     __syncthreads();
-    if (!kept) return;
-    uint32_t pos = offsets[blockIdx.x];
-    for (int w = 0; w < wave; ++w) pos += wave_cnt[w];
-    pos += static_cast<uint32_t>(__popcll(bal & ((1ull << lane) - 1ull)));
-    ref_out[pos] = ref_in[i];
-    for (int k = 0; k < 6; ++k) box_out[6 * static_cast<int64_t>(pos) + k] = box_in[6 * static_cast<int64_t>(i) + k];
+    if (i >= m) return;
+    int before = static_cast<int>(offsets[blockIdx.x]);  // survivors before i
+    for (int w = 0; w < wave; ++w) before += wave_cnt[w];
+    before += __popcll(bal & ((1ull << lane) - 1ull));
+    float b[6];
+    for (int k = 0; k < 6; ++k) b[k] = box_in[6 * static_cast<int64_t>(i) + k];
+    const int j = nn[i];
+    if (kept) {
+        if (j >= 0 && nn[j] == i) return;  // a pair's lower cluster: the upper one writes
+        ref_out[before] = ref_in[i];
+        for (int k = 0; k < 6; ++k) box_out[6 * static_cast<int64_t>(before) + k] = b[k];
+        return;
+    }
+    int at = before;  // of the partner j, a few positions below
+    for (int k = j; k < i; ++k) at -= keep[k] != 0 ? 1 : 0;
+    float a[6], u[6];
+    for (int k = 0; k < 6; ++k) a[k] = box_in[6 * static_cast<int64_t>(j) + k];
+    box_union(a, b, u);
+    const int id = m - 2 - (i - before);
+    const int ra = ref_in[j], rb = ref_in[i];
+    ploc_node(nodes, id, ra, rb, ref_count(nodes, ra), ref_count(nodes, rb));
+    ref_out[at] = id;
+    for (int k = 0; k < 6; ++k) box_out[6 * static_cast<int64_t>(at) + k] = u[k];
 }
 
-__device__ __forceinline__ int ref_count(const BvhNode* nodes, int r)
+// The remaining iterations of at most kPlocFinish clusters, in one block: half
+// of all iterations run on so few, and four launches each took longer than
+// their work.
+__global__ __launch_bounds__(kPlocFinish) void k_ploc_finish(uint32_t* __restrict__ left,
+                                                              const int* __restrict__ ref_in,
+                                                              const float* __restrict__ box_in,
+                                                              BvhNode* __restrict__ nodes)
 {
-    return (r & kLeafBit) ? 1 : nodes[r].ch.w;
+    __shared__ float box[kPlocFinish * 6];
+    __shared__ int ref[kPlocFinish], cnt[kPlocFinish], near[kPlocFinish];
+    __shared__ int wave_cnt[kPlocFinish / 64];
+    int m = static_cast<int>(*left);  // rewritten at the end, after barriers that every wave passes
+    const int i = threadIdx.x, lane = i & 63, wave = i >> 6;
+    if (i < m) {
+        ref[i] = ref_in[i];
+        cnt[i] = ref_count(nodes, ref[i]);
+        for (int k = 0; k < 6; ++k) box[6 * i + k] = box_in[6 * i + k];
+    }
+    __syncthreads();
+    while (m > 1) {
+        if (i < m) {
+            float best = 0.0f;
+            int bj = -1;
+            for (int d = -kPlocRadius; d <= kPlocRadius; ++d) {  // increasing positions: ties keep the smaller
+                const int j = i + d;
+                if (d == 0 || j < 0 || j >= m) continue;
+                const float c = union_cost(box + 6 * i, box + 6 * j);
+                if (bj < 0 || c < best) {
+                    best = c;
+                    bj = j;
+                }
+            }
+            near[i] = bj;
+        }
+        __syncthreads();
+        const int j = i < m ? near[i] : -1;
+        const bool pair = j >= 0 && near[j] == i;
+        const bool kept = i < m && !(pair && j < i);
+        const uint64_t bal = __ballot(kept);
+        if (lane == 0) wave_cnt[wave] = __popcll(bal);
+        __syncthreads();
+        int before = __popcll(bal & ((1ull << lane) - 1ull)), total = 0;
+        for (int w = 0; w < kPlocFinish / 64; ++w) {
+            before += w < wave ? wave_cnt[w] : 0;
+            total += wave_cnt[w];
+        }
+        // the lower cluster of a pair takes the union, the upper one makes the node
+        float u[6];
+        int r = -1, c = 0, upper = 0;
+        if (i < m) {
+            r = ref[i];
+            c = cnt[i];
+            if (pair && i < j) {
+                box_union(box + 6 * i, box + 6 * j, u);
+                c += cnt[j];
+                // the upper cluster's rank among those that go: survivors before it
+                for (int k = i; k < j; ++k) upper += !(near[k] >= 0 && near[k] < k && near[near[k]] == k) ? 1 : 0;
+                const int id = m - 2 - (j - (before + upper));
+                ploc_node(nodes, id, r, ref[j], cnt[i], cnt[j]);
+                r = id;
+            } else {
+                for (int k = 0; k < 6; ++k) u[k] = box[6 * i + k];
+            }
+        }
+        __syncthreads();
+        if (kept) {
+            ref[before] = r;
+            cnt[before] = c;
+            for (int k = 0; k < 6; ++k) box[6 * before + k] = u[k];
+        }
+        if (total >= m) break;  // no merge: cannot happen with finite costs
+        m = total;
+        __syncthreads();
+    }
+    if (i == 0) *left = static_cast<uint32_t>(m);
 }
 
 // First depth-first leaf of every internal node: the leaves of the left
@@ -995,12 +1099,12 @@ hipError_t fill_u32(void* p, int64_t n, uint32_t v, hipStream_t st)
     return hipGetLastError();
 }
 
-// `sums`: one word per kScanSpan counters.
-static hipError_t scan_exclusive(uint32_t* data, int len, uint32_t* sums, hipStream_t st)
+// `sums`: one word per kScanSpan counters; the sum of all goes to *total (if given).
+static hipError_t scan_exclusive(uint32_t* data, int len, uint32_t* sums, uint32_t* total, hipStream_t st)
 {
     const int nb = blocks_for(len, kScanSpan);
     if (nb > 1) k_scan_sums<<<nb, kScanThreads, 0, st>>>(data, len, sums);
-    k_scan_exclusive<<<nb, kScanThreads, 0, st>>>(data, len, sums);
+    k_scan_exclusive<<<nb, kScanThreads, 0, st>>>(data, len, sums, total);
     return hipGetLastError();
 }
 
@@ -1020,7 +1124,7 @@ hipError_t sort_pairs(int n, uint64_t* k0, uint32_t* v0, uint64_t* k1, uint32_t*
     const int ntiles = blocks_for(n, kSortTile);
     for (int pass = 0; pass < passes; ++pass) {
         k_radix_hist<<<ntiles, kSortThreads, 0, st>>>(n, pass * 8, k0, counts, ntiles);
-        hipError_t e = scan_exclusive(counts, ntiles * kRadixBins, counts + ntiles * kRadixBins, st);
+        hipError_t e = scan_exclusive(counts, ntiles * kRadixBins, counts + ntiles * kRadixBins, nullptr, st);
         if (e != hipSuccess) return e;
         k_radix_scatter<<<ntiles, kSortThreads, 0, st>>>(n, pass * 8, ntiles, k0, v0, k1, v1, counts);
         e = hipGetLastError();
@@ -1042,7 +1146,7 @@ static size_t ploc_scratch_bytes(int n)
     const size_t nb = static_cast<size_t>(blocks_for(n, kPlocBlock));
     // eight arrays, each rounded up to 256 bytes by ploc_tree
     return static_cast<size_t>(n) * (2 * (sizeof(int) + 6 * sizeof(float)) + 4 * sizeof(int)) +
-           (nb + blocks_for(static_cast<int64_t>(nb), kScanSpan)) * sizeof(uint32_t) + 2 * sizeof(int) + 8 * 256;
+           (nb + blocks_for(static_cast<int64_t>(nb), kScanSpan)) * sizeof(uint32_t) + (1 + kPlocGroup) * sizeof(uint32_t) + 8 * 256;
 }
 
 hipError_t lbvh_sort_scratch_bytes(int n, size_t* bytes)
@@ -1076,36 +1180,42 @@ static hipError_t ploc_tree(BuildArgs& a, void* scratch, hipStream_t st)
     uint32_t* keep = reinterpret_cast<uint32_t*>(take(sizeof(uint32_t) * n));
     const int nb0 = blocks_for(n, kPlocBlock);
     uint32_t* counts = reinterpret_cast<uint32_t*>(take(sizeof(uint32_t) * (nb0 + blocks_for(nb0, kScanSpan))));
-    int* ctr = reinterpret_cast<int*>(take(2 * sizeof(int)));  // node counter, survivors
+    uint32_t* survivors = reinterpret_cast<uint32_t*>(take((1 + kPlocGroup) * sizeof(uint32_t)));  // per iteration
 
     k_ploc_init<<<blocks_for(n, 256), 256, 0, st>>>(n, a.leafbox, refA, boxA);
     hipError_t e = hipGetLastError();
-    if (e == hipSuccess) e = fill_u32(ctr, 2, 0u, st);
+    if (e == hipSuccess) e = fill_u32(survivors, 1, static_cast<uint32_t>(n), st);
     int m = n;
-    for (int iter = 0; e == hipSuccess && m > 1; ++iter) {
+    while (e == hipSuccess && m > kPlocFinish) {
+        // kPlocGroup iterations per read-back (one more on a single cluster
+        // only copies it); their launches are sized for the clusters at the start
         const int nb = blocks_for(m, kPlocBlock);
-        k_ploc_nn<<<nb, kPlocBlock, 0, st>>>(m, boxA, nn);
-        e = hipGetLastError();
-        if (e == hipSuccess) e = fill_u32(ctr + 1, 1, 0u, st);
-        if (e != hipSuccess) break;
-        k_ploc_merge<<<nb, kPlocBlock, 0, st>>>(m, refA, boxA, nn, a.nodes, keep, counts, ctr, n - 2,
-                                                reinterpret_cast<uint32_t*>(ctr + 1));
-        e = scan_exclusive(counts, nb, counts + nb0, st);
-        if (e != hipSuccess) break;
-        k_ploc_scatter<<<nb, kPlocBlock, 0, st>>>(m, keep, counts, refA, boxA, refB, boxB);
-        e = hipGetLastError();
-        int survivors = m;
-        if (e == hipSuccess) e = hipMemcpyAsync(&survivors, ctr + 1, sizeof(int), hipMemcpyDeviceToHost, st);
+        for (int g = 0; e == hipSuccess && g < kPlocGroup; ++g) {
+            k_ploc_nn<<<nb, kPlocBlock, 0, st>>>(survivors + g, boxA, nn);
+            k_ploc_flags<<<nb, kPlocBlock, 0, st>>>(survivors + g, nn, keep, counts);
+            e = scan_exclusive(counts, nb, counts + nb0, survivors + g + 1, st);
+            if (e != hipSuccess) break;
+            k_ploc_merge<<<nb, kPlocBlock, 0, st>>>(survivors + g, keep, counts, nn, refA, boxA, refB, boxB, a.nodes);
+            e = hipGetLastError();
+            std::swap(refA, refB);
+            std::swap(boxA, boxB);
+        }
+        uint32_t left = 0;
+        if (e == hipSuccess)
+            e = hipMemcpyAsync(&left, survivors + kPlocGroup, sizeof(left), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) break;
-        if (survivors >= m || iter > 4 * n) return hipErrorUnknown;  // no merge: cannot happen
-        m = survivors;
-        int* tr = refA;
-        refA = refB;
-        refB = tr;
-        float* tb = boxA;
-        boxA = boxB;
-        boxB = tb;
+        if (static_cast<int64_t>(left) >= m || left == 0) return hipErrorUnknown;  // no merge: cannot happen
+        m = static_cast<int>(left);
+        e = fill_u32(survivors, 1, left, st);
+    }
+    if (e == hipSuccess) {
+        k_ploc_finish<<<1, kPlocFinish, 0, st>>>(survivors, refA, boxA, a.nodes);
+        uint32_t left = 0;
+        e = hipGetLastError();
+        if (e == hipSuccess) e = hipMemcpyAsync(&left, survivors, sizeof(left), hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e == hipSuccess && left != 1) e = hipErrorUnknown;
     }
     if (e != hipSuccess) return e;
     // the cluster buffers are free again
@@ -1119,12 +1229,11 @@ static hipError_t ploc_tree(BuildArgs& a, void* scratch, hipStream_t st)
     return e;
 }
 
-__global__ void k_collapse_init(int* wide_src, int* front, int* counts)
+__global__ void k_collapse_init(int* wide_src, int* counts, int len)
 {
-    wide_src[0] = 0;
-    front[0] = 0;
-    counts[0] = 1;
-    counts[1] = 0;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < len) counts[i] = i == 0 ? 1 : 0;
+    if (i == 0) wide_src[0] = 0;
 }
 
 // Records + leaf boxes in the current leaf order, then the node boxes level
@@ -1163,38 +1272,44 @@ static hipError_t child_slabs(const BuildArgs& a, hipStream_t st)
 
 // Internal nodes grouped by depth (root = depth 0): a.level_nodes holds their
 // ids level after level and *a.levels the level offsets (depth + 2 entries).
-// Uses the build scratch and reads the level sizes back (synchronises st).
+// Uses the build scratch and reads the depth and the level sizes back in one
+// copy (trees deeper than kLevelBins: the sizes in a second one).
 static hipError_t group_levels(BuildArgs& a, void* scratch, hipStream_t st)
 {
     const int nint = a.n > 1 ? a.n - 1 : 1;
     int* ndepth = static_cast<int*>(scratch);
     int* maxd = ndepth + nint;
-    hipError_t e = fill_u32(maxd, 1, 0u, st);
+    int* hist = maxd + 1;
+    const int bins = std::min(nint, kLevelBins);  // the depth is below nint
+    hipError_t e = fill_u32(maxd, 1 + bins, 0u, st);
     if (e != hipSuccess) return e;
     k_node_depth<<<blocks_for(nint, 256), 256, 0, st>>>(nint, a.nodes, ndepth, maxd);
-    int D = 0;
+    k_level_hist<<<blocks_for(nint, 256), 256, 0, st>>>(nint, bins, maxd, ndepth, hist);
+    std::vector<int> h(1 + bins);
     e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(&D, maxd, sizeof(int), hipMemcpyDeviceToHost, st);
+    if (e == hipSuccess) e = hipMemcpyAsync(h.data(), maxd, sizeof(int) * (1 + bins), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess) e = hipStreamSynchronize(st);
     if (e != hipSuccess) return e;
-    int* hist = maxd + 1;
-    e = fill_u32(hist, D + 1, 0u, st);
-    if (e != hipSuccess) return e;
-    k_level_hist<<<blocks_for(nint, 256), 256, 0, st>>>(nint, D + 1, ndepth, hist);
-    std::vector<int> h(D + 1);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = hipMemcpyAsync(h.data(), hist, sizeof(int) * (D + 1), hipMemcpyDeviceToHost, st);
-    if (e == hipSuccess) e = hipStreamSynchronize(st);
-    if (e != hipSuccess) return e;
+    const int D = h[0];
+    h.erase(h.begin());
+    if (D >= bins) {
+        h.resize(D + 1);
+        e = fill_u32(hist, D + 1, 0u, st);
+        if (e != hipSuccess) return e;
+        k_level_hist<<<blocks_for(nint, 256), 256, 0, st>>>(nint, D + 1, maxd, ndepth, hist);
+        e = hipGetLastError();
+        if (e == hipSuccess) e = hipMemcpyAsync(h.data(), hist, sizeof(int) * (D + 1), hipMemcpyDeviceToHost, st);
+        if (e == hipSuccess) e = hipStreamSynchronize(st);
+        if (e != hipSuccess) return e;
+    }
     std::vector<int>& off = *a.levels;
     off.assign(D + 2, 0);
     for (int d = 0; d <= D; ++d) off[d + 1] = off[d] + h[d];
+    // (a pageable source is staged before the call returns)
     e = hipMemcpyAsync(hist, off.data(), sizeof(int) * (D + 1), hipMemcpyHostToDevice, st);
     if (e != hipSuccess) return e;
     k_level_scatter<<<blocks_for(nint, 256), 256, 0, st>>>(nint, D + 1, ndepth, hist, a.level_nodes);
-    e = hipGetLastError();
-    if (e == hipSuccess) e = hipStreamSynchronize(st);  // the host offsets outlive this call
-    return e;
+    return hipGetLastError();
 }
 
 hipError_t lbvh_build(BuildArgs& a, void* scratch, hipStream_t st)
@@ -1249,45 +1364,42 @@ hipError_t lbvh_build(BuildArgs& a, void* scratch, hipStream_t st)
     if (e != hipSuccess) return e;
     e = refit_boxes(a, st);
     if (e != hipSuccess) return e;
-    // top-down collapse into the 4-wide tree, one level per launch
+    // top-down collapse into the 4-wide tree, one launch per level; the sizes
+    // are read back once per kCollapseGroup levels
     {
-        const int nmax = nint;
+        constexpr int kCollapseGroup = 16;
         int* wide_src = a.wscratch;
-        int* fa = a.wscratch + nmax;
-        int* fb = a.wscratch + 2 * nmax;
-        int* counts = a.wscratch + 3 * nmax;
-        k_collapse_init<<<1, 1, 0, st>>>(wide_src, fa, counts);
-        int nfront = 1, levels = 0;
+        int* counts = a.wscratch + nint;  // 2 nint + 4 words: more than the levels there can be
+        const int len = std::min(nint + 1, 2 * nint + 4);
+        k_collapse_init<<<blocks_for(len, 256), 256, 0, st>>>(wide_src, counts, len);
         std::vector<int>& off = *a.wide_levels;
         off.assign(1, 0);
-        while (nfront > 0) {
-            off.push_back(off.back() + nfront);  // a level's nodes are numbered together
-            e = fill_u32(counts + 1, 1, 0u, st);
-            if (e != hipSuccess) return e;
-            k_collapse<<<blocks_for(nfront, 128), 128, 0, st>>>(nfront, fa, fb, counts, wide_src, a.nodes,
-                                                                  a.brange, a.wnodes, a.wsrc, a.leaf_size);
+        int h[kCollapseGroup + 1];
+        int known = 1, level = 0;  // nodes of `level`
+        while (known > 0) {
+            const int group = std::min(kCollapseGroup, len - 1 - level);
+            int64_t bound = known;
+            for (int l = 0; l < group; ++l) {
+                k_collapse<<<blocks_for(bound, 128), 128, 0, st>>>(level + l, counts, wide_src, a.nodes, a.brange,
+                                                                   a.wnodes, a.wsrc, a.leaf_size);
+                bound = std::min<int64_t>(4 * bound, nint);
+            }
             e = hipGetLastError();
-            if (e == hipSuccess) e = hipMemcpyAsync(&nfront, counts + 1, sizeof(int), hipMemcpyDeviceToHost, st);
+            if (e == hipSuccess)
+                e = hipMemcpyAsync(h, counts + level, sizeof(int) * (group + 1), hipMemcpyDeviceToHost, st);
             if (e == hipSuccess) e = hipStreamSynchronize(st);
             if (e != hipSuccess) return e;
-            int* t = fa;
-            fa = fb;
-            fb = t;
-            ++levels;
+            for (int l = 0; l < group && h[l] > 0; ++l) off.push_back(off.back() + h[l]);
+            level += group;
+            known = group > 0 ? h[group] : 0;
         }
-        int nw = 0;
-        e = hipMemcpyAsync(&nw, counts, sizeof(int), hipMemcpyDeviceToHost, st);
-        if (e == hipSuccess) e = hipStreamSynchronize(st);
-        if (e != hipSuccess) return e;
-        a.n_wide = nw;
-        a.wide_depth = levels;
+        a.n_wide = off.back();
+        a.wide_depth = static_cast<int>(off.size()) - 1;
     }
     e = child_slabs(a, st);
     if (e != hipSuccess) return e;
-    e = fill_u32(a.depth, 1, 0u, st);
-    if (e != hipSuccess) return e;
-    k_depth<<<blocks_for(n, 256), 256, 0, st>>>(n, a.leaf_parent, a.nodes, a.depth);
-    return hipGetLastError();
+    a.max_depth = static_cast<int>(a.levels->size()) - 1;  // a leaf's ancestors: the deepest node's depth + 1
+    return hipSuccess;
 }
 
 hipError_t lbvh_refit(const BuildArgs& a, hipStream_t st)
