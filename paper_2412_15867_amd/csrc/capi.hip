@@ -303,6 +303,8 @@ irgs_status noalloc_scratch_ptr(char** out)
     return IRGS_OK;
 }
 
+size_t aligned(size_t bytes) { return (bytes + 255) & ~static_cast<size_t>(255); }
+
 struct AsyncBuf {
     void* p = nullptr;
     hipStream_t st = nullptr;
@@ -562,7 +564,8 @@ irgs_status irgs_trace(irgs_scene s, const irgs_params* p, int64_t R, const floa
     const bool lanes = !use_wave_trace(bvh, out->counters != nullptr, s->wide_depth);
     const size_t thr = lanes ? static_cast<size_t>(trace_threads(R)) : 0;
     hipError_t e = ovf.alloc(thr * slots * sizeof(int), hs);
-    if (e == hipSuccess && bvh) e = dq.alloc(kClaimBytes + thr * 2 * kDeferCap * sizeof(int), hs);
+    if (e == hipSuccess && bvh && (lanes || wave_claims(trace_params(p, s->F), R)))
+        e = dq.alloc(kClaimBytes + thr * 2 * kDeferCap * sizeof(int), hs);
     if (e == hipSuccess && sorted) e = srt.alloc(ray_sort_words(R) * sizeof(float), hs);
     if (e == hipSuccess && bvh && lanes) e = need_cluster_bounds(s, hs);
     if (e != hipSuccess) return hip_fail(e, "trace scratch");
@@ -626,17 +629,17 @@ irgs_status irgs_trace_backward(irgs_scene s, const irgs_params* p, int64_t R, c
     GradIn g{gin->g_opacity, gin->g_feat, gin->g_depth};
     GradOut go{grads->mu, grads->quat, grads->scale, grads->opacity, grads->feat};
     // the parameters packed one row per surfel, read by every hit's gradient
-    AsyncBuf pk;
-    hipError_t pe = pk.alloc(static_cast<size_t>(s->n) * raw.ps * sizeof(float), hs);
-    if (pe == hipSuccess) pe = pack_surfels(raw, s->n, s->F, static_cast<float*>(pk.p), hs);
-    if (pe != hipSuccess) return hip_fail(pe, "backward parameter pack");
-    raw.pk = static_cast<const float*>(pk.p);
+    const size_t pk_bytes = static_cast<size_t>(s->n) * raw.ps * sizeof(float);
+    AsyncBuf mem;  // one allocation: each costs the host 30 to 80 us to make and to give back
     if (use_saved) {
-        AsyncBuf ck;
-        hipError_t e = ck.alloc(plan_backward(R, s->n, s->F, s->wide_depth).bytes, hs);
+        const size_t ck = aligned(pk_bytes);
+        hipError_t e = mem.alloc(ck + plan_backward(R, s->n, s->F, s->wide_depth).bytes, hs);
         if (e != hipSuccess) return hip_fail(e, "backward scratch");
+        e = pack_surfels(raw, s->n, s->F, static_cast<float*>(mem.p), hs);
+        if (e != hipSuccess) return hip_fail(e, "backward parameter pack");
+        raw.pk = static_cast<const float*>(mem.p);
         e = launch_backward(view_of(s), raw, tp, p->k, R, ro, rd, out_ptrs(saved), g, go, s->wide_depth,
-                            static_cast<char*>(ck.p), hs);
+                            static_cast<char*>(mem.p) + ck, hs);
         if (e != hipSuccess) return hip_fail(e, "backward launch");
         return IRGS_OK;
     }
@@ -653,18 +656,28 @@ irgs_status irgs_trace_backward(irgs_scene s, const irgs_params* p, int64_t R, c
     const bool bvh = !(p->flags & IRGS_FLAG_BRUTE_FORCE);
     const size_t thr = static_cast<size_t>(trace_threads(B));
     const bool sorted = bvh && (p->flags & IRGS_FLAG_SORT_RAYS) && ray_sort_words(B) > 0;
-    AsyncBuf ovf, dq, ck, lists, srt;
     const size_t lane_thr = use_wave_trace(bvh, false, s->wide_depth) ? 0 : thr;  // of the retrace
     const int slots = bvh ? ovf_slots_of(s) : 0;
-    hipError_t e = ovf.alloc(lane_thr * slots * sizeof(int), hs);
-    if (e == hipSuccess && bvh) e = dq.alloc(kClaimBytes + lane_thr * 2 * kDeferCap * sizeof(int), hs);
-    if (e == hipSuccess && sorted) e = srt.alloc(ray_sort_words(B) * sizeof(float), hs);
-    if (e == hipSuccess) e = ck.alloc(plan_backward(B, s->n, s->F, s->wide_depth).bytes, hs);
-    if (e == hipSuccess) e = lists.alloc(static_cast<size_t>(B) * per_ray, hs);
+    size_t total = aligned(pk_bytes);
+    auto place = [&](size_t bytes) {
+        const size_t at = total;
+        total += aligned(bytes);
+        return at;
+    };
+    const size_t ovf = place(lane_thr * slots * sizeof(int));
+    const size_t dq = place(bvh ? kClaimBytes + lane_thr * 2 * kDeferCap * sizeof(int) : 0);
+    const size_t srt = place(sorted ? ray_sort_words(B) * sizeof(float) : 0);
+    const size_t ck = place(plan_backward(B, s->n, s->F, s->wide_depth).bytes);
+    const size_t lists = place(static_cast<size_t>(B) * per_ray);
+    hipError_t e = mem.alloc(total, hs);
     if (e == hipSuccess && lane_thr > 0) e = need_cluster_bounds(s, hs);
     if (e != hipSuccess) return hip_fail(e, "backward scratch");
+    char* base = static_cast<char*>(mem.p);
+    e = pack_surfels(raw, s->n, s->F, static_cast<float*>(mem.p), hs);
+    if (e != hipSuccess) return hip_fail(e, "backward parameter pack");
+    raw.pk = static_cast<const float*>(mem.p);
     OutPtrs tmp{};
-    tmp.hit_ids = static_cast<int32_t*>(lists.p);
+    tmp.hit_ids = reinterpret_cast<int32_t*>(base + lists);
     tmp.hit_T = reinterpret_cast<float*>(tmp.hit_ids + static_cast<size_t>(B) * kRetraceCap);
     tmp.O = tmp.hit_T + static_cast<size_t>(B) * kRetraceCap;
     tmp.D = tmp.O + B;
@@ -672,19 +685,19 @@ irgs_status irgs_trace_backward(irgs_scene s, const irgs_params* p, int64_t R, c
     tmp.feat = reinterpret_cast<float*>(tmp.n_hits + B);
     tmp.H_cap = kRetraceCap;
     const SceneView sv = view_of(s);
-    FlatScratch fs = flat_scratch(ovf.p, slots, dq.p, s->wide_depth);
+    FlatScratch fs = flat_scratch(base + ovf, slots, bvh ? base + dq : nullptr, s->wide_depth);
     for (int64_t b0 = 0; b0 < R; b0 += B) {
         const int64_t nb = std::min(B, R - b0);
         const float* bro = ro + 3 * b0;
         const float* brd = rd + 3 * b0;
         if (sorted) {
-            e = ray_order_by_origin(sv, nb, bro, srt.p, &fs.order, hs);
+            e = ray_order_by_origin(sv, nb, bro, base + srt, &fs.order, hs);
             if (e != hipSuccess) return hip_fail(e, "ray order");
         }
         e = launch_trace(sv, tp, p->k, bvh, nb, bro, brd, tmp, fs, hs);
         if (e != hipSuccess) return hip_fail(e, "backward retrace");
         const GradIn gb{g.gO ? g.gO + b0 : nullptr, g.gF ? g.gF + b0 * fo : nullptr, g.gD ? g.gD + b0 : nullptr};
-        e = launch_backward(sv, raw, tp, p->k, nb, bro, brd, tmp, gb, go, s->wide_depth, static_cast<char*>(ck.p), hs);
+        e = launch_backward(sv, raw, tp, p->k, nb, bro, brd, tmp, gb, go, s->wide_depth, base + ck, hs);
         if (e != hipSuccess) return hip_fail(e, "backward launch");
     }
     return IRGS_OK;

@@ -170,6 +170,9 @@ hipError_t ray_order_by_origin(const SceneView& sc, int64_t R, const float* ro, 
 // (work counters asked for, or a wide tree deeper than the wave's stack takes).
 bool use_wave_trace(bool bvh, bool counters, int wide_depth);
 constexpr int kWaveClaimBytes = 1024;  // the claim counters of a wave launch
+// True when a wave launch over R rays takes claim counters (more rays than
+// waves fit the chip).
+bool wave_claims(const TraceParams& P, int64_t R);
 
 // Forward trace.  use_bvh = false tests every record (the plain tracer).
 hipError_t launch_trace(const SceneView& sc, const TraceParams& P, int k, bool use_bvh, int64_t R,

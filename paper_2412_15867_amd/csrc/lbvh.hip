@@ -504,17 +504,70 @@ __global__ void k_leaf_up(int n, const float* __restrict__ leafbox, BvhNode* __r
     put_child_box(&nodes[node], nodes[node].ch.x == (p | kLeafBit) ? 0 : 1, b);
 }
 
-// Every node of one level: the union of its two slots into its parent's.
-__global__ void k_level_up(int cnt, const int* __restrict__ ids, BvhNode* __restrict__ nodes)
+// Consecutive small levels, deepest first: level l of the run has the elements
+// [begin[l], begin[l] + count[l]), at most kRunBlock threads' worth each.
+constexpr int kRunBlock = 1024;
+constexpr int kRunLevels = 32;
+struct LevelRun {
+    int levels;
+    int begin[kRunLevels], count[kRunLevels];
+};
+
+// Launches levels off.size() - 2 ... last, deepest first: a level of more than
+// kRunBlock threads by `wide`(level), runs of smaller ones by `run`(LevelRun).
+// A launch costs the host and the chip's front end about 5 us each, more than
+// a small level's work, which is one block's either way: with 512 surfels a
+// refit's 16 level launches became 2, a training step 401 -> 279 us (together
+// with the backward's one scratch allocation).
+template <class Wide, class Run>
+hipError_t by_levels(const std::vector<int>& off, int last, int per_element, Wide wide, Run run)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= cnt) return;
-    const int x = ids[t];
+    LevelRun lr{};
+    hipError_t e = hipSuccess;
+    for (int d = static_cast<int>(off.size()) - 2; e == hipSuccess && d >= last - 1; --d) {
+        const int cnt = d >= last ? off[d + 1] - off[d] : 0;
+        const bool big = static_cast<int64_t>(cnt) * per_element > kRunBlock;
+        if (lr.levels > 0 && (d < last || big || lr.levels == kRunLevels)) {
+            run(lr);
+            e = hipGetLastError();
+            lr.levels = 0;
+        }
+        if (e != hipSuccess || cnt <= 0) continue;
+        if (big) {
+            wide(d);
+            e = hipGetLastError();
+        } else {
+            lr.begin[lr.levels] = off[d];
+            lr.count[lr.levels++] = cnt;
+        }
+    }
+    return e;
+}
+
+// The union of a node's two slots into its parent's.
+__device__ __forceinline__ void node_up(int x, BvhNode* nodes)
+{
     const BvhNode nd = nodes[x];
     float b[6];
     node_union(nd, b);
     const int parent = nd.ch.z;
     put_child_box(&nodes[parent], nodes[parent].ch.x == x ? 0 : 1, b);
+}
+
+// Every node of one level.
+__global__ void k_level_up(int cnt, const int* __restrict__ ids, BvhNode* __restrict__ nodes)
+{
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < cnt) node_up(ids[t], nodes);
+}
+
+// The levels of a run, one block.
+__global__ __launch_bounds__(kRunBlock) void k_levels_up(LevelRun run, const int* __restrict__ ids, BvhNode* nodes)
+{
+    for (int l = 0; l < run.levels; ++l) {
+        if (static_cast<int>(threadIdx.x) < run.count[l]) node_up(ids[run.begin[l] + threadIdx.x], nodes);
+        __syncthreads();
+    }
 }
 
 // An FP16 no smaller than x >= 0 (+inf past the FP16 range), as its bits.
@@ -584,10 +637,8 @@ __global__ void k_cluster_slabs(int nw, const WideNode* __restrict__ wn, SurfelR
 // discs lie in box and slab alike: along N they reach at most the box's
 // extent, or their slab's thickness turned by the angle between the normals
 // plus the box's diagonal times its sine.
-__global__ void k_child_slabs(int begin, int count, WideNode* wn, const SurfelRec* __restrict__ rec)
+__device__ void child_slab_store(int begin, int t, WideNode* wn, const SurfelRec* __restrict__ rec)
 {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= 4 * count) return;
     WideChild* out = &wn[begin + (t >> 2)].c[t & 3];
     WideChild w = *out;
     const float inf = __int_as_float(0x7f800000);
@@ -658,6 +709,22 @@ __global__ void k_child_slabs(int begin, int count, WideNode* wn, const SurfelRe
         }
     }
     out->slab = w.slab;
+}
+
+__global__ void k_child_slabs(int begin, int count, WideNode* wn, const SurfelRec* __restrict__ rec)
+{
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < 4 * count) child_slab_store(begin, t, wn, rec);
+}
+
+// The levels of a run, one block.
+__global__ __launch_bounds__(kRunBlock) void k_child_slabs_run(LevelRun run, WideNode* wn,
+                                                                const SurfelRec* __restrict__ rec)
+{
+    for (int l = 0; l < run.levels; ++l) {
+        if (static_cast<int>(threadIdx.x) < 4 * run.count[l]) child_slab_store(run.begin[l], threadIdx.x, wn, rec);
+        __syncthreads();
+    }
 }
 
 __global__ void k_fill_u32(uint32_t* __restrict__ p, int64_t n, uint32_t v)
@@ -1245,14 +1312,15 @@ static hipError_t refit_boxes(const BuildArgs& a, hipStream_t st)
                                                     a.sigma, a.rec, a.leafbox);
     k_leaf_up<<<blocks_for(n, 256), 256, 0, st>>>(n, a.leafbox, a.nodes, a.leaf_parent);
     hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
     const std::vector<int>& off = *a.levels;
-    for (int d = static_cast<int>(off.size()) - 2; e == hipSuccess && d >= 1; --d) {
-        const int cnt = off[d + 1] - off[d];
-        if (cnt <= 0) continue;
-        k_level_up<<<blocks_for(cnt, 256), 256, 0, st>>>(cnt, a.level_nodes + off[d], a.nodes);
-        e = hipGetLastError();
-    }
-    return e;
+    return by_levels(
+        off, 1, 1,
+        [&](int d) {
+            const int cnt = off[d + 1] - off[d];
+            k_level_up<<<blocks_for(cnt, 256), 256, 0, st>>>(cnt, a.level_nodes + off[d], a.nodes);
+        },
+        [&](const LevelRun& run) { k_levels_up<<<1, kRunBlock, 0, st>>>(run, a.level_nodes, a.nodes); });
 }
 
 // Slabs of the wide tree's children, deepest level first (an inner child's
@@ -1260,14 +1328,13 @@ static hipError_t refit_boxes(const BuildArgs& a, hipStream_t st)
 static hipError_t child_slabs(const BuildArgs& a, hipStream_t st)
 {
     const std::vector<int>& off = *a.wide_levels;
-    hipError_t e = hipSuccess;
-    for (int d = static_cast<int>(off.size()) - 2; e == hipSuccess && d >= 0; --d) {
-        const int cnt = off[d + 1] - off[d];
-        if (cnt <= 0) continue;
-        k_child_slabs<<<blocks_for(4 * static_cast<int64_t>(cnt), 256), 256, 0, st>>>(off[d], cnt, a.wnodes, a.rec);
-        e = hipGetLastError();
-    }
-    return e;
+    return by_levels(
+        off, 0, 4,
+        [&](int d) {
+            const int cnt = off[d + 1] - off[d];
+            k_child_slabs<<<blocks_for(4 * static_cast<int64_t>(cnt), 256), 256, 0, st>>>(off[d], cnt, a.wnodes, a.rec);
+        },
+        [&](const LevelRun& run) { k_child_slabs_run<<<1, kRunBlock, 0, st>>>(run, a.wnodes, a.rec); });
 }
 
 // Internal nodes grouped by depth (root = depth 0): a.level_nodes holds their

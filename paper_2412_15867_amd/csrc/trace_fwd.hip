@@ -260,13 +260,19 @@ void k_trace_wave(Source src, TraceParams P, unsigned long long* next, int reser
 }
 
 template <int CM, class Source>
+int64_t waves_at_once()
+{
+    const int64_t resident = resident_blocks(k_trace_wave<CM, Source>, kWaveBlock);
+    return resident > 0 ? resident : 256 * 16;
+}
+
+template <int CM, class Source>
 hipError_t launch_wave(const Source& src, int64_t rays, const TraceParams& P, unsigned long long* next, int wide_depth,
                        hipStream_t st)
 {
-    const int64_t resident = resident_blocks(k_trace_wave<CM, Source>, kWaveBlock);
-    const int64_t waves = resident > 0 ? resident : 256 * 16;
     const int reserve = wave_stack_reserve(wide_depth);
-    if (rays <= waves) {  // every ray has a wave of its own: nothing to claim or clear
+    const int64_t waves = waves_at_once<CM, Source>();
+    if (rays <= waves || !next) {  // every ray has a wave of its own: nothing to claim or clear
         k_trace_wave<CM, Source><<<static_cast<unsigned>(rays), kWaveBlock, 0, st>>>(src, P, nullptr, reserve);
         return hipGetLastError();
     }
@@ -289,6 +295,13 @@ bool features_offered(int k, int F, bool special)
 bool use_wave_trace(bool bvh, bool counters, int wide_depth)
 {
     return bvh && !counters && wave_stack_fits(wide_depth);
+}
+
+bool wave_claims(const TraceParams& P, int64_t R)
+{
+    if (P.sh_deg >= 0) return R > waves_at_once<kColSH, WavePlain>();
+    if (P.normals) return R > waves_at_once<kColNormal, WavePlain>();
+    return R > waves_at_once<kColPlain, WavePlain>();
 }
 
 hipError_t launch_trace(const SceneView& sc, const TraceParams& P, int k, bool use_bvh, int64_t R,
