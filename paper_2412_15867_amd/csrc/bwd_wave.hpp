@@ -20,10 +20,17 @@
 // hit, two scattered list reads per hit, 96 slots): 1M surfels, F = 8 18.4 ->
 // 16.4 ms, SH degree 3 58.0 -> 42.6 ms; 5M surfels 51 -> 38.6 ms and the rays
 // with cut lists, re-marched by one lane each before, 219 -> 7 ms.  With LDS
-// atomics: 25.1 and 67.5 ms.  What bounds it: of 40,000 cycles per step of a
-// block of 12 waves, 14,000 are the FP64 chain rule (VALU), 10,500 the table,
-// 7,000 waiting for the slowest wave, 6,000 slots and staging, 4,000 writing
-// out (135M atomic requests of 64 bytes, against 188M hits).
+// atomics: 25.1 and 67.5 ms.  Of 40,000 cycles per step of a block of 12 waves
+// 14,000 went to the FP64 chain rule and its loads, so these were cut: a row's
+// reciprocals are packed once per surfel, its loads are all issued at once
+// (none behind a branch), the first words a step ahead: F = 8 16.3 -> 14.3 ms.
+// With many components the table is what counts: groups of 3 rays leave room
+// for more slots than groups of 16: SH 41.3 -> 36.8 ms, 262,144 SH rays of 1,024
+// pixels 4.1 -> 2.8 ms; 24 and 64 features, groups of 8 -> 3, 10.0 -> 9.5 and
+// 15.2 -> 14.3 ms; 8 and 16 features lose or are level.  What bounds it: F = 8
+// the steps' own work (VALU 35%, 135M atomic requests of 64 bytes against 188M
+// hits); SH the atomics (472M before the groups of 3: they are done in memory,
+// 11 per ns).
 #pragma once
 
 #include "irgs_internal.hpp"
@@ -39,8 +46,8 @@ constexpr int kWalkProbes = 16;
 template <int FM>
 struct WalkShape {
     static constexpr int waves = 12;
-    static constexpr int group = FM <= 48 ? 16 : 8;  // rays per group at most
-    static constexpr int slots = FM <= 8 ? 1350 : FM <= 16 ? 900 : FM <= 48 ? 400 : 290;
+    static constexpr int group = FM <= 16 ? 16 : 3;  // rays per group at most
+    static constexpr int slots = FM <= 8 ? 1350 : FM <= 16 ? 900 : FM <= 48 ? 476 : 350;
     static constexpr int comps = 10 + FM;
     static constexpr int per_wave = (comps + waves - 1) / waves;  // components a wave adds
     static constexpr int stride = slots | 1;      // words between components: odd, so a row's lie in different banks
@@ -151,7 +158,7 @@ struct WalkHit {
     uint32_t lit;  // SH: channels that are not clamped
 };
 
-// One step: lane's hit (id, transmittance Ti before it) of the ray in row ri;
+// One step: lane's hit (id, 0 if not valid, transmittance Ti before it) of the ray in row ri;
 // `last`: the ray's last hit (its suffix is 0).  S carries the suffix from step
 // to step.  The geometry and the chain rule are evaluated in FP64 from the
 // FP32 parameters: for a grazing ray (small n.r_d) FP32 rounding of the depth
@@ -163,22 +170,31 @@ struct WalkHit {
 // gradient of n.
 template <int FM, int CM>
 __device__ __forceinline__ WalkHit walk_step(const RawSurfels& raw, const TraceParams& P, const lds_f32* rows, int ri,
-                                             bool valid, bool last, int id, float Ti_f, double& S, int lane)
+                                             bool valid, bool last, int id, float4 mo, float Ti_f, double& S, int lane)
 {
     using Row = WalkRow<FM, CM>;
     const lds_f32* row = rows + ri * Row::words;
     const int F = P.F;
-    const int sid = valid ? id : 0;
-    const float* prow = raw.pk + static_cast<int64_t>(sid) * raw.ps;  // the packed copy of the surfel's parameters
-    const float4 mo = *reinterpret_cast<const float4*>(prow);
+    const float* prow = raw.pk + static_cast<int64_t>(id) * raw.ps;  // the packed copy of the surfel's parameters
     const float4 qf = *reinterpret_cast<const float4*>(prow + 4);
-    const float2 sc = *reinterpret_cast<const float2*>(prow + 8);
-    const float* f = raw.feat_packed ? prow + 12 : raw.feat + static_cast<int64_t>(sid) * F;
+    // Every load of the hit is issued here, none behind a branch: a load in a
+    // branch waits for itself before the next.
+    constexpr int held = CM != kColSH && FM <= 16 ? FM : 0;  // features in the row, zeros past F
+    float4 ff[held / 4 + 1];
+#pragma unroll
+    for (int k = 0; k < held / 4; ++k) ff[k] = *reinterpret_cast<const float4*>(prow + 12 + 4 * k);
+    const float* f = raw.feat_packed ? prow + 12 : raw.feat + static_cast<int64_t>(id) * F;
     const float gO = row[6], gD_f = row[7];
-    const double su = sc.x, sv = sc.y;
     const double o = mo.w;
-    const double qq = double(qf.x) * qf.x + double(qf.y) * qf.y + double(qf.z) * qf.z + double(qf.w) * qf.w;
-    const double inv = 1.0 / sqrt(qq);
+    const double inv = *reinterpret_cast<const double*>(prow + 10);
+    double rsu, rsv;
+    if (FM <= 48 || raw.recips) {
+        const double2 rs = *reinterpret_cast<const double2*>(prow + raw.ps - 4);
+        rsu = rs.x, rsv = rs.y;
+    } else {
+        const float2 sc = *reinterpret_cast<const float2*>(prow + 8);
+        rsu = 1.0 / double(sc.x), rsv = 1.0 / double(sc.y);
+    }
     const double w = qf.x * inv, x = qf.y * inv, y = qf.z * inv, z = qf.w * inv;
     const double tu0 = 1.0 - 2.0 * (y * y + z * z), tu1 = 2.0 * (x * y + w * z), tu2 = 2.0 * (x * z - w * y);
     const double tv0 = 2.0 * (x * y - w * z), tv1 = 1.0 - 2.0 * (x * x + z * z), tv2 = 2.0 * (y * z + w * x);
@@ -188,7 +204,6 @@ __device__ __forceinline__ WalkHit walk_step(const RawSurfels& raw, const TraceP
     const double rden = 1.0 / (n0 * dx_ + n1 * dy_ + n2 * dz_);
     const double tau = (n0 * wx + n1 * wy + n2 * wz) * rden;
     const double px = tau * dx_ - wx, py = tau * dy_ - wy, pz = tau * dz_ - wz;
-    const double rsu = 1.0 / su, rsv = 1.0 / sv;
     const double u = (px * tu0 + py * tu1 + pz * tu2) * rsu;
     const double v = (px * tv0 + py * tv1 + pz * tv2) * rsv;
     const double G = exp(-0.5 * (u * u + v * v));
@@ -203,10 +218,18 @@ __device__ __forceinline__ WalkHit walk_step(const RawSurfels& raw, const TraceP
     if constexpr (CM == kColSH) {
         const int nb = (P.sh_deg + 1) * (P.sh_deg + 1);
         float col[3] = {0.5f, 0.5f, 0.5f};
-        for (int j = 0; j < nb; ++j) {
-            const float Y = row[Row::basis + j];
+        int j0 = 0;
+        for (; j0 + 4 <= nb; j0 += 4) {  // a dozen loads in flight
+            float x[12];
 #pragma unroll
-            for (int ch = 0; ch < 3; ++ch) col[ch] = fmaf(Y, f[3 * j + ch], col[ch]);
+            for (int i = 0; i < 12; ++i) x[i] = f[3 * j0 + i];
+#pragma unroll
+            for (int i = 0; i < 12; ++i) col[i % 3] = fmaf(row[Row::basis + j0 + i / 3], x[i], col[i % 3]);
+        }
+        for (; j0 < nb; ++j0) {
+            const float Y = row[Row::basis + j0];
+#pragma unroll
+            for (int ch = 0; ch < 3; ++ch) col[ch] = fmaf(Y, f[3 * j0 + ch], col[ch]);
         }
 #pragma unroll
         for (int ch = 0; ch < 3; ++ch) {
@@ -215,9 +238,18 @@ __device__ __forceinline__ WalkHit walk_step(const RawSurfels& raw, const TraceP
             h.lit |= col[ch] > 0.0f ? 1u << ch : 0u;
         }
     } else {
+        if constexpr (held > 0) {
 #pragma unroll
-        for (int k = 0; k < FM; ++k)
-            if (k < F) c += double(row[8 + k]) * f[k];
+            for (int k = 0; k < FM; ++k) {
+                const float fk = reinterpret_cast<const float*>(ff)[k];
+                // (the upstream past F is zero, but for the normal's channels)
+                if (CM != kColNormal || k < F) c += double(row[8 + k]) * fk;
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < FM; ++k)
+                if (k < F) c += double(row[8 + k]) * f[k];
+        }
         if constexpr (CM == kColNormal) {
             float tf[3], vf[3], nf[3];
             quat_frame(qf, tf, vf, nf);
@@ -435,6 +467,7 @@ void k_walk(RawSurfels raw, TraceParams P, int64_t R, const float* __restrict__ 
     int id = 0, ri = 0, held = 0, segs = 0;
     float Ti = 0.0f;
     bool valid = false, last = false;
+    float4 mo{};
     auto take_hits = [&]() {
         // the ray of stream place at + lane: the one that holds `at`, plus the
         // rays that start between
@@ -497,7 +530,10 @@ void k_walk(RawSurfels raw, TraceParams P, int64_t R, const float* __restrict__ 
                     first = __float_as_int(l[3]);
                     end = first + __float_as_int(l[2]);
                 }
-                if (n_hits > 0) take_hits();
+                if (n_hits > 0) {
+                    take_hits();
+                    mo = *reinterpret_cast<const float4*>(raw.pk + static_cast<int64_t>(id) * raw.ps);
+                }
             }
         }
         if (at < n_hits) {
@@ -505,7 +541,7 @@ void k_walk(RawSurfels raw, TraceParams P, int64_t R, const float* __restrict__ 
                 take_rays();
             else if (ahead == 0 && more)
                 take_group();
-            const WalkHit hit = walk_step<FM, CM>(raw, P, rows, ri, valid, last, id, Ti, S, lane);
+            const WalkHit hit = walk_step<FM, CM>(raw, P, rows, ri, valid, last, id, mo, Ti, S, lane);
             const int slot = valid ? tb.find(id) : -1;
             add_direct<FM, CM>(__ballot(valid && slot < 0), hit, P, rows, ri, id, gbuf, gs, lane);
 #pragma unroll
@@ -527,6 +563,7 @@ void k_walk(RawSurfels raw, TraceParams P, int64_t R, const float* __restrict__ 
         const bool busy = __syncthreads_or(at < n_hits || ahead != 0) != 0;
         const bool full = filled > Sh::flush;
         const bool refill = more && next >= left;
+        if (at < n_hits) mo = *reinterpret_cast<const float4*>(raw.pk + static_cast<int64_t>(id) * raw.ps);
         // This wave's components of every wave's hits, a ray's hits at a time
         // (rays share surfels).  With two components per wave all values are
         // loaded first, so that their latencies overlap; more do not fit the
@@ -659,7 +696,8 @@ void k_remarch(SceneView sc, RawSurfels raw, TraceParams P, const float* __restr
                 id = lists.hit_ids[me * kRemarchList + n - 1 - t];
                 Ti = lists.hit_T[me * kRemarchList + n - 1 - t];
             }
-            const WalkHit hit = walk_step<FM, CM>(raw, P, row, 0, valid, t == 0, id, Ti, S, lane);
+            const WalkHit hit = walk_step<FM, CM>(
+                raw, P, row, 0, valid, t == 0, id, *reinterpret_cast<const float4*>(raw.pk + static_cast<int64_t>(id) * raw.ps), Ti, S, lane);
             add_direct<FM, CM>(__ballot(valid), hit, P, row, 0, id, gbuf, gs, lane);
         }
     }

@@ -625,7 +625,8 @@ irgs_status irgs_trace_backward(irgs_scene s, const irgs_params* p, int64_t R, c
     const bool use_saved = !(p->flags & IRGS_FLAG_RECOMPUTE) && saved->hit_ids && saved->hit_T && saved->H_cap > 0;
     hipStream_t hs = static_cast<hipStream_t>(stream);
     const TraceParams tp = trace_params(p, s->F);
-    RawSurfels raw{s->p.mu, s->p.quat, s->p.scale, s->p.opacity, s->p.feat, nullptr, pack_stride(s->F), pack_features(s->F)};
+    RawSurfels raw{s->p.mu, s->p.quat, s->p.scale, s->p.opacity, s->p.feat, nullptr, pack_stride(s->F),
+                   pack_features(s->F), pack_recips(s->F)};
     GradIn g{gin->g_opacity, gin->g_feat, gin->g_depth};
     GradOut go{grads->mu, grads->quat, grads->scale, grads->opacity, grads->feat};
     // the parameters packed one row per surfel, read by every hit's gradient

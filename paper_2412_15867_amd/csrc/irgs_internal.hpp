@@ -82,15 +82,19 @@ struct RawSurfels {
     const float* opac;
     const float* feat;
     // The backward's copy of the same parameters, one row of `ps` floats per
-    // surfel id: (mu, o), q, (s_u, s_v, -, -), then the F features if they
+    // surfel id: (mu, o), q, (s_u, s_v, 1 / |q| in FP64), then the F features if they
     // fit one 128-byte line with these (F <= 20; a hit then reads that line
-    // instead of five scattered ones); wider features stay in `feat`.
+    // instead of five scattered ones); wider features stay in `feat`.  The
+    // row's last four words hold 1 / s_u and 1 / s_v in FP64 where no feature
+    // does (`recips`): an FP64 division or root per hit costs the walk over
+    // the hits more than a row's few words.
     const float* pk;
     int ps;
-    bool feat_packed;
+    bool feat_packed, recips;
 };
 
 inline bool pack_features(int F) { return F <= 20; }
+inline bool pack_recips(int F) { return F <= 16 || !pack_features(F); }
 // Floats per packed row.
 inline int pack_stride(int F) { return pack_features(F) ? 32 : 16; }
 // Fill pk (n rows of raw.ps floats) from the raw arrays.

@@ -370,7 +370,7 @@ __global__ void k_ray_keys(int64_t R, const float* __restrict__ ro, const float*
 
 // One packed row per surfel (see RawSurfels).  A thread writes 16 bytes of a
 // row, so that a wave writes whole lines.
-__global__ void k_pack(int64_t n, int F, int ps, bool feats, const float* __restrict__ mu,
+__global__ void k_pack(int64_t n, int F, int ps, bool feats, bool recips, const float* __restrict__ mu,
                        const float* __restrict__ quat, const float* __restrict__ scale, const float* __restrict__ opac,
                        const float* __restrict__ feat, float* __restrict__ pk)
 {
@@ -386,6 +386,14 @@ __global__ void k_pack(int64_t n, int F, int ps, bool feats, const float* __rest
         v = make_float4(quat[4 * i], quat[4 * i + 1], quat[4 * i + 2], quat[4 * i + 3]);
     } else if (c == 2) {
         v.x = scale[2 * i], v.y = scale[2 * i + 1];
+        const double w = quat[4 * i], x = quat[4 * i + 1], y = quat[4 * i + 2], z = quat[4 * i + 3];
+        const long long inv = __double_as_longlong(1.0 / sqrt(w * w + x * x + y * y + z * z));
+        v.z = __int_as_float(static_cast<int>(inv)), v.w = __int_as_float(static_cast<int>(inv >> 32));
+    } else if (recips && c == parts - 1) {
+        const long long u = __double_as_longlong(1.0 / double(scale[2 * i]));
+        const long long w = __double_as_longlong(1.0 / double(scale[2 * i + 1]));
+        v = make_float4(__int_as_float(static_cast<int>(u)), __int_as_float(static_cast<int>(u >> 32)),
+                        __int_as_float(static_cast<int>(w)), __int_as_float(static_cast<int>(w >> 32)));
     } else if (feats) {
         const int f0 = 4 * (c - 3);
         const float* f = feat + i * F;
@@ -512,7 +520,7 @@ hipError_t pack_surfels(const RawSurfels& raw, int64_t n, int F, float* pk, hipS
 {
     if (n <= 0) return hipSuccess;
     const int64_t t = n * (raw.ps / 4);
-    k_pack<<<static_cast<unsigned>((t + 255) / 256), 256, 0, st>>>(n, F, raw.ps, raw.feat_packed, raw.mu, raw.quat,
+    k_pack<<<static_cast<unsigned>((t + 255) / 256), 256, 0, st>>>(n, F, raw.ps, raw.feat_packed, raw.recips, raw.mu, raw.quat,
                                                                    raw.scale, raw.opac, raw.feat, pk);
     return hipGetLastError();
 }
