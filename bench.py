@@ -41,7 +41,7 @@ HBM_PEAK_GBS = 8000.0  # MI355X HBM3E, GB/s
 PROFILES = os.path.join(ROOT, "profiles")
 TRAFFIC_FILE = os.path.join(PROFILES, "k_trace_traffic_1M_surfels_4M_rays.md")
 CSRC = os.path.join(ROOT, "paper_2412_15867_amd", "csrc")
-FWD_SOURCES = ("trace_fwd.hip", "trace_flat.hpp", "march.hpp", "irgs_device.hpp", "irgs_internal.hpp", "lbvh.hip")
+FWD_SOURCES = ("trace_fwd.hip", "trace_flat.hpp", "trace_wave.hpp", "wave_ops.hpp", "march.hpp", "irgs_device.hpp", "irgs_internal.hpp", "lbvh.hip")
 
 
 def log(msg):
@@ -285,7 +285,7 @@ def run_c3(args):
     dom_ms = f_med if dom_is_fwd else b_med
     # without stored lists the backward call traces the rays again first
     dom_bytes = fb if dom_is_fwd else (bb + fb if args.recompute else bb)
-    bwd_name = "k_trace (retrace) + k_backward" if args.recompute else "k_backward"
+    bwd_name = "k_trace_wave (retrace) + k_walk" if args.recompute else "k_walk"
     achieved = dom_bytes / (dom_ms * 1e-3) / 1e9
     line = {
         "metric": "Mrays/s fwd+bwd @1M surfels (refit + forward + backward per step)" +
@@ -316,7 +316,7 @@ def run_c3(args):
         "build_ms": round(build_ms, 3),
         "hits_per_ray": round(H, 3),
         "bvh_depth": info["max_depth"],
-        "roofline": {"bound": "hbm", "kernel": "k_trace (forward)" if dom_is_fwd else bwd_name,
+        "roofline": {"bound": "hbm", "kernel": "k_trace_wave (forward)" if dom_is_fwd else bwd_name,
                      "achieved": round(achieved, 3), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBS, 5),
                      "traffic": measured_traffic() if dom_is_fwd and not sh else None,
@@ -385,7 +385,7 @@ def run_forward_only(args, small: bool):
             "hits_per_ray": round(float(n_hits.mean()), 3),
             "plain_gpu_bruteforce": {"mrays_s": round(n_brute / (bms * 1e-3) / 1e6, 3), "rays": n_brute,
                                      "ms": round(bms, 3), "bitwise_equal_to_bvh": same},
-            "roofline": {"bound": "hbm", "kernel": "k_trace (forward)", "achieved": round(ach, 3),
+            "roofline": {"bound": "hbm", "kernel": "k_trace_wave (forward)", "achieved": round(ach, 3),
                          "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBS, 5), "traffic": None}}
     if not args.no_cpu_baseline:
         import oracle
@@ -600,7 +600,7 @@ def run_pbr(args):
                                    "T_min=1e-4, store mode", "pixels": P, "rays": R},
             "refit_ms": round(med(0, 1), 3), "render_fwd_ms": round(fwd_ms, 3), "bwd_ms": round(med(2, 3), 3),
             "hits_per_ray": round(float(nh.mean()), 3),
-            "roofline": {"bound": "hbm", "kernel": "rays + k_trace + shading (forward)",
+            "roofline": {"bound": "hbm", "kernel": "rays + k_trace_wave + shading (forward)",
                          "achieved": round(fb / (fwd_ms * 1e-3) / 1e9, 3), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": round(fb / (fwd_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 5), "traffic": None}}
     scene.close()
@@ -686,7 +686,7 @@ def run_relight(args):
                        "pixels": P, "rays": R},
             "sky_precompute_ms": round(pre_ms, 3), "trace_ms": round(trace_ms, 3),
             "hits_per_ray": round(float(nh.mean()), 3),
-            "roofline": {"bound": "hbm", "kernel": "k_trace (normal blending)",
+            "roofline": {"bound": "hbm", "kernel": "k_trace_wave (normal blending)",
                          "achieved": round(fb / (trace_ms * 1e-3) / 1e9, 3), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                          "frac": round(fb / (trace_ms * 1e-3) / 1e9 / HBM_PEAK_GBS, 5), "traffic": None}}
     scene.close()

@@ -124,8 +124,8 @@ typedef struct {
  * traced side by side start near each other and share cached nodes and
  * surfels.  Outputs stay in the caller's order and every ray's result is
  * the same bit for bit; it pays when the scene's working set outgrows the
- * caches and the caller's rays are spatially incoherent (5M surfels, random
- * surface points: forward -11% at k = 64).  Extra scratch: 24 bytes per ray
+ * caches and the caller's rays are spatially incoherent (scenes of 5M surfels,
+ * random surface points).  Extra scratch: 24 bytes per ray
  * plus the sort's tile counts (irgs_trace_bytes).  Ignored by
  * irgs_trace_packed, by brute-force traces and by calls of more than
  * 2^31 - 1 rays (traced in the caller's order). */
@@ -234,8 +234,9 @@ irgs_status irgs_trace(irgs_scene scene, const irgs_params* params, int64_t R, c
 /* irgs_trace for callers that cannot allocate device memory: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
  * arguments, kernels and results (bit for bit) as irgs_trace, but the call
- * allocates nothing: its scratch (the ray-claim counter, each persistent
- * thread's traversal-stack overflow and deferred-work lists) lives in one
+ * allocates nothing: its scratch (the ray-claim counters and, where a launch runs
+ * one lane per ray, each persistent thread's traversal-stack overflow and
+ * deferred-work lists) lives in one
  * 64 MiB array inside the library's code object, one copy per device, held
  * until the process ends.  The launch fits its grid and deferred-list length
  * into that array (resident blocks are dropped only when even 32 entries per
@@ -259,7 +260,7 @@ irgs_status irgs_trace_noalloc(irgs_scene scene, const irgs_params* params, int6
  * re-marches its hits.  Without saved lists (or with IRGS_FLAG_RECOMPUTE)
  * the call traces the rays again, in equal batches whose hit lists (256 per
  * ray) fit a transient 4 GiB workspace, replays those lists and re-marches rays
- * with more hits; results are the same either way up to the order of the
+ * with more hits (by a wave each, up to 2,048 hits; by a lane past that); results are the same either way up to the order of the
  * gradient sums.  Parameters must not have changed since the forward
  * trace. */
 irgs_status irgs_trace_backward(irgs_scene scene, const irgs_params* params, int64_t R, const float* ro,

@@ -15,7 +15,8 @@
 //   4. Karras' hierarchy (longest common prefix of adjacent codes, index
 //      tie-break for equal codes);
 //   5. node boxes level by level from the deepest (nodes grouped by depth
-//      once per build; one launch per level, no atomics).
+//      once per build; no atomics; a launch per large level, one per run of
+//      small ones).
 // Refit repeats 1 (in the existing leaf order) and 5 with the topology kept.
 #include <hip/hip_runtime.h>
 

@@ -1,9 +1,10 @@
 // Forward 2D Gaussian ray tracing (Sec. 3.2, Eq. 2, 6-8) on gfx950.
 //
-// One lane traces one ray at a time: with the BVH, through the flat state
-// machine of trace_flat.hpp (rays claimed per wave from a counter); the
-// plain tracer strides a persistent grid over the rays.  Each k-buffer
-// round collects the K nearest hits after the resume key (by BVH traversal,
+// With the BVH a wave traces one ray at a time (trace_wave.hpp); launches that
+// ask for work counters, and trees too deep for the wave's stack, run one lane
+// per ray through the flat state machine of trace_flat.hpp; the plain tracer
+// strides a persistent grid over the rays, one lane each.  Each k-buffer round
+// of a lane collects the K nearest hits after the resume key (by BVH traversal,
 // or by testing every record in the plain tracer), then composites them
 // front to back in registers:
 //     w = T alpha;  O += w;  F += w f;  D += w tau;  T *= (1 - alpha)

@@ -56,10 +56,9 @@ def _req(t: torch.Tensor, name: str, shape, dtype=torch.float32, device=None) ->
 class TraceConfig:
     """Trace parameters (see irgs_params in include/irgs.h).  ``k`` (the
     k-buffer size of Sec. 3.2, the paper's 16) changes only the number of
-    marching rounds, never the result; on gfx950 k = 32 runs as fast or
-    faster on every workload measured, and k = 64 faster still for launches
-    bound by their slowest rays and for scenes past the caches (fewer rounds
-    outweigh the lower occupancy).  ``sort_rays`` hands rays to the traversal
+    marching rounds, never the result; with the BVH a wave holds a ray's
+    buffer of 128 hits whatever k is, so there k changes nothing but which
+    feature counts are taken.  ``sort_rays`` hands rays to the traversal
     in the Morton order of their origins (results unchanged bit for bit)."""
     k: int = 16
     T_min: float = DEFAULT_T_MIN
@@ -68,9 +67,8 @@ class TraceConfig:
     brute_force: bool = False
     recompute: bool = False      # backward: trace the rays again instead of storing hit lists
     # hits stored per ray for the backward (store mode, 8 bytes each); rays
-    # with more re-march in the backward, about ten times a forward per ray,
-    # so the capacity should cover nearly every ray (256 covers the 1M-surfel
-    # Monte Carlo workload: at 64 its backward takes 696 ms instead of 24.5)
+    # with more are traced again in the backward, so the capacity should cover
+    # most rays (256 covers the 1M-surfel Monte Carlo workload)
     hit_cap: int = 256
     sh: bool = False             # features are RGB SH coefficients (view-dependent colour, 3 channels)
     normals: bool = False        # 3 more channels, the ray-facing normal (relighting blend; differentiable)
@@ -271,7 +269,7 @@ def trace_backward(scene: Scene, ro, rd, saved: TraceResult, g_opacity=None, g_f
     when not given).  Rays whose hits fit `saved`'s stored lists replay them;
     with ``cfg.recompute`` (or no stored lists) the rays are traced again in
     batches within a transient 4 GiB workspace and replayed; rays longer than
-    the lists re-march, about ten times a forward per ray."""
+    the lists are traced again, a wave each."""
     cfg = cfg or TraceConfig(**kw)
     R = _rays(scene, ro, rd)
     if saved.n_hits is None:
