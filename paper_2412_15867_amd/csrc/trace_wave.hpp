@@ -23,11 +23,12 @@
 //
 // What bounds it: VALU issue (1M surfels, 4.2M rays: 2,740 VALU and 990 scalar
 // instructions per ray, a VALU instruction in every issue slot of 4 cycles; 68%
-// L2 hits, 9 KB per ray past L2).  Against one ray per lane, whose waves
+// L2 hits, 18.7 KB per ray past L2).  Against one ray per lane, whose waves
 // stepped through 1,230 dependent iterations with 45% of their lanes active:
 // 1M surfels, 4.2M rays 70.3 -> 34.4 ms; 200K surfels 36.6 -> 11.9 ms; launches
 // smaller than the chip, whose time is one ray's chain of round trips: 4,096
-// rays 580 -> 33 us, 2^18 rays 13.9 -> 5 ms.  Then, forward of 1M / 5M surfels:
+// rays 580 -> 33 us (19 without the scratch that such a launch does not use),
+// 2^18 rays 13.9 -> 5 ms.  Then, forward of 1M / 5M surfels:
 //   34.4 / 232 -> 25.3 / 128 ms: the children's slabs cull what only crosses
 //     the fat boxes of tilted patches (records tested per ray 1,206 -> 718);
 //   -> 23.6 / 127 ms: corner sums and extents in the nodes, the first step at a
