@@ -3,8 +3,10 @@
 // The hits of a group of rays form one stream, every ray's back to front, and
 // a wave takes 64 hits of it per step, whatever ray they belong to.  The suffix
 // composite S_i = alpha_i c_i + (1 - alpha_i) S_{i+1} is an affine map per hit,
-// so a step runs it as an inclusive scan of maps over the lanes (FP64); the map
-// of a ray's last hit ignores its input, which keeps the rays apart.
+// so a step runs it as an inclusive scan of maps over the lanes (FP64).  A
+// ray's last hit starts it anew: lanes whose range holds one take nothing from
+// the lanes before, by selection, so that what is not finite in one ray stays
+// out of the others (a map with the factor 0 would make NaN of it).
 //
 // Per-surfel sums are collected in a hash table in LDS shared by a block's
 // waves and written out when it fills: groups are taken in the order of where
@@ -259,23 +261,27 @@ __device__ __forceinline__ WalkHit walk_step(const RawSurfels& raw, const TraceP
             c += sN * (gN0 * n0 + gN1 * n1 + gN2 * n2);
         }
     }
-    // suffix composites: inclusive scan of the maps S -> A + B S over the lanes
-    double A = valid ? alpha * c : 0.0, B = valid ? (last ? 0.0 : 1.0 - alpha) : 1.0;
+    // suffix composites: inclusive scan of the maps S -> A + B S over the lanes.
+    // `closed`: the lanes whose range so far holds a ray's last hit; a step
+    // takes in a neighbouring range, then the masks its closed lanes.
+    double A = valid ? alpha * c : 0.0, B = valid ? 1.0 - alpha : 1.0;
     const double Sin = S;
-#define IRGS_AFFINE_STEP(ctrl, rows)                                                                      \
+    uint64_t closed = __ballot(last);
+#define IRGS_AFFINE_STEP(ctrl, rows, reach)                                                               \
     {                                                                                                     \
         const double Ap = dpp_f64<ctrl, rows>(0.0, A), Bp = dpp_f64<ctrl, rows>(1.0, B);                  \
-        A = fma(B, Ap, A);                                                                                \
-        B = B * Bp;                                                                                       \
+        A = __builtin_amdgcn_inverse_ballot_w64(closed) ? A : fma(B, Ap, A);                              \
+        B = B * Bp; /* of no use in a closed lane */                                                      \
+        closed |= reach;                                                                                  \
     }
-    IRGS_AFFINE_STEP(0x111, 0xf)
-    IRGS_AFFINE_STEP(0x112, 0xf)
-    IRGS_AFFINE_STEP(0x114, 0xf)
-    IRGS_AFFINE_STEP(0x118, 0xf)
-    IRGS_AFFINE_STEP(0x142, 0xa)
-    IRGS_AFFINE_STEP(0x143, 0xc)
+    IRGS_AFFINE_STEP(0x111, 0xf, (closed & 0x7fff7fff7fff7fffull) << 1)  // within rows of 16 lanes
+    IRGS_AFFINE_STEP(0x112, 0xf, (closed & 0x3fff3fff3fff3fffull) << 2)
+    IRGS_AFFINE_STEP(0x114, 0xf, (closed & 0x0fff0fff0fff0fffull) << 4)
+    IRGS_AFFINE_STEP(0x118, 0xf, (closed & 0x00ff00ff00ff00ffull) << 8)
+    IRGS_AFFINE_STEP(0x142, 0xa, (closed >> 15 & 0x0000000100000001ull) * 0xffff0000ull)  // lane 15 to row 1, 47 to 3
+    IRGS_AFFINE_STEP(0x143, 0xc, (closed >> 31 & 1ull) * 0xffffffff00000000ull)           // lane 31 to rows 2 and 3
 #undef IRGS_AFFINE_STEP
-    const double Sout = fma(B, Sin, A);
+    const double Sout = __builtin_amdgcn_inverse_ballot_w64(closed) ? A : fma(B, Sin, A);
     double Sn = dpp_f64<0x138, 0xf>(Sin, Sout);  // the suffix behind this hit: the lane before's
     Sn = last ? 0.0 : Sn;
     S = bcast(Sout, 63);

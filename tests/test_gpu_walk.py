@@ -80,3 +80,54 @@ def test_hits_past_the_wave_list():
     sc, ro, rd = stack(2600, 3, 0.006, 5)
     n = check(sc, ro, rd, TraceConfig(k=16, T_min=0.0), 256, full=2600)
     assert n.max() > 2048
+
+
+MODES = {"plain3": dict(F=3), "plain12": dict(F=12), "plain20": dict(F=20), "sh": dict(F=48, sh=True),
+         "normals": dict(F=5, normals=True)}
+
+
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+@pytest.mark.parametrize("R", [13_000, 20_000])
+@pytest.mark.parametrize("mode", list(MODES))
+def test_a_bad_upstream_stays_with_its_ray(mode, R, bad):
+    """A few rays with a non-finite upstream gradient among many (two or three
+    rays share a group, in the caller's order and in the landing order): every
+    surfel that none of them hits has the gradients of a run in which they have
+    no upstream at all.  Both runs add the same terms with FP32 atomics in
+    different orders, a few dozen per surfel."""
+    kw = dict(MODES[mode])
+    F = kw.pop("F")
+    sc = synth.surface_scene(20_000, F=F, seed=11)
+    if mode == "sh":
+        sc.feat[:] = synth.sh_coefficients(sc.n, 3)
+    ro, rd = (a[:R] for a in synth.mc_rays(-(-R // 16), 16, seed=12))
+    FO = 3 if mode == "sh" else F + 3 if mode == "normals" else F
+    gO, gF, gD, _ = synth.upstream(R, FO, seed=13)
+    s = make_scene(sc)
+    cfg = TraceConfig(k=16, **kw)
+    res = trace(s, dev(ro), dev(rd), cfg, hit_cap=256)
+    n = res.n_hits.cpu().numpy()
+    assert n.max() <= 256
+    who = np.flatnonzero(n > 4)[::400]
+    spoilt = np.unique(np.concatenate([res.hit_ids[int(r), :n[r]].cpu().numpy() for r in who]))
+    clean = np.setdiff1d(np.arange(sc.n), spoilt)
+    grads = []
+    for value in (0.0, bad):
+        for g in (gO, gF, gD):
+            g[who] = 0.0
+        for i, r in enumerate(who):
+            if i % 3 == 0:
+                gO[r] = value
+            elif i % 3 == 1:
+                gF[r, -1] = value
+            else:
+                gD[r] = value
+        got = trace_backward(s, dev(ro), dev(rd), res, dev(gO), dev(gF), dev(gD), cfg=cfg)
+        grads.append({a: got[a].cpu().numpy().reshape(sc.n, -1) for a, _ in KEYS})
+    s.close()
+    want, got = grads
+    assert not np.all(np.isfinite(got["mu"][spoilt]))
+    for a, _ in KEYS:
+        w, g = want[a][clean], got[a][clean]
+        assert np.all(np.isfinite(g)), (a, np.flatnonzero(~np.isfinite(g).all(1)).size)
+        np.testing.assert_allclose(g, w, rtol=1e-4, atol=1e-5 * np.abs(want[a]).max(), err_msg=a)
