@@ -246,7 +246,11 @@ struct WavePlain {
 };
 
 // Several requests over several scenes: a slot indexes the concatenation of
-// the items' rays; the lanes look for the owning item 64 items at a time.
+// the items' rays.  The lanes look for the owning item, the last one whose
+// first slot is not past it, in 64ths of the range left: one dependent read
+// up to 64 items, three up to 262,144 (a scan from the first item, 64 at a
+// time, read 60 KB of items per ray with 1,000 of them: 2.1M rays in 1,000 /
+// 10,000 items 9.3 / 39.5 ms, this 7.6 / 7.7; one item 6.6).
 struct WavePacked {
     const SceneView* scenes;
     const WorkItem* items;
@@ -256,12 +260,14 @@ struct WavePacked {
     __device__ __forceinline__ int64_t total() const { return n_rays; }
     __device__ __forceinline__ int64_t locate(int64_t slot, int lane, int* item) const
     {
-        int it = -1;
-        for (int b = 0; b < n_items; b += 64) {
-            const bool before = b + lane < n_items && items[b + lane].chunk_begin <= slot;
-            const int c = __popcll(__ballot(before));  // first slots ascend: the items at or before it lead
-            it += c;
-            if (c < 64) break;
+        int it = 0, n = n_items;  // the item is one of the n from `it` on
+        while (n > 1) {
+            const int step = (n + 63) >> 6;
+            const int at = lane * step;
+            const bool before = at < n && items[it + at].chunk_begin <= slot;
+            const int skip = (__popcll(__ballot(before)) - 1) * step;  // first slots ascend; the first item's is not past it
+            it += skip;
+            n = min(step, n - skip);
         }
         *item = it;
         return items[it].ray_begin + (slot - items[it].chunk_begin);

@@ -137,3 +137,24 @@ def test_sorted_launch_sizes(R):
     ro = torch.rand(R, 3, generator=g, device="cuda") * 4 - 2
     rd = -ro / ro.norm(dim=1, keepdim=True)
     same(trace(s, ro, rd, TraceConfig(k=16, sort_rays=True)), trace(s, ro, rd, TraceConfig(k=16)))
+
+
+@pytest.mark.parametrize("items", [1000, 4096, 4097])
+def test_packed_many_items(items):
+    """As many items as take one, two and three looks of 64 to find a ray's own,
+    some of them without rays."""
+    scenes = [make_scene(synth.surface_scene(n, F=4, seed=n)) for n in (700, 2500)]
+    cfg = TraceConfig(k=16)
+    ro, rd = (torch.from_numpy(a).cuda() for a in synth.mc_rays(6000, 3, seed=items))
+    g = np.random.Generator(np.random.PCG64(items))
+    count = g.integers(0, 4, items)
+    end = np.cumsum(count)
+    reqs = [(i % 2, ro[e - c:e], rd[e - c:e], alloc_result(int(c), 4, ro.device))
+            for i, (c, e) in enumerate(zip(count, end))]
+    trace_packed(scenes, reqs, cfg)
+    for s in range(2):
+        ref = trace(scenes[s], ro, rd, cfg)
+        rays = torch.from_numpy(np.concatenate([np.arange(e - c, e) for c, e in zip(count[s::2], end[s::2])])).cuda()
+        for name in ("opacity", "feat", "depth", "T", "n_hits"):
+            got = torch.cat([getattr(r[3], name) for r in reqs[s::2]])
+            assert torch.equal(got, getattr(ref, name)[rays]), name
