@@ -33,7 +33,7 @@ struct BuildArgs {
     int2* brange;           // per binary node: first leaf, leaf count
     WideNode* wnodes;       // up to max(N - 1, 1) wide nodes
     int4* wsrc;             // per wide node and slot: (binary parent << 1 | side), -1 = empty
-    int* wscratch;          // 3 * max(N - 1, 1) + 4 ints: collapse sources and level sizes
+    int* wscratch;          // 3 * max(N - 1, 1) + 4 ints: collapse sources, level sizes and firsts
     int leaf_size;          // surfels per cluster leaf (1..16)
     bool ploc;              // binary tree by PLOC (else the Morton radix tree)
     int n_wide;             // out (host): wide nodes built; also the refit input
@@ -42,7 +42,7 @@ struct BuildArgs {
 };
 
 hipError_t lbvh_sort_scratch_bytes(int n, size_t* bytes);
-// Build: synchronises `st` (the wide collapse reads each level's size back).
+// Build: synchronises `st` (the clusters left and the levels' sizes are read back).
 hipError_t lbvh_build(BuildArgs& a, void* scratch, hipStream_t st);
 hipError_t lbvh_refit(const BuildArgs& a, hipStream_t st);
 // The bounds of each leaf cluster's remaining records (k_cluster_slabs), which
