@@ -656,27 +656,33 @@ void k_walk(RawSurfels raw, TraceParams P, int64_t R, const float* __restrict__ 
     tb.write(tid, threads, nc, gbuf, gs);
 }
 
-// Rays whose stored list was cut: each is traced again by one wave into the
-// wave's own list of kRemarchList hits, which the wave then walks (no table:
-// they are few).  A ray with more hits is left to `rest`.
-template <int FM, int CM>
+// Rays of rm_list (their stored list was cut), each traced again by one wave
+// into a list of List hits in LDS, which the wave then walks (no table: they
+// are few).  A ray with more hits is left to `rest`.
+template <int FM, int CM, int List>
 __global__ __launch_bounds__(kWaveBlock)
 void k_remarch(SceneView sc, RawSurfels raw, TraceParams P, const float* __restrict__ ro, const float* __restrict__ rd,
-               GradIn gin, float* gbuf, int gs, OutPtrs lists, int reserve, const int* __restrict__ rm_list,
+               GradIn gin, float* gbuf, int gs, int reserve, const int* __restrict__ rm_list,
                const unsigned long long* rm_count, unsigned long long* next, int* rest, unsigned long long* rest_count)
 {
     using Row = WalkRow<FM, CM>;
     __shared__ uint32_t lds[kWaveLdsWords];
+    __shared__ int list_ids[List];
+    __shared__ float list_T[List];
     __shared__ float row_mem[Row::words];
     lds_f32* row = (lds_f32*)row_mem;
     const int lane = threadIdx.x;
     const int64_t count = static_cast<int64_t>(*rm_count);
-    const int64_t me = blockIdx.x;
-    while (true) {
-        unsigned long long b = 0;
-        if (lane == 0) b = atomicAdd(next, 1ull);
-        const int64_t i = static_cast<int64_t>(bcast(static_cast<uint64_t>(b), 0));
-        if (i >= count) return;
+    OutPtrs out{};  // the composite goes where the traversal's areas are, idle by then
+    out.O = reinterpret_cast<float*>(lds);
+    out.D = out.O + 1;
+    out.feat = out.O + 2;
+    out.hit_ids = list_ids;
+    out.hit_T = list_T;
+    out.H_cap = List;
+    // the first ray by the block's number, the others by claims: a launch
+    // that has nothing to do touches no counter
+    for (int64_t i = blockIdx.x; i < count;) {
         const int64_t r = bcast(rm_list[i], 0);
         const Ray v = load_ray(ro, rd, r);
         Ray ray;
@@ -684,28 +690,31 @@ void k_remarch(SceneView sc, RawSurfels raw, TraceParams P, const float* __restr
         ray.dx = bcast(v.dx, 0), ray.dy = bcast(v.dy, 0), ray.dz = bcast(v.dz, 0);
         WalkInput<FM, CM> in;
         in.load(P, ro, rd, gin, r);
-        if (!in.work(P, gin, r)) continue;  // the same in every lane
-        in.store(row, P, gin, r);
-        const int n = trace_ray_wave<CM>(sc, P, ray, me, lists, (lds_u32*)lds, reserve, lane);
-        if (n > kRemarchList) {
-            if (lane == 0) rest[atomicAdd(rest_count, 1ull)] = static_cast<int>(r);
-            continue;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");  // the list is read by other lanes than wrote it
-        double S = 0.0;
-        for (int at = 0; at < n; at += 64) {
-            const int t = at + lane;
-            const bool valid = t < n;
-            int id = 0;
-            float Ti = 0.0f;
-            if (valid) {
-                id = lists.hit_ids[me * kRemarchList + n - 1 - t];
-                Ti = lists.hit_T[me * kRemarchList + n - 1 - t];
+        if (in.work(P, gin, r)) {  // the same in every lane
+            in.store(row, P, gin, r);
+            const int n = trace_ray_wave<CM>(sc, P, ray, 0, out, (lds_u32*)lds, reserve, lane);
+            // the list is read by other lanes than wrote it
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");
+            lds_order();
+            if (n > List) {
+                if (lane == 0) rest[atomicAdd(rest_count, 1ull)] = static_cast<int>(r);
+            } else {
+                double S = 0.0;
+                for (int at = 0; at < n; at += 64) {
+                    const int t = at + lane;
+                    const bool valid = t < n;
+                    const int id = valid ? list_ids[n - 1 - t] : 0;
+                    const float Ti = valid ? list_T[n - 1 - t] : 0.0f;
+                    const float4 mo = *reinterpret_cast<const float4*>(raw.pk + static_cast<int64_t>(id) * raw.ps);
+                    const WalkHit hit = walk_step<FM, CM>(raw, P, row, 0, valid, t == 0, id, mo, Ti, S, lane);
+                    add_direct<FM, CM>(__ballot(valid), hit, P, row, 0, id, gbuf, gs, lane);
+                }
             }
-            const WalkHit hit = walk_step<FM, CM>(
-                raw, P, row, 0, valid, t == 0, id, *reinterpret_cast<const float4*>(raw.pk + static_cast<int64_t>(id) * raw.ps), Ti, S, lane);
-            add_direct<FM, CM>(__ballot(valid), hit, P, row, 0, id, gbuf, gs, lane);
+            lds_order();
         }
+        unsigned long long b = 0;
+        if (lane == 0) b = atomicAdd(next, 1ull);
+        i = static_cast<int64_t>(gridDim.x) + static_cast<int64_t>(bcast(static_cast<uint64_t>(b), 0));
     }
 }
 

@@ -454,7 +454,8 @@ size_t irgs_trace_bytes(int64_t R, int32_t F, uint32_t flags)
         const size_t per_ray = static_cast<size_t>(kRetraceCap) * 8 + (3 + fo) * sizeof(float);
         const int64_t bmax = std::max<int64_t>(1, static_cast<int64_t>(kRetraceBytes / per_ray));
         const int64_t nb = (R + bmax - 1) / bmax;
-        b += static_cast<size_t>((R + nb - 1) / nb) * per_ray + plan_backward((R + nb - 1) / nb, 0, F, 64).bytes;
+        b += static_cast<size_t>((R + nb - 1) / nb) * per_ray +
+             plan_backward((R + nb - 1) / nb, kRemarchList + 1, F, 64, kRetraceCap).bytes;
     }
     return b;  // plus, for a backward, 4 * (ceil32(10 + F) + ceil32(12 + F)) bytes per surfel
 }
@@ -634,7 +635,7 @@ irgs_status irgs_trace_backward(irgs_scene s, const irgs_params* p, int64_t R, c
     AsyncBuf mem;  // one allocation: each costs the host 30 to 80 us to make and to give back
     if (use_saved) {
         const size_t ck = aligned(pk_bytes);
-        hipError_t e = mem.alloc(ck + plan_backward(R, s->n, s->F, s->wide_depth).bytes, hs);
+        hipError_t e = mem.alloc(ck + plan_backward(R, s->n, s->F, s->wide_depth, saved->H_cap).bytes, hs);
         if (e != hipSuccess) return hip_fail(e, "backward scratch");
         e = pack_surfels(raw, s->n, s->F, static_cast<float*>(mem.p), hs);
         if (e != hipSuccess) return hip_fail(e, "backward parameter pack");
@@ -668,7 +669,7 @@ irgs_status irgs_trace_backward(irgs_scene s, const irgs_params* p, int64_t R, c
     const size_t ovf = place(lane_thr * slots * sizeof(int));
     const size_t dq = place(bvh ? kClaimBytes + lane_thr * 2 * kDeferCap * sizeof(int) : 0);
     const size_t srt = place(sorted ? ray_sort_words(B) * sizeof(float) : 0);
-    const size_t ck = place(plan_backward(B, s->n, s->F, s->wide_depth).bytes);
+    const size_t ck = place(plan_backward(B, s->n, s->F, s->wide_depth, kRetraceCap).bytes);
     const size_t lists = place(static_cast<size_t>(B) * per_ray);
     hipError_t e = mem.alloc(total, hs);
     if (e == hipSuccess && lane_thr > 0) e = need_cluster_bounds(s, hs);

@@ -188,22 +188,32 @@ hipError_t launch_trace(const SceneView& sc, const TraceParams& P, int k, bool u
 bool features_offered(int k, int F, bool special);
 
 // Backward over saved hit lists (ids and T).  Rays with n_hits > H_cap are
-// traced again: by at most kRemarchWaves waves with lists of kRemarchList hits
-// and, with more hits (or a tree too deep for the wave form), by at most
-// kRemarchLanes lanes.
+// traced again by a wave each, into a list in its LDS that the wave walks: a
+// launch whose lists hold kRemarchShort hits, of which a CU keeps 12, and one
+// for what it leaves with lists of kRemarchList hits, of which it keeps 8.
+// Launches of at most kRemarchSmall rays take the second alone: there all lists
+// can be cut, and twice the launches cost more than the waves.  Rays with more
+// hits (and all, of a tree too deep for the wave form) go to at most
+// kRemarchLanes lanes.  Against lists in global memory and a wave per 64 rays to
+// keep them small, all lists cut: 64 / 4,000 rays of 1,500 hits 49.5 / 49.7 ->
+// 0.9 / 1.9 ms, 1M rays of 44 hits 13.9 -> 13.8 ms (18.0 with the long lists
+// alone); none cut, 262,144 rays: 1.29 -> 1.00 ms (68 MB less to allocate).
 constexpr int kBwdCheckpoints = 16;
+constexpr int kRemarchShort = 1024;
 constexpr int kRemarchList = 2048;
-constexpr int64_t kRemarchWaves = 4096;
+constexpr int64_t kRemarchSmall = 32768;
+constexpr int64_t kRemarchWaves = 4096;  // of a launch at most
 constexpr int64_t kRemarchLanes = 16384;
 // Rays from which on the walk takes them in the order of where they land.
 constexpr int64_t kSortWalkRays = 16384;
 // Byte offsets in the backward's scratch: the interleaved per-surfel
 // accumulator, then these.
 struct BackwardPlan {
-    size_t claims, rm_list, rest, sort, lists, stacks, checkpoints, bytes;
-    int64_t waves, lane_blocks;  // that re-march
+    size_t claims, rm_list, rest, sort, stacks, checkpoints, bytes;
+    bool short_lists, long_lists;  // wave launches over the cut lists
+    int64_t lane_blocks;           // lanes' blocks of a launch over what is left (none: 0)
 };
-BackwardPlan plan_backward(int64_t R, int64_t N, int F, int wide_depth);
+BackwardPlan plan_backward(int64_t R, int64_t N, int F, int wide_depth, int H_cap);
 inline int grad_stride(int F) { return ((10 + F + 31) / 32) * 32; }
 size_t sort_pairs_count_bytes(int n);
 hipError_t sort_pairs(int n, uint64_t* k0, uint32_t* v0, uint64_t* k1, uint32_t* v1, uint32_t* counts, int passes,

@@ -21,6 +21,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <utility>
 
 #include "irgs_internal.hpp"
 #include "bwd_wave.hpp"
@@ -450,12 +451,11 @@ hipError_t launch_f(const SceneView& sc, const RawSurfels& raw, const TraceParam
                     char* scratch, hipStream_t st)
 {
     using Sh = WalkShape<FM>;
-    const BackwardPlan pl = plan_backward(R, sc.n, P.F, wide_depth);
+    const BackwardPlan pl = plan_backward(R, sc.n, P.F, wide_depth, saved.H_cap);
     const int gs = grad_stride(P.F);
     float* gbuf = reinterpret_cast<float*>(scratch);
+    // a claim counter for the walk, then a count and a claim counter per re-march
     unsigned long long* claims = reinterpret_cast<unsigned long long*>(scratch + pl.claims);
-    unsigned long long *next_chunk = claims, *rm_count = claims + 1, *next_rm = claims + 2, *rest_count = claims + 3,
-                       *next_rest = claims + 4;
     int* rm_list = reinterpret_cast<int*>(scratch + pl.rm_list);
     int* rest = reinterpret_cast<int*>(scratch + pl.rest);
     // zero the accumulator and the claim counters behind it
@@ -476,38 +476,32 @@ hipError_t launch_f(const SceneView& sc, const RawSurfels& raw, const TraceParam
         const int groups = group == Sh::group ? 2 * Sh::waves : Sh::waves;
         const int64_t chunks = (R + group * groups - 1) / (group * groups);
         k_walk<FM, CM><<<persistent_grid(chunks, resident), Sh::waves * 64, 0, st>>>(
-            raw, P, R, ro, rd, saved, gin, gbuf, gs, next_chunk, order, static_cast<int>(group), groups, rm_list, rm_count);
+            raw, P, R, ro, rd, saved, gin, gbuf, gs, claims, order, static_cast<int>(group), groups, rm_list, claims + 1);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (sc.n > saved.H_cap) {  // a list can have been cut
-        const bool wave = wave_stack_fits(wide_depth);
-        if (wave) {
-            OutPtrs lists{};
-            lists.hit_ids = reinterpret_cast<int32_t*>(scratch + pl.lists);
-            lists.hit_T = reinterpret_cast<float*>(lists.hit_ids + pl.waves * kRemarchList);
-            lists.O = lists.hit_T + pl.waves * kRemarchList;
-            lists.D = lists.O + pl.waves;
-            lists.feat = lists.D + pl.waves;
-            lists.H_cap = kRemarchList;
-            const unsigned grid = persistent_grid(pl.waves, resident_blocks(k_remarch<FM, CM>, kWaveBlock));
-            k_remarch<FM, CM><<<grid, kWaveBlock, 0, st>>>(sc, raw, P, ro, rd, gin, gbuf, gs, lists,
-                                                           wave_stack_reserve(wide_depth), rm_list, rm_count, next_rm,
-                                                           rest, rest_count);
-            e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
-        if (!wave || sc.n > kRemarchList) {
-            constexpr int FU = CM == kColSH ? 4 : FM;
-            k_remarch_lanes<kMarchK, FM, FU, CM == kColSH, CM == kColNormal>
-                <<<static_cast<unsigned>(pl.lane_blocks), kBwdBlock, 0, st>>>(
-                    sc, raw, P, ro, rd, gin, gbuf, gs, reinterpret_cast<int*>(scratch + pl.stacks),
-                    reinterpret_cast<float4*>(scratch + pl.checkpoints), wave ? rest : rm_list,
-                    wave ? rest_count : rm_count, next_rest);
-            e = hipGetLastError();
-            if (e != hipSuccess) return e;
-        }
+    // the cut lists, then what each launch leaves to the next
+    int *todo = rm_list, *left = rest;
+    unsigned long long *count = claims + 1, *next = claims + 2;
+    auto wave_launch = [&](auto kern) {
+        const unsigned grid = persistent_grid(std::min(R, kRemarchWaves), resident_blocks(kern, kWaveBlock));
+        kern<<<grid, kWaveBlock, 0, st>>>(sc, raw, P, ro, rd, gin, gbuf, gs, wave_stack_reserve(wide_depth), todo, count,
+                                          next, left, count + 2);
+        std::swap(todo, left);
+        count += 2, next += 2;
+        return hipGetLastError();
+    };
+    if (pl.short_lists) e = wave_launch(k_remarch<FM, CM, kRemarchShort>);
+    if (e == hipSuccess && pl.long_lists) e = wave_launch(k_remarch<FM, CM, kRemarchList>);
+    if (e == hipSuccess && pl.lane_blocks > 0) {
+        constexpr int FU = CM == kColSH ? 4 : FM;
+        k_remarch_lanes<kMarchK, FM, FU, CM == kColSH, CM == kColNormal>
+            <<<static_cast<unsigned>(pl.lane_blocks), kBwdBlock, 0, st>>>(
+                sc, raw, P, ro, rd, gin, gbuf, gs, reinterpret_cast<int*>(scratch + pl.stacks),
+                reinterpret_cast<float4*>(scratch + pl.checkpoints), todo, count, next);
+        e = hipGetLastError();
     }
+    if (e != hipSuccess) return e;
     const int64_t work = static_cast<int64_t>(sc.n) * (10 + P.F);
     const int blocks = static_cast<int>(work < 2048 * 256 ? (work + 255) / 256 : 2048);
     k_grad_out<<<blocks > 0 ? blocks : 1, 256, 0, st>>>(sc.n, P.F, gs, gbuf, go);
@@ -525,7 +519,7 @@ hipError_t pack_surfels(const RawSurfels& raw, int64_t n, int F, float* pk, hipS
     return hipGetLastError();
 }
 
-BackwardPlan plan_backward(int64_t R, int64_t N, int F, int wide_depth)
+BackwardPlan plan_backward(int64_t R, int64_t N, int F, int wide_depth, int H_cap)
 {
     BackwardPlan pl{};
     size_t at = 0;
@@ -539,14 +533,17 @@ BackwardPlan plan_backward(int64_t R, int64_t N, int F, int wide_depth)
     pl.rm_list = take(static_cast<size_t>(R) * sizeof(int));
     pl.rest = take(static_cast<size_t>(R) * sizeof(int));
     pl.sort = take(R >= kSortWalkRays ? ray_sort_words(R) * sizeof(float) : 0);
-    // (few rays are cut: a wave per 64 rays of the launch is plenty)
-    pl.waves = std::min<int64_t>((R + 63) / 64, kRemarchWaves);
-    const int64_t blocks = (R + kBwdBlock - 1) / kBwdBlock;
-    pl.lane_blocks = blocks < kRemarchLanes / kBwdBlock ? blocks : kRemarchLanes / kBwdBlock;
-    const size_t lanes = static_cast<size_t>(pl.lane_blocks) * kBwdBlock;
-    pl.lists = take(static_cast<size_t>(pl.waves) * (2 * kRemarchList + 2 + kMaxF + 3) * sizeof(float));
-    pl.stacks = take(lanes * (3 * wide_depth + 1) * sizeof(int));
-    pl.checkpoints = take(lanes * kBwdCheckpoints * sizeof(float4));
+    const bool cut = N > H_cap;  // a list can have been cut
+    const bool wave = wave_stack_fits(wide_depth);
+    pl.short_lists = cut && wave && R > kRemarchSmall;
+    pl.long_lists = cut && wave && !(pl.short_lists && N <= kRemarchShort);
+    if (cut && (!wave || N > kRemarchList)) {
+        const int64_t blocks = (R + kBwdBlock - 1) / kBwdBlock;
+        pl.lane_blocks = blocks < kRemarchLanes / kBwdBlock ? blocks : kRemarchLanes / kBwdBlock;
+        const size_t lanes = static_cast<size_t>(pl.lane_blocks) * kBwdBlock;
+        pl.stacks = take(lanes * (3 * wide_depth + 1) * sizeof(int));
+        pl.checkpoints = take(lanes * kBwdCheckpoints * sizeof(float4));
+    }
     pl.bytes = at;
     return pl;
 }

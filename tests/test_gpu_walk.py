@@ -131,3 +131,48 @@ def test_a_bad_upstream_stays_with_its_ray(mode, R, bad):
         w, g = want[a][clean], got[a][clean]
         assert np.all(np.isfinite(g)), (a, np.flatnonzero(~np.isfinite(g).all(1)).size)
         np.testing.assert_allclose(g, w, rtol=1e-4, atol=1e-5 * np.abs(want[a]).max(), err_msg=a)
+
+
+def scene_of(sc, mode, **kw):
+    """`sc` with the features of a mode, its config and what the oracle takes."""
+    F = MODES[mode]["F"]
+    g = np.random.Generator(np.random.PCG64(21))
+    feat = synth.sh_coefficients(sc.n, 3) if mode == "sh" else g.uniform(0, 1, (sc.n, F)).astype(np.float32)
+    sc = synth.Surfels(sc.mu, sc.quat, sc.scale, sc.opac, feat)
+    cfg = TraceConfig(k=16, T_min=0.0, **{k: v for k, v in MODES[mode].items() if k != "F"})
+    oracle = dict(sh_deg=3) if mode == "sh" else dict(with_normal=True) if mode == "normals" else {}
+    return sc, make_scene(sc, **kw), cfg, oracle
+
+
+def check_cut(sc, s, ro, rd, cfg, oracle, busy, cap, full):
+    """Gradients with lists cut at `cap` against the oracle over the whole lists
+    of the first `busy` rays, the only ones with an upstream."""
+    R, FO = ro.shape[0], cfg.out_channels(sc.F)
+    gO, gF, gD, _ = synth.upstream(R, FO, seed=3)
+    gO[busy:], gF[busy:], gD[busy:] = 0, 0, 0
+    whole = trace(s, dev(ro[:busy]), dev(rd[:busy]), cfg, hit_cap=full)
+    res = trace(s, dev(ro), dev(rd), cfg, hit_cap=cap)
+    got = trace_backward(s, dev(ro), dev(rd), res, dev(gO), dev(gF), dev(gD), cfg=cfg)
+    n = whole.n_hits.cpu().numpy()
+    assert cap < n.max() <= full
+    ids = np.where(np.arange(full)[None] < n[:, None], whole.hit_ids.cpu().numpy(), -1)[:, :int(n.max())]
+    want = ograd.grad_given_hits(sc.astuple(), ro[:busy], rd[:busy], ids, gO[:busy], gF[:busy], gD[:busy], **oracle)
+    for a, b in KEYS:
+        g, w = got[a].cpu().numpy().reshape(want[b].shape), want[b]
+        assert np.all(np.abs(g - w) <= 1e-3 * (np.abs(w) + np.abs(w).mean() + 1e-12)), a
+    return n
+
+
+@pytest.mark.parametrize("R", [30, 33_000])
+@pytest.mark.parametrize("n", [1000, 1500, 2600])
+@pytest.mark.parametrize("mode", list(MODES))
+def test_cut_lists_of_every_length(mode, n, R):
+    """Hits around the list lengths of the wave re-marches (1,024 and 2,048) and
+    past them, in a launch that takes the longer lists at once and in one that
+    takes the shorter first; plain, SH and normal channels."""
+    base, ro, rd = stack(n, 1, 0.006, R)
+    rd[30:] *= -1  # away from the stack
+    sc, s, cfg, oracle = scene_of(base, mode)
+    hits = check_cut(sc, s, ro, rd, cfg, oracle, 30, 64, n)
+    s.close()
+    assert hits.max() > 0.8 * n
