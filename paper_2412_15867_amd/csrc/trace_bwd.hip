@@ -230,15 +230,17 @@ __device__ __forceinline__ LaneUp<FU> load_upstream(const GradIn& gin, int64_t r
 }
 
 // Re-march one ray.  Pass 1 marches the k-buffer rounds again (the forward's
-// arithmetic, so T is reproduced bit for bit), recording the state at the
-// start of rounds as checkpoints.  Pass 2 re-collects the rounds last to first
-// from the nearest checkpoint.  Checkpoints are kept for every stride-th round:
+// arithmetic, so T is reproduced bit for bit), recording the hits (id and T) in
+// the lane's list of `cap` while it holds them and the state at the start of
+// rounds as checkpoints.  Pass 2 walks the list back to front or, for a ray
+// with more hits, re-collects the rounds last to first from the nearest
+// checkpoint.  Checkpoints are kept for every stride-th round:
 // once all kBwdCheckpoints are taken every other one is dropped and the stride
 // doubles, so pass 2 re-collects at most stride - 1 extra rounds per round.
 template <int K, int FM, int FU, bool SH, bool NRM, class Acc>
 __device__ __forceinline__ void bwd_remarch(const SceneView& sc, const RawSurfels& raw, const TraceParams& P,
                                             const Ray& ray, const LaneUp<FU>& up, const Acc& acc, Stack& st,
-                                            float4* ck, int64_t ck_stride)
+                                            float4* ck, int64_t ck_stride, int* list_ids, float* list_T, int cap)
 {
     float S = 0.0f;
     Counters ct;
@@ -268,6 +270,10 @@ __device__ __forceinline__ void bwd_remarch(const SceneView& sc, const RawSurfel
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             if (j < kb.cnt && !done) {
+                if (nh < cap) {
+                    list_ids[nh] = __float_as_int(sc.rec[kb.pos(j)].c.w);
+                    list_T[nh] = T;
+                }
                 T = T * (1.0f - entry_alpha(sc, ray, kb.pos(j)));
                 ++nh;
                 if (T < P.T_min) done = true;
@@ -280,6 +286,14 @@ __device__ __forceinline__ void bwd_remarch(const SceneView& sc, const RawSurfel
         ++rounds;
     }
     const int total = nh;
+    if (total <= cap) {
+        for (int i = total - 1; i >= 0; --i) {
+            HitGrad<FM> h;
+            grad_hit<FM, FU, SH, NRM>(raw, P, list_ids[i], ray, list_T[i], S, up.gO, up.gF, up.gD, h);
+            acc.template direct<FM>(list_ids[i], h);
+        }
+        return;
+    }
     for (int rr = rounds - 1; rr >= 0; --rr) {
         const int base = rr / stride;
         float4 c4 = ck[base * ck_stride];
@@ -321,7 +335,7 @@ template <int K, int FM, int FU, bool SH, bool NRM>
 __global__ __launch_bounds__(kBwdBlock) void k_remarch_lanes(SceneView sc, RawSurfels raw, TraceParams P,
                                                              const float* __restrict__ ro, const float* __restrict__ rd,
                                                              GradIn gin, float* gbuf, int gs, int* ovf, float4* ck,
-                                                             const int* __restrict__ list,
+                                                             int* lists, int cap, const int* __restrict__ list,
                                                              const unsigned long long* list_count,
                                                              unsigned long long* next)
 {
@@ -331,6 +345,8 @@ __global__ __launch_bounds__(kBwdBlock) void k_remarch_lanes(SceneView sc, RawSu
     // the stack lives entirely in the global area (0 LDS slots)
     Stack st{nullptr, as_glb(ovf + gtid), static_cast<int>(nthr), tid, 0, 0};
     const GradAcc acc{gbuf, gs, P.F};
+    int* my_ids = lists + gtid * 2 * cap;
+    float* my_T = reinterpret_cast<float*>(my_ids + cap);
     const int64_t count = static_cast<int64_t>(*list_count);
     while (true) {
         unsigned long long c = 0;
@@ -341,7 +357,8 @@ __global__ __launch_bounds__(kBwdBlock) void k_remarch_lanes(SceneView sc, RawSu
             const int64_t r = list[base + tid];
             const Ray ray = load_ray(ro, rd, r);
             const LaneUp<FU> up = load_upstream<FU>(gin, r, SH ? 3 : (NRM ? P.F + 3 : P.F));
-            if (up.any && ray_valid(ray)) bwd_remarch<K, FM, FU, SH, NRM>(sc, raw, P, ray, up, acc, st, ck + gtid, nthr);
+            if (up.any && ray_valid(ray))
+                bwd_remarch<K, FM, FU, SH, NRM>(sc, raw, P, ray, up, acc, st, ck + gtid, nthr, my_ids, my_T, cap);
         }
     }
 }
@@ -498,7 +515,8 @@ hipError_t launch_f(const SceneView& sc, const RawSurfels& raw, const TraceParam
         k_remarch_lanes<kMarchK, FM, FU, CM == kColSH, CM == kColNormal>
             <<<static_cast<unsigned>(pl.lane_blocks), kBwdBlock, 0, st>>>(
                 sc, raw, P, ro, rd, gin, gbuf, gs, reinterpret_cast<int*>(scratch + pl.stacks),
-                reinterpret_cast<float4*>(scratch + pl.checkpoints), todo, count, next);
+                reinterpret_cast<float4*>(scratch + pl.checkpoints), reinterpret_cast<int*>(scratch + pl.lists),
+                pl.lane_list, todo, count, next);
         e = hipGetLastError();
     }
     if (e != hipSuccess) return e;
@@ -538,11 +556,13 @@ BackwardPlan plan_backward(int64_t R, int64_t N, int F, int wide_depth, int H_ca
     pl.short_lists = cut && wave && R > kRemarchSmall;
     pl.long_lists = cut && wave && !(pl.short_lists && N <= kRemarchShort);
     if (cut && (!wave || N > kRemarchList)) {
-        const int64_t blocks = (R + kBwdBlock - 1) / kBwdBlock;
-        pl.lane_blocks = blocks < kRemarchLanes / kBwdBlock ? blocks : kRemarchLanes / kBwdBlock;
+        const int64_t most = (wave ? kRemarchLanes : kRemarchLanesAll) / kBwdBlock;
+        pl.lane_blocks = std::min<int64_t>((R + kBwdBlock - 1) / kBwdBlock, most);
+        pl.lane_list = wave ? 0 : static_cast<int>(std::min<int64_t>(kRemarchLaneList, N));
         const size_t lanes = static_cast<size_t>(pl.lane_blocks) * kBwdBlock;
         pl.stacks = take(lanes * (3 * wide_depth + 1) * sizeof(int));
         pl.checkpoints = take(lanes * kBwdCheckpoints * sizeof(float4));
+        pl.lists = take(lanes * 2 * pl.lane_list * sizeof(int));
     }
     pl.bytes = at;
     return pl;

@@ -2,6 +2,8 @@
 around its groups and chunks, feature counts around its instances, lists cut at
 their capacity (traced again by a wave) and hits past the wave's own list
 (re-marched by a lane).  Reference: FP64 autograd over the GPU's own hit lists."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
@@ -176,3 +178,30 @@ def test_cut_lists_of_every_length(mode, n, R):
     hits = check_cut(sc, s, ro, rd, cfg, oracle, 30, 64, n)
     s.close()
     assert hits.max() > 0.8 * n
+
+
+@pytest.mark.parametrize("R", [60, 20_000])
+@pytest.mark.parametrize("n", [480, 512, 513, 700])
+@pytest.mark.parametrize("mode", list(MODES))
+def test_cut_lists_in_a_tree_too_deep_for_a_wave(mode, n, R):
+    """Coincident surfels cluster into a chain (at most three binary levels per
+    wide one, the last 12 surfels in a leaf: more than 150 wide levels, the wave
+    form takes 132): forward and re-march run one lane per ray, its list holding
+    512 hits.  The support is capped at half a scale, so that the boxes are the
+    same whatever the opacity."""
+    g = np.random.Generator(np.random.PCG64(17))
+    base = synth.Surfels(np.zeros((n, 3), np.float32), np.tile(np.float32([1, 0.02, 0.03, 0.01]), (n, 1)),
+                         np.full((n, 2), 0.5, np.float32), g.uniform(0.005, 0.012, n).astype(np.float32),
+                         np.zeros((n, 1), np.float32))
+    d = np.concatenate([g.uniform(-0.05, 0.05, (R, 2)), np.ones((R, 1))], 1)
+    rd = (d / np.linalg.norm(d, axis=1, keepdims=True)).astype(np.float32)
+    ro = (g.uniform(-0.05, 0.05, (R, 3)) - rd).astype(np.float32)
+    rd[30:] *= -1  # away from the surfels
+    sc, s, cfg, oracle = scene_of(base, mode, support_sigma=0.5)
+    assert s.info()["max_depth"] == n - 1
+    got, want = (trace(s, dev(ro[:60]), dev(rd[:60]), dataclasses.replace(cfg, brute_force=b)) for b in (False, True))
+    for name in ("opacity", "feat", "depth", "T", "n_hits"):
+        assert torch.equal(getattr(got, name), getattr(want, name)), name
+    hits = check_cut(sc, s, ro, rd, cfg, oracle, 30, 8, n)
+    s.close()
+    assert hits.min() > 400
