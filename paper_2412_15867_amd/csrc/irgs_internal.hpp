@@ -194,12 +194,14 @@ bool features_offered(int k, int F, bool special);
 // Launches of at most kRemarchSmall rays take the second alone: there all lists
 // can be cut, and twice the launches cost more than the waves.  Rays with more
 // hits go to at most kRemarchLanes lanes.  With a tree too deep for the wave
-// form all go to at most kRemarchLanesAll lanes, each with a list of
-// kRemarchLaneList hits (4,000 rays with few hits each 7.5 -> 3.8 ms by the
-// lists; 200,000 rays of 700 hits 936 -> 359 ms against 16,384 lanes).  Against lists in global memory and a wave per 64 rays to
-// keep them small, all lists cut: 64 / 4,000 rays of 1,500 hits 49.5 / 49.7 ->
-// 0.9 / 1.9 ms, 1M rays of 44 hits 13.9 -> 13.8 ms (18.0 with the long lists
-// alone); none cut, 262,144 rays: 1.29 -> 1.00 ms (68 MB less to allocate).
+// form all go to at most kRemarchLanesAll lanes (fewer where their stacks and
+// lists take more than kRemarchLaneBytes), each with a list of kRemarchLaneList
+// hits (4,000 rays with few hits each 7.5 -> 3.8 ms by the lists; 200,000 rays
+// of 700 hits 936 -> 359 ms against 16,384 lanes).  Against lists in global
+// memory and a wave per 64 rays to keep them small, all lists cut: 64 / 4,000
+// rays of 1,500 hits 49.5 / 49.7 -> 0.9 / 1.9 ms, 1M rays of 44 hits 13.9 ->
+// 13.8 ms (18.0 with the long lists alone); none cut, 262,144 rays: 1.29 ->
+// 1.00 ms (68 MB less to allocate).
 constexpr int kBwdCheckpoints = 16;
 constexpr int kRemarchShort = 1024;
 constexpr int kRemarchList = 2048;
@@ -208,6 +210,7 @@ constexpr int64_t kRemarchWaves = 4096;  // of a launch at most
 constexpr int64_t kRemarchLanes = 16384;
 constexpr int64_t kRemarchLanesAll = 131072;
 constexpr int kRemarchLaneList = 512;
+constexpr size_t kRemarchLaneBytes = size_t(1) << 30;
 // Rays from which on the walk takes them in the order of where they land.
 constexpr int64_t kSortWalkRays = 16384;
 // Byte offsets in the backward's scratch: the interleaved per-surfel

@@ -556,13 +556,20 @@ BackwardPlan plan_backward(int64_t R, int64_t N, int F, int wide_depth, int H_ca
     pl.short_lists = cut && wave && R > kRemarchSmall;
     pl.long_lists = cut && wave && !(pl.short_lists && N <= kRemarchShort);
     if (cut && (!wave || N > kRemarchList)) {
-        const int64_t most = (wave ? kRemarchLanes : kRemarchLanesAll) / kBwdBlock;
-        pl.lane_blocks = std::min<int64_t>((R + kBwdBlock - 1) / kBwdBlock, most);
         pl.lane_list = wave ? 0 : static_cast<int>(std::min<int64_t>(kRemarchLaneList, N));
-        const size_t lanes = static_cast<size_t>(pl.lane_blocks) * kBwdBlock;
-        pl.stacks = take(lanes * (3 * wide_depth + 1) * sizeof(int));
-        pl.checkpoints = take(lanes * kBwdCheckpoints * sizeof(float4));
-        pl.lists = take(lanes * 2 * pl.lane_list * sizeof(int));
+        const size_t stack = (3 * static_cast<size_t>(wide_depth) + 1) * sizeof(int);
+        const size_t checkpoints = kBwdCheckpoints * sizeof(float4);
+        const size_t list = 2 * static_cast<size_t>(pl.lane_list) * sizeof(int);
+        int64_t lanes = kRemarchLanes;
+        if (!wave) {
+            const int64_t fit = static_cast<int64_t>(kRemarchLaneBytes / (stack + checkpoints + list));
+            lanes = std::max(lanes, std::min(kRemarchLanesAll, fit / kBwdBlock * kBwdBlock));
+        }
+        pl.lane_blocks = std::min((R + kBwdBlock - 1) / kBwdBlock, lanes / kBwdBlock);
+        lanes = pl.lane_blocks * kBwdBlock;
+        pl.stacks = take(lanes * stack);
+        pl.checkpoints = take(lanes * checkpoints);
+        pl.lists = take(lanes * list);
     }
     pl.bytes = at;
     return pl;
