@@ -205,3 +205,39 @@ def test_cut_lists_in_a_tree_too_deep_for_a_wave(mode, n, R):
     hits = check_cut(sc, s, ro, rd, cfg, oracle, 30, 8, n)
     s.close()
     assert hits.min() > 400
+
+
+@pytest.mark.parametrize("F,sh", [(8, False), (16, False), (64, False), (48, True)])
+def test_more_surfels_than_the_table_takes(F, sh):
+    """Faint surfels all over a cube: the 64 rays of a block meet about 2,000
+    different ones, several times what its table of sums holds (843 of 1,350
+    slots at F <= 8, fewer with more features) before it is written out, and a
+    step's 768 hits bring more new ones than the slots then left, so that some
+    are added to memory directly."""
+    g = np.random.Generator(np.random.PCG64(23))
+    n, R = 8000, 16_384
+    q = g.normal(size=(n, 4))
+    sc = synth.Surfels(g.uniform(-1, 1, (n, 3)).astype(np.float32), q.astype(np.float32),
+                       g.uniform(0.05, 0.08, (n, 2)).astype(np.float32), g.uniform(0.03, 0.06, n).astype(np.float32),
+                       synth.sh_coefficients(n, 3) if sh else g.uniform(0, 1, (n, F)).astype(np.float32))
+    ro = g.uniform(-1, 1, (R, 3)).astype(np.float32)
+    d = g.uniform(-1, 1, (R, 3)) - ro
+    rd = (d / np.linalg.norm(d, axis=1, keepdims=True)).astype(np.float32)
+    cfg = TraceConfig(k=16, sh=sh)
+    gO, gF, gD, _ = synth.upstream(R, cfg.out_channels(F), seed=3)
+    s = make_scene(sc)
+    res = trace(s, dev(ro), dev(rd), cfg, hit_cap=256)
+    got = trace_backward(s, dev(ro), dev(rd), res, dev(gO), dev(gF), dev(gD), cfg=cfg)
+    got = {a: got[a].cpu().numpy().astype(np.float64) for a, _ in KEYS}
+    hits, ids = res.n_hits.cpu().numpy(), res.hit_ids.cpu().numpy()
+    s.close()
+    assert hits.mean() > 30 and hits.max() <= 256
+    want = None
+    for b in range(0, R, 2048):  # the oracle's memory
+        e = slice(b, b + 2048)
+        lists = np.where(np.arange(256)[None] < hits[e, None], ids[e], -1)[:, :int(hits[e].max())]
+        part = ograd.grad_given_hits(sc.astuple(), ro[e], rd[e], lists, gO[e], gF[e], gD[e], sh_deg=3 if sh else -1)
+        want = part if want is None else {k: want[k] + part[k] for k in part}
+    for a, b in KEYS:
+        x, w = got[a].reshape(want[b].shape), want[b]
+        assert np.all(np.abs(x - w) <= 1e-3 * (np.abs(w) + np.abs(w).mean())), a
