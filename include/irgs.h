@@ -194,9 +194,16 @@ typedef struct {
 } irgs_work;
 
 /* Bytes the library allocates for a scene of n surfels (records, nodes,
- * build scratch), and the per-call scratch of a trace of R rays with the
- * given flags (with IRGS_FLAG_RECOMPUTE: of the backward that traces the
- * rays again). */
+ * build scratch), and the per-call scratch that a trace of R rays with the
+ * given flags takes at most (with IRGS_FLAG_RECOMPUTE: the backward that traces
+ * the rays again).  It is that of a launch with one lane per ray (work counters
+ * asked for, or a tree of more than 132 levels of four: 1,792 bytes per thread,
+ * 524,288 threads at most); other traces take 1 KiB of it, and the sort's.
+ * A backward takes besides, per surfel, 128 ceil((10 + F) / 32) bytes of sums
+ * and 128 of parameters (64 with F > 20); one over stored lists takes those, 8
+ * bytes per ray (32 from 16,384 rays on) and, where a list can have been cut and
+ * a ray can have more than 2,048 hits, 260 + 12 levels bytes for each of at most
+ * 16,384 lanes. */
 size_t irgs_scene_bytes(int64_t n, int32_t F);
 size_t irgs_trace_bytes(int64_t R, int32_t F, uint32_t flags);
 
@@ -244,7 +251,8 @@ irgs_status irgs_trace(irgs_scene scene, const irgs_params* params, int64_t R, c
  * deep that one block's stack overflow does not fit returns IRGS_E_INVALID.
  * IRGS_FLAG_SORT_RAYS needs a per-ray workspace and returns IRGS_E_INVALID.
  * The claim counter is cleared by a fill kernel on `stream` before each
- * launch (no memset node).  Every call on one device shares that device's
+ * launch (no memset node).  A recorded launch holds the tree's shape: record it
+ * again after irgs_scene_build (a refit keeps the shape).  Every call on one device shares that device's
  * array: calls that overlap on one GPU (other streams, other threads) race
  * and give undefined results; order them on one stream. */
 irgs_status irgs_trace_noalloc(irgs_scene scene, const irgs_params* params, int64_t R, const float* ro,
@@ -260,8 +268,8 @@ irgs_status irgs_trace_noalloc(irgs_scene scene, const irgs_params* params, int6
  * re-marches its hits.  Without saved lists (or with IRGS_FLAG_RECOMPUTE)
  * the call traces the rays again, in equal batches whose hit lists (256 per
  * ray) fit a transient 4 GiB workspace, replays those lists and re-marches rays
- * with more hits (by a wave each, up to 2,048 hits; by a lane past that); results are the same either way up to the order of the
- * gradient sums.  Parameters must not have changed since the forward
+ * with more hits (by a wave each, up to 2,048 hits; by a lane past that);
+ * results are the same either way up to the order of the gradient sums.  Parameters must not have changed since the forward
  * trace. */
 irgs_status irgs_trace_backward(irgs_scene scene, const irgs_params* params, int64_t R, const float* ro,
                                 const float* rd, const irgs_out* saved, const irgs_grad_in* grad_in,

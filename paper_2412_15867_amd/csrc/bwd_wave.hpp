@@ -29,10 +29,10 @@
 // With many components the table is what counts: groups of 3 rays leave room
 // for more slots than groups of 16: SH 41.3 -> 36.8 ms, 262,144 SH rays of 1,024
 // pixels 4.1 -> 2.8 ms; 24 and 64 features, groups of 8 -> 3, 10.0 -> 9.5 and
-// 15.2 -> 14.3 ms; 8 and 16 features lose or are level.  What bounds it: F = 8
-// the steps' own work (VALU 35%, 135M atomic requests of 64 bytes against 188M
-// hits); SH the atomics (472M before the groups of 3: they are done in memory,
-// 11 per ns).
+// 15.2 -> 14.3 ms; 8 and 16 features lose or are level.  Keeping the rays apart
+// by selection costs 0.14 ms at F = 8.  What bounds it: F = 8 the steps' own work
+// (VALU 34%, 120M atomic requests against 183M hits); SH the atomics (401M for
+// 4.2M rays, 28M for 262,144: they are done in memory, 11 per ns).
 #pragma once
 
 #include "irgs_internal.hpp"
@@ -53,7 +53,7 @@ struct WalkShape {
     static constexpr int comps = 10 + FM;
     static constexpr int per_wave = (comps + waves - 1) / waves;  // components a wave adds
     static constexpr int stride = slots | 1;      // words between components: odd, so a row's lie in different banks
-    static constexpr int fill = slots * 7 / 8;    // no new keys past this many
+    static constexpr int fill = slots * 7 / 8;    // a step that starts past this many adds no new keys (others until none is free)
     static constexpr int flush = slots * 5 / 8;   // written out when it holds more
 };
 

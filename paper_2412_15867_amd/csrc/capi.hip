@@ -447,9 +447,10 @@ size_t irgs_trace_bytes(int64_t R, int32_t F, uint32_t flags)
 {
     if (R <= 0) return 0;
     const size_t thr = static_cast<size_t>(trace_threads(R));
-    size_t b = thr * (64 + 2 * kDeferCap) * sizeof(int) + kClaimBytes;  // stack overflow, deferred lists
+    // the lane form's stack overflow and deferred lists (the wave form: claim counters alone)
+    size_t b = thr * (64 + 2 * kDeferCap) * sizeof(int) + kClaimBytes;
     if (flags & IRGS_FLAG_SORT_RAYS) b += ray_sort_words(R) * sizeof(float);
-    if (flags & IRGS_FLAG_RECOMPUTE) {  // the backward's retrace: one batch of lists, its checkpoints
+    if (flags & IRGS_FLAG_RECOMPUTE) {  // the backward's retrace: one batch of lists, its own scratch but for the surfels'
         const int fo = (flags & IRGS_FLAG_SH) ? 3 : F;
         const size_t per_ray = static_cast<size_t>(kRetraceCap) * 8 + (3 + fo) * sizeof(float);
         const int64_t bmax = std::max<int64_t>(1, static_cast<int64_t>(kRetraceBytes / per_ray));
@@ -457,7 +458,7 @@ size_t irgs_trace_bytes(int64_t R, int32_t F, uint32_t flags)
         b += static_cast<size_t>((R + nb - 1) / nb) * per_ray +
              plan_backward((R + nb - 1) / nb, kRemarchList + 1, F, 64, kRetraceCap).bytes;
     }
-    return b;  // plus, for a backward, 4 * (ceil32(10 + F) + ceil32(12 + F)) bytes per surfel
+    return b;  // plus, for a backward, 4 * (grad_stride(F) + pack_stride(F)) bytes per surfel
 }
 
 irgs_status irgs_scene_create(int64_t n, int32_t F, const irgs_surfels* params, irgs_scene* out)

@@ -56,7 +56,7 @@ struct __align__(16) BvhNode {
 struct __align__(16) WideChild {
     float c2[3], ext[3];
     int32_t ref;
-    uint32_t slab;  // a slab that holds the child's discs (see slab_span)
+    uint32_t slab;  // a slab that holds the child's discs (see Slab, child_span)
 };
 struct __align__(128) WideNode {
     WideChild c[4];

@@ -150,7 +150,7 @@ __global__ __launch_bounds__(kSortThreads) void k_radix_hist(int n, int shift, c
 
 // Exclusive scan of `len` counters in place.  Blocks of kScanSpan counters:
 // their sums first, then every block scans its span from the sum of the
-// blocks before it (which it adds up itself: at most a few thousand sums).  A
+// blocks before it (which it adds up itself: 128 for 4.2M rays, 65,536 at most).  A
 // single block over everything took 0.8 ms for the 524,288 tile counters of a
 // sort of 4.2M rays, four times per sort; these two launches take 8 us.
 constexpr int kScanThreads = 256;

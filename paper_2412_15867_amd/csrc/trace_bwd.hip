@@ -16,8 +16,9 @@
 // transmittance before each hit) and walked by bwd_wave.hpp.  A ray whose list
 // was cut is traced again by one wave; what does not fit that wave's list
 // either (or a tree its stack does not take) is re-marched by one lane: a first
-// pass records the state at the start of k-buffer rounds, a second re-collects
-// the rounds last to first and walks each one back to front.
+// pass lists the hits and records the state at the start of k-buffer rounds, a
+// second walks the list back to front or, where it does not hold them,
+// re-collects the rounds last to first and walks each one.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

@@ -353,7 +353,7 @@ __device__ __forceinline__ void trace_flat(const Source& src, unsigned long long
                 for (int c = 0; c < 4; ++c) {
                     ref[c] = w[c].ref;
                     child_span(w[c], ray, q, lo, tmax_c, &tn[c], &tf[c]);
-                    // an empty slot has an all +inf box, which is never crossed
+                    // an empty slot's extent is -inf, which is never crossed
                     const bool crossed = tn[c] <= tf[c];
                     const bool inside = crossed && tn[c] <= hi;
                     if (crossed && !inside) dq.put(ref[c]);  // beyond this round's K-th key

@@ -21,9 +21,9 @@
 // A round whose buffer let hits go and whose transmittance stays above the
 // cutoff is followed by another from the top, after the last complete key.
 //
-// What bounds it: VALU issue (1M surfels, 4.2M rays: 2,740 VALU and 990 scalar
-// instructions per ray, a VALU instruction in every issue slot of 4 cycles; 68%
-// L2 hits, 18.7 KB per ray past L2).  Against one ray per lane, whose waves
+// What bounds it: VALU issue (1M surfels, 4.2M rays: 2,712 VALU and 978 scalar
+// instructions per ray, a VALU instruction per SIMD every 3.3 cycles; 68% L2
+// hits, 18.7 KB per ray past L2).  Against one ray per lane, whose waves
 // stepped through 1,230 dependent iterations with 45% of their lanes active:
 // 1M surfels, 4.2M rays 70.3 -> 34.4 ms; 200K surfels 36.6 -> 11.9 ms; launches
 // smaller than the chip, whose time is one ray's chain of round trips: 4,096
