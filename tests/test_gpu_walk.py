@@ -209,9 +209,9 @@ def test_cut_lists_in_a_tree_too_deep_for_a_wave(mode, n, R):
 
 @pytest.mark.parametrize("F,sh", [(8, False), (16, False), (64, False), (48, True)])
 def test_more_surfels_than_the_table_takes(F, sh):
-    """Faint surfels all over a cube: the 64 rays of a block meet about 2,000
-    different ones, several times what its table of sums holds (843 of 1,350
-    slots at F <= 8, fewer with more features) before it is written out, and a
+    """Faint surfels all over a cube: the 64 rays of a block meet about 1,500
+    different ones, twice what its table of sums holds (843 of 1,350 slots at
+    F <= 8, 218 of 350 with 64 features) before it is written out, and a
     step's 768 hits bring more new ones than the slots then left, so that some
     are added to memory directly."""
     g = np.random.Generator(np.random.PCG64(23))
